@@ -203,6 +203,7 @@ struct dmrg_hop {
     int tune_lds64_task_route = 0;              // 1: a target within its tiles keeps the tasks whose source fits
                                                 // them (larger sources: two-pass or one-wave path); 0: a
                                                 // target with any larger source leaves it entirely
+    int tune_rs64 = 7;                          // launch groups (bits) of the register-streamed kernel in use
     dmrg::LdsPlan64 lplan64{};
     std::vector<void*> plan_allocations;   // freed when the plan is rebuilt
     int64_t dev_bytes = 0, plan_bytes = 0; // device memory held (handle lifetime / current plan)

@@ -777,6 +777,7 @@ extern "C" dmrg_status dmrg_build_blocks(const dmrg_problem* p, const dmrg_block
         if (const char* e = std::getenv("DMRG_BIG64")) H->tune_big64 = std::max(0, std::min(2, std::atoi(e)));
         if (const char* e = std::getenv("DMRG_LDS64")) H->tune_lds64 = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_ITEMS")) H->tune_lds64_items = std::max(64, std::atoi(e));
+        if (const char* e = std::getenv("DMRG_RS64")) H->tune_rs64 = std::atoi(e) & 7;
         if (const char* e = std::getenv("DMRG_LDS64_SMALL")) H->tune_lds64_small = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_W7")) H->tune_lds64_w7 = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_CW")) H->tune_lds64_cw = std::atoi(e) != 0;
@@ -1099,6 +1100,7 @@ extern "C" dmrg_status dmrg_hop_combine(dmrg_hop* const* hops, int32_t n, void* 
         }
         C->tune_big64 = hops[0]->tune_big64;
         C->tune_lds64 = hops[0]->tune_lds64;
+        C->tune_rs64 = hops[0]->tune_rs64;
         C->tune_lds64_items = hops[0]->tune_lds64_items;
         C->tune_lds64_small = hops[0]->tune_lds64_small;
         C->tune_lds64_w7 = hops[0]->tune_lds64_w7;

@@ -63,8 +63,8 @@ __device__ __forceinline__ TD load_td(const LTask64* __restrict__ p) {
     d.f = unid(p->f);
     d.pa16 = uni(p->pa16);
     d.pd16 = uni(p->pd16);
-    d.ka16 = uni(p->ka16);
-    d.kd16 = uni(p->kd16);
+    d.ka16 = (uni(p->ka4) + 3) >> 2;
+    d.kd16 = (uni(p->kd4) + 3) >> 2;
     return d;
 }
 
@@ -310,6 +310,7 @@ __global__ __launch_bounds__((W + CW) * 64, MINW) void k_hpsi_lds64(const Item* 
 hipError_t launch_hpsi_lds64(const LdsPlan64& P, const double* pool_t, const double* xt, double* y, hipStream_t s,
                              const int32_t* active) {
     if (P.n_items == 0) return hipSuccess;
+    if (const hipError_t e = launch_hpsi_rs64(P.rs, P.tasks, pool_t, xt, y, P.partial, s, active); e != hipSuccess) return e;
     for (int c = 0; c < kLds64Classes; ++c) {
         const int b = P.cls_begin[c], n = P.cls_begin[c + 1] - b;
         if (n <= 0) continue;

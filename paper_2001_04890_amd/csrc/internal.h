@@ -198,9 +198,22 @@ constexpr int kLds64MaxTiles = 7;       // target rows / columns and source rows
 struct LTask64 {
     int64_t x_off, a_off, b_off;
     double  f;
-    int16_t pa16, pd16;      // source rows / columns padded to 32, in 16-wide tiles (tile strides)
-    int16_t ka16, kd16;      // source rows / columns padded to 16: the k tiles and j tiles that hold
-                             // data (the others are zero padding and are skipped)
+    int32_t pa16, pd16;      // source rows / columns padded to 32, in 16-wide tiles (tile strides)
+    int32_t ka4, kd4;        // 4-wide k steps of the source rows / columns that hold data (the rest of
+                             // the padding is skipped; 16-wide tiles: rounded up)
+};
+// Items of the register-streamed FP64 kernel (hpsi_rs64.hip), one wavefront each: r0 = 16 x the row
+// tile, c0 = the class, 8 * k + q with the indices of its source-row and target-column tiles in
+// kRsSizes. begin[g] .. begin[g + 1]: the items of launch group g (register budgets, see there).
+constexpr int kRsWaves = 4;             // wavefronts (items) per workgroup
+constexpr int kRsGroups = 3;
+constexpr int kRsSizes[6] = {1, 2, 3, 4, 6, 8};
+constexpr int kRsMaxTiles = 8;
+inline int rs_class(int tiles) { int c = 0; while (kRsSizes[c] < tiles) ++c; return c; }
+inline int rs_group(int k, int q) { const int m = k > q ? k : q; return m <= 1 ? 0 : m <= 2 ? 1 : 2; }
+struct RsPlan64 {
+    const Item* items = nullptr;        // device
+    int begin[kRsGroups + 1] = {0, 0, 0, 0};
 };
 struct LdsPlan64 {
     const Item* items = nullptr;        // device
@@ -215,11 +228,16 @@ struct LdsPlan64 {
     int w7_min_waves = 1;               // 4: the (7, 7, 7) class held to 128 VGPRs (two workgroups per CU)
     int copy_wave = 1;                  // 1: one more wavefront per workgroup issues every LDS copy
     int three_slots = 0;                // with the copy wavefront: the KT = 2 classes stage two steps ahead
+    RsPlan64 rs;                        // items of the register-streamed kernel over the same tasks, partial
+                                        // tiles and reductions
 };
 // y (one vector) += the plan's targets of f A X B^T; xt = that vector's tiled FP64 X^T
 // (launch_pack_xt64 with the FP64 packing geometry)
 hipError_t launch_hpsi_lds64(const LdsPlan64& P, const double* pool_t, const double* xt, double* y, hipStream_t s,
                              const int32_t* active = nullptr);
+// the register-streamed items of the same plan (launched by launch_hpsi_lds64 before its reductions)
+hipError_t launch_hpsi_rs64(const RsPlan64& P, const LTask64* tasks, const double* pool_t, const double* xt, double* y,
+                            double* partial, hipStream_t s, const int32_t* active = nullptr);
 // tiled FP64 X^T of every psi block (hpsi_big64.hip)
 hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x, double* xt, hipStream_t s);
 // y (one vector) += the partial tiles of each record, in order (hpsi_lds.hip)

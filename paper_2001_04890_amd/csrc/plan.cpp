@@ -789,6 +789,9 @@ void drop_graphs(dmrg_hop& H) {
 
 namespace {
 
+// Widest target or source of the FP64 kernels for small and middle sectors, in 16-wide tiles.
+int lds64_tiles(const dmrg_hop& H) { return H.tune_rs64 >> (dmrg::kRsGroups - 1) & 1 ? dmrg::kRsMaxTiles : dmrg::kLds64MaxTiles; }
+
 // Targets whose own or some source's dimension exceeds `limit` (the 96-wide LDS stages of the split
 // kernel; 112 for the FP64 LDS-staged kernel).
 std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
@@ -808,7 +811,7 @@ std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
 // Tasks already taken by the FP64 LDS-staged kernel (lds_task) are left out of the comparison.
 std::vector<char> fp64_big_targets(const dmrg_hop& H, int mode, const std::vector<char>* lds_task) {
     // with the LDS-staged kernel on, targets within its 112 x 112 tiles are its own
-    std::vector<char> big = large_targets(H, H.tune_lds64 ? 16 * dmrg::kLds64MaxTiles : 96);
+    std::vector<char> big = large_targets(H, H.tune_lds64 ? 16 * lds64_tiles(H) : 96);
     if (mode == 2) return big;
     auto up = [](double m, double q) { return std::ceil(m / q) * q; };
     std::vector<double> c_big(H.blk.size(), 0.0), c_one(H.blk.size(), 0.0);
@@ -898,23 +901,28 @@ void build_lds64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large
     };
     // MFMA instructions of one wavefront (per source column tile: GEMM1 over ka16 k tiles, GEMM2 over
     // tq column tiles) + per-step and per-task overhead
-    auto cost = [](const dmrg::LTask64& L, int tq) { return L.kd16 * (4.0 * (L.ka16 + tq) + 6.0) + 4.0; };
-    struct Run { int j, cls, tq; int32_t tb, te; };
+    auto k16 = [](int k4) { return (k4 + 3) / 4; };
+    auto cost = [&](const dmrg::LTask64& L, int tq) { return k16(L.kd4) * (4.0 * (k16(L.ka4) + tq) + 6.0) + 4.0; };
+    // the same of the register-streamed kernel, which runs the k steps that hold data only
+    auto rs_cost = [&](const dmrg::LTask64& L, int tq) {
+        return k16(L.kd4) * (L.ka4 + 4.0) + (double)L.kd4 * tq + 4.0;
+    };
+    struct Run { int j, cls, tq, rs; int32_t tb, te; };   // rs: class of the register-streamed kernel or -1
     std::vector<dmrg::LTask64> lt;
     lt.reserve(H.tasks.size());
     std::vector<Run> runs;
-    CostCaps caps(H);
+    CostCaps caps(H), rs_caps(H);
     size_t k = 0;
     for (size_t j = 0; j < nb; ++j) {
         const size_t kb = k;
         while (k < H.tasks.size() && H.tasks[k].j == (int)j) ++k;
         if (k == kb || large[j]) continue;
         const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16, tq = dmrg::rows_of(H.blk_md[j]) / 16;
-        constexpr int kMax = dmrg::kLds64MaxTiles;
-        if (nrt > kMax || tq > kMax) throw Error(DMRG_ERR_ARG, "internal: FP64 LDS target beyond 112 x 112");
+        const int kMax = lds64_tiles(H);
+        if (nrt > kMax || tq > kMax) throw Error(DMRG_ERR_ARG, "internal: FP64 LDS target beyond its tiles");
         const bool wide = nrt > 6 || tq > 6;      // the (7, 7, 7) class takes every task of the target
         const int qcls = tq <= 3 ? 0 : 1;
-        std::vector<dmrg::LTask64> v2, v6, v7;
+        std::vector<dmrg::LTask64> v[3 + 6];      // LDS-staged: KT = 2, 6, 7; register-streamed: by kRsSizes
         for (size_t t = kb; t < k; ++t) {
             const auto& ht = H.tasks[t];
             const int a = H.blk[ht.i][0], d = H.blk[ht.i][3];
@@ -928,67 +936,110 @@ void build_lds64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large
             L.b_off = ht.rm >= 0 ? H.mats[ht.rm].pool_of_in[d] : ident(pd);
             if (L.a_off < 0 || L.b_off < 0) throw Error(DMRG_ERR_ARG, "internal: operator block missing from the pool");
             L.f = ht.f;
-            L.pa16 = (int16_t)(pa / 16);
-            L.pd16 = (int16_t)(pd / 16);
-            L.ka16 = (int16_t)((H.blk_ma[ht.i] + 15) / 16);
-            L.kd16 = (int16_t)((H.blk_md[ht.i] + 15) / 16);
-            if (L.ka16 > kMax || L.kd16 > kMax || L.x_off + (int64_t)pa * pd > psize)
-                throw Error(DMRG_ERR_ARG, "internal: FP64 LDS task beyond 112-wide sources");
+            L.pa16 = pa / 16;
+            L.pd16 = pd / 16;
+            L.ka4 = (H.blk_ma[ht.i] + 3) / 4;
+            L.kd4 = (H.blk_md[ht.i] + 3) / 4;
+            const int ka16 = k16(L.ka4);
+            if (ka16 > kMax || k16(L.kd4) > kMax || L.x_off + (int64_t)pa * pd > psize)
+                throw Error(DMRG_ERR_ARG, "internal: FP64 LDS task beyond its sources");
             check(L.a_off, nrt, L.pa16);
             check(L.b_off, tq, L.pd16);
-            (wide || L.ka16 > 6 ? v7 : L.ka16 <= 2 ? v2 : v6).push_back(L);
+            const int kc = dmrg::rs_class(ka16);
+            const bool rs = (H.tune_rs64 >> dmrg::rs_group(kc, dmrg::rs_class(tq))) & 1;
+            v[rs ? 3 + kc : wide || ka16 > 6 ? 2 : ka16 <= 2 ? 0 : 1].push_back(L);
         }
-        for (int kc : {0, 1, 2}) {
-            const auto& v = kc == 0 ? v2 : kc == 1 ? v6 : v7;
-            if (v.empty()) continue;
-            Run R{(int)j, kc == 2 ? 4 : 2 * kc + qcls, tq, (int32_t)lt.size(), 0};
-            for (const auto& L : v) {
+        for (int kc = 0; kc < 9; ++kc) {
+            if (v[kc].empty()) continue;
+            const bool rs = kc >= 3;
+            const int size = rs ? dmrg::kRsSizes[kc - 3] : 0;
+            const int lc = rs ? (wide || size > 6 ? 2 : size <= 2 ? 0 : 1) : kc;   // stage-size bucket (trace)
+            Run R{(int)j, lc == 2 ? 4 : 2 * lc + qcls, tq, rs ? 8 * (kc - 3) + dmrg::rs_class(tq) : -1, (int32_t)lt.size(), 0};
+            for (const auto& L : v[kc]) {
                 lt.push_back(L);
-                caps.add((int)j, cost(L, tq));
+                if (rs) rs_caps.add((int)j, rs_cost(L, tq) * nrt);
+                else caps.add((int)j, cost(L, tq));
             }
             R.te = (int32_t)lt.size();
             runs.push_back(R);
         }
     }
     H.lplan64 = dmrg::LdsPlan64{};
-    struct It { dmrg::Item item; double cost; int cls; };
-    std::vector<It> its;
+    struct It { dmrg::Item item; double cost; int cls, rs; };
+    std::vector<It> its, rs_its;
     std::vector<dmrg::Reduce> reds;
     int64_t part = 0;
     int most = 1;
+    auto put = [&](const It& x) { (x.rs >= 0 ? rs_its : its).push_back(x); };
     // the runs of one target (one per stage size) are consecutive; all their chunks share one
     // reduction record, so that no two records of the one reduction launch add into the same tile
     for (size_t r0 = 0, r1; r0 < runs.size(); r0 = r1) {
         r1 = r0;
         while (r1 < runs.size() && runs[r1].j == runs[r0].j) ++r1;
-        struct Chunk { int32_t b, e; double cost; int cls; };
+        struct Chunk { int32_t b, e; double cost; int cls, rs; };
         std::vector<Chunk> chunks;
         for (size_t r = r0; r < r1; ++r) {
             const Run& R = runs[r];
             int32_t b = R.tb;
             double c = 0.0;
-            const double cmax = caps.cap(R.j, H.tune_lds64_items, 200.0);
+            const double cmax = R.rs >= 0 ? rs_caps.cap(R.j, H.tune_lds64_items, 64.0) : caps.cap(R.j, H.tune_lds64_items, 200.0);
             for (int32_t t = R.tb; t < R.te; ++t) {
-                const double tc = cost(lt[t], R.tq);
-                if (c + tc > cmax && t > b) { chunks.push_back({b, t, c, R.cls}); b = t; c = 0.0; }
+                const double tc = R.rs >= 0 ? rs_cost(lt[t], R.tq) : cost(lt[t], R.tq);
+                if (c + tc > cmax && t > b) { chunks.push_back({b, t, c, R.cls, R.rs}); b = t; c = 0.0; }
                 c += tc;
             }
-            chunks.push_back({b, R.te, c, R.cls});
+            chunks.push_back({b, R.te, c, R.cls, R.rs});
         }
         const int j = runs[r0].j, tm = dmrg::rows_of(H.blk_ma[j]), tn = 16 * runs[r0].tq;
         if (chunks.size() == 1) {
             const Chunk& q = chunks[0];
-            its.push_back({{H.blk_off[j], -1, H.blk_ma[j], H.blk_md[j], 0, 0, q.b, q.e}, q.cost, q.cls});
+            put({{H.blk_off[j], -1, H.blk_ma[j], H.blk_md[j], 0, 0, q.b, q.e}, q.cost, q.cls, q.rs});
             continue;
         }
         reds.push_back({H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 0, 0, tm, tn, (int32_t)chunks.size(), 0});
         most = std::max(most, tm * tn);
         for (const Chunk& q : chunks) {
-            its.push_back({{H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 0, 0, q.b, q.e}, q.cost, q.cls});
+            put({{H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 0, 0, q.b, q.e}, q.cost, q.cls, q.rs});
             part += (int64_t)tm * tn;
         }
     }
-    // launch order: class, then heaviest item first
+    // register-streamed items: per launch group, the chunks (heaviest first) are dealt to the XCDs by
+    // load; a chunk's row tiles follow one another in its XCD's workgroups and share the tiles they read
+    // in that XCD's caches. Workgroup b runs on XCD b % 8.
+    std::stable_sort(rs_its.begin(), rs_its.end(), [](const It& a, const It& b) { return a.cost > b.cost; });
+    int bucket[dmrg::kLds64Classes] = {0};
+    std::vector<dmrg::Item> rs_items;
+    for (int g = 0; g < dmrg::kRsGroups; ++g) {
+        constexpr int kXcds = 8;
+        std::vector<dmrg::Item> list[kXcds];
+        double load[kXcds] = {0.0};
+        for (const It& x : rs_its) {
+            if (dmrg::rs_group(x.rs / 8, x.rs % 8) != g) continue;
+            bucket[x.cls]++;
+            const int to = (int)(std::min_element(load, load + kXcds) - load);
+            for (int rt = 0; rt < dmrg::rows_of(x.item.m_ap) / 16; ++rt) {
+                dmrg::Item it = x.item;
+                it.r0 = 16 * rt;
+                it.c0 = x.rs;
+                list[to].push_back(it);
+                load[to] += x.cost;
+            }
+        }
+        size_t wgs = 0;
+        for (const auto& v : list) wgs = std::max(wgs, (v.size() + dmrg::kRsWaves - 1) / dmrg::kRsWaves);
+        dmrg::Item none{};
+        none.part_off = -1;                      // t_begin == t_end: no work
+        for (size_t w = 0; w < wgs; ++w)
+            for (const auto& v : list)
+                for (size_t i = w * dmrg::kRsWaves; i < (w + 1) * dmrg::kRsWaves; ++i) rs_items.push_back(i < v.size() ? v[i] : none);
+        H.lplan64.rs.begin[g + 1] = (int)rs_items.size();
+    }
+    tag_parts(H, rs_items);
+    dmrg::Item* d_rs = plan_alloc<dmrg::Item>(H, rs_items.size());
+    if (!rs_items.empty())
+        HIPCHK(hipMemcpyAsync(d_rs, rs_items.data(), rs_items.size() * sizeof(dmrg::Item), hipMemcpyHostToDevice, s));
+    H.lplan64.rs.items = d_rs;
+    // LDS-staged items: class, then heaviest item first
     std::stable_sort(its.begin(), its.end(), [](const It& a, const It& b) {
         if (a.cls != b.cls) return a.cls < b.cls;
         return a.cost > b.cost;
@@ -1014,15 +1065,17 @@ void build_lds64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large
     H.lplan64.red_chunks = (most + 255) / 256;
     H.lplan64.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part, 1));
     H.lplan64.partial_size = part;
-    H.lplan64.n_items = (int)items.size();
+    H.lplan64.n_items = (int)(items.size() + rs_its.size());
     H.lplan64.w7_min_waves = H.tune_lds64_w7 ? 4 : 1;
     H.lplan64.copy_wave = H.tune_lds64_cw;
     H.lplan64.three_slots = H.tune_lds64_ns3;
     if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
         if (e[0] == '1') {
-            std::fprintf(stderr, "[dmrg lds64 plan] items %zu classes", items.size());
-            for (int c = 0; c < dmrg::kLds64Classes; ++c) std::fprintf(stderr, " %d", cnt[c]);
-            std::fprintf(stderr, " reduces %zu partial %.1f MB\n", reds.size(), part * 8e-6);
+            std::fprintf(stderr, "[dmrg lds64 plan] items %d classes", H.lplan64.n_items);
+            for (int c = 0; c < dmrg::kLds64Classes; ++c) std::fprintf(stderr, " %d", cnt[c] + bucket[c]);
+            std::fprintf(stderr, " reduces %zu partial %.1f MB register-streamed wavefronts", reds.size(), part * 8e-6);
+            for (int g = 0; g < dmrg::kRsGroups; ++g) std::fprintf(stderr, " %d", H.lplan64.rs.begin[g + 1] - H.lplan64.rs.begin[g]);
+            std::fprintf(stderr, "\n");
         }
     HIPCHK(hipStreamSynchronize(s));
 }
@@ -1049,9 +1102,9 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
         // the LDS-staged kernel takes the targets within its 112 x 112 tiles: with task routing every
         // task of such a target whose source fits too, otherwise only targets whose sources all fit
         make_tiled_f64(H, s);
-        std::vector<char> lds_large = large_targets(H, 16 * dmrg::kLds64MaxTiles);
+        std::vector<char> lds_large = large_targets(H, 16 * lds64_tiles(H));
         if (H.tune_lds64_task_route)
-            for (size_t j = 0; j < nb; ++j) lds_large[j] = std::max(H.blk_ma[j], H.blk_md[j]) > 16 * dmrg::kLds64MaxTiles;
+            for (size_t j = 0; j < nb; ++j) lds_large[j] = std::max(H.blk_ma[j], H.blk_md[j]) > 16 * lds64_tiles(H);
         build_lds64_plan(H, s, lds_large, lds64);
         for (char b : lds64) any_lds |= b != 0;
     }
