@@ -54,6 +54,7 @@ struct MatDef {
     // materialized:
     std::vector<int> out_of_in;
     std::vector<int64_t> pool_of_in;
+    std::vector<int64_t> op64_of_in;  // the same blocks in the FP64 operand pool (make_op64)
     double bytes = 0.0;             // padded pool bytes of all its sector blocks
 };
 
@@ -185,26 +186,25 @@ struct dmrg_hop {
                                                 // the whole target to the two-pass path
     // FP64 two-pass path (hpsi_big64.hip) for the same large targets
     int tune_big64 = 1;                         // FP64 two-pass path: 0 off, 1 where cheaper, 2 every target above 96
-    double* d_tiled64 = nullptr;                // FP64 tiled operators + identity blocks (made on first use)
-    int64_t tiled64_size = 0;
-    std::vector<int64_t> ident64_off;           // FP64 tiled identity block of size 32 (k + 1)
+    double* d_op64 = nullptr;                   // FP64 operand pool + zeros + identity blocks (made on first use)
+    int64_t op64_len = 0;
+    int64_t zeros64_off = 0;                    // 1 KB of zeros in it
+    std::vector<int64_t> ident64_off;           // identity block by 4-row groups, or -1
+    std::vector<int64_t> xt64_off;              // X^T of every psi block in xt64
+    const dmrg::PackBlock* packs64 = nullptr;   // its packing (plan allocation)
+    int n_packs64 = 0;
     dmrg::BigPlan bplan64{};
     std::vector<dmrg::BigChunk> big_chunks64;
-    double* xt64 = nullptr;                     // FP64 tiled X^T of one vector (plan allocation)
-    // FP64 LDS-staged kernel (hpsi_lds64.hip) for the targets within the 96-wide stages
+    double* xt64 = nullptr;                     // X^T of one vector in FP64 operand form (plan allocation)
+    // register-streamed FP64 kernel (hpsi_rs64.hip) for targets and sources within 128 x 128
     int tune_lds64 = 1;                         // 0: those targets take the one-wave kernel
-    int tune_lds64_items = 32768;               // target number of its work items per H.psi
+    int tune_lds64_items = 32768;               // target number of its wavefronts per H.psi
     int tune_lds64_small = 1;                   // 1: it also takes tasks whose source is one 32 x 32 tile
                                                 // (0: those run in the one-wave kernel)
-    int tune_lds64_w7 = 1;                      // 1: its 7-wavefront class held to 128 VGPRs (two per CU)
-    int tune_lds64_cw = 1;                      // 1: a copy wavefront per workgroup issues every LDS copy
-    int tune_lds64_ns3 = 0;                     // 1: its KT = 2 classes keep three LDS slots (copies two steps
-                                                // ahead; measured no faster at L = 24, M = 1024)
     int tune_lds64_task_route = 0;              // 1: a target within its tiles keeps the tasks whose source fits
                                                 // them (larger sources: two-pass or one-wave path); 0: a
                                                 // target with any larger source leaves it entirely
-    int tune_rs64 = 7;                          // launch groups (bits) of the register-streamed kernel in use
-    dmrg::LdsPlan64 lplan64{};
+    dmrg::RsPlan64 rplan64{};
     std::vector<void*> plan_allocations;   // freed when the plan is rebuilt
     int64_t dev_bytes = 0, plan_bytes = 0; // device memory held (handle lifetime / current plan)
     int vec_step = 1;                      // vectors per launch sequence (packed-input and partial buffers)

@@ -529,7 +529,7 @@ void upload(dmrg_hop& H, const dmrg_build_opts* opts) {
     H.pool_blocks.clear();
     auto reserve = [&](int rows, int cols) {
         int64_t o = pool;
-        H.pool_blocks.push_back({o, dmrg::rows_of(rows) / 16, dmrg::ld_of(cols) / 32});
+        H.pool_blocks.push_back({o, dmrg::rows_of(rows) / 16, dmrg::ld_of(cols) / 32, rows, cols});
         pool += (int64_t)dmrg::rows_of(rows) * dmrg::ld_of(cols);
         pool = (pool + 31) / 32 * 32;
         return o;
@@ -777,11 +777,7 @@ extern "C" dmrg_status dmrg_build_blocks(const dmrg_problem* p, const dmrg_block
         if (const char* e = std::getenv("DMRG_BIG64")) H->tune_big64 = std::max(0, std::min(2, std::atoi(e)));
         if (const char* e = std::getenv("DMRG_LDS64")) H->tune_lds64 = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_ITEMS")) H->tune_lds64_items = std::max(64, std::atoi(e));
-        if (const char* e = std::getenv("DMRG_RS64")) H->tune_rs64 = std::atoi(e) & 7;
         if (const char* e = std::getenv("DMRG_LDS64_SMALL")) H->tune_lds64_small = std::atoi(e) != 0;
-        if (const char* e = std::getenv("DMRG_LDS64_W7")) H->tune_lds64_w7 = std::atoi(e) != 0;
-        if (const char* e = std::getenv("DMRG_LDS64_CW")) H->tune_lds64_cw = std::atoi(e) != 0;
-        if (const char* e = std::getenv("DMRG_LDS64_NS3")) H->tune_lds64_ns3 = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_TASK_ROUTE")) H->tune_lds64_task_route = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS_CW")) H->tune_lds_cw = std::atoi(e) & 0xF;
         if (const char* e = std::getenv("DMRG_SPLIT_TASK_ROUTE")) H->tune_split_task_route = std::atoi(e) != 0;
@@ -908,13 +904,13 @@ void enqueue_hpsi(dmrg_hop* H, const double* x, double* y, int32_t nvec, int32_t
         if (precision == DMRG_PREC_FP64) {
             // zeroes y, then the one-wave targets
             HIPCHK(dmrg::launch_hpsi_f64(H->plan, H->d_pool, xv, yv, H->n_coeff, nv, s, act));
-            const bool lds = H->lplan64.n_items > 0, big = H->bplan64.n_chunks > 0;
-            for (int v = 0; v < nv && (lds || big); ++v) {
+            const bool rs = H->rplan64.n_items > 0, big = H->bplan64.n_chunks > 0;
+            for (int v = 0; v < nv && (rs || big); ++v) {
                 const double* x1 = xv + (int64_t)v * H->n_coeff;
                 double* y1 = yv + (int64_t)v * H->n_coeff;
-                HIPCHK(dmrg::launch_pack_xt64(H->plan.packs, H->plan.n_packs, x1, H->xt64, s));
-                if (lds) HIPCHK(dmrg::launch_hpsi_lds64(H->lplan64, H->d_tiled64, H->xt64, y1, s, act));
-                if (big) HIPCHK(dmrg::launch_hpsi_big64(H->bplan64, H->d_tiled64, nullptr, 0, x1, H->xt64, y1, s, act));
+                HIPCHK(dmrg::launch_pack_xt64(H->packs64, H->n_packs64, x1, H->xt64, s));
+                if (rs) HIPCHK(dmrg::launch_hpsi_rs64(H->rplan64, H->d_op64, H->xt64, y1, s, act));
+                if (big) HIPCHK(dmrg::launch_hpsi_big64(H->bplan64, H->d_op64, H->xt64, y1, s, act));
             }
         } else {
             HIPCHK(dmrg::launch_hpsi_lds(H->lplan, H->d_tiled, xv, yv, H->n_coeff, nv, true, s, act));
@@ -1071,7 +1067,7 @@ extern "C" dmrg_status dmrg_hop_combine(dmrg_hop* const* hops, int32_t n, void* 
             for (const auto& t : h.tasks)
                 C->tasks.push_back({t.i + blk_base, t.j + blk_base, t.lm >= 0 ? t.lm + mat_base : -1,
                                     t.rm >= 0 ? t.rm + mat_base : -1, t.f});
-            for (const auto& pb : h.pool_blocks) C->pool_blocks.push_back({pb.off + pool_base, pb.r16, pb.k32});
+            for (const auto& pb : h.pool_blocks) C->pool_blocks.push_back({pb.off + pool_base, pb.r16, pb.k32, pb.rows, pb.cols});
             C->n_coeff += h.n_coeff;
             C->pool_size += h.pool_size;
             C->flops += h.flops;
@@ -1100,12 +1096,8 @@ extern "C" dmrg_status dmrg_hop_combine(dmrg_hop* const* hops, int32_t n, void* 
         }
         C->tune_big64 = hops[0]->tune_big64;
         C->tune_lds64 = hops[0]->tune_lds64;
-        C->tune_rs64 = hops[0]->tune_rs64;
         C->tune_lds64_items = hops[0]->tune_lds64_items;
         C->tune_lds64_small = hops[0]->tune_lds64_small;
-        C->tune_lds64_w7 = hops[0]->tune_lds64_w7;
-        C->tune_lds64_cw = hops[0]->tune_lds64_cw;
-        C->tune_lds64_ns3 = hops[0]->tune_lds64_ns3;
         C->tune_lds64_task_route = hops[0]->tune_lds64_task_route;
         C->tune_split_task_route = hops[0]->tune_split_task_route;
         C->tune_part_items = hops[0]->tune_part_items;
@@ -1155,7 +1147,9 @@ extern "C" dmrg_status dmrg_hop_trim(dmrg_hop* H) {
         H->lplan = dmrg::LdsPlan{};
         H->bplan = dmrg::BigPlan{};
         H->bplan64 = dmrg::BigPlan{};
-        H->lplan64 = dmrg::LdsPlan64{};
+        H->rplan64 = dmrg::RsPlan64{};
+        H->packs64 = nullptr;
+        H->n_packs64 = 0;
         H->launches.clear(); H->phases.clear(); H->launches_fb.clear(); H->phases_fb.clear();
         H->big_chunks.clear(); H->big_chunks64.clear();
         H->n_fallback_targets = 0;
@@ -1168,11 +1162,11 @@ extern "C" dmrg_status dmrg_hop_trim(dmrg_hop* H) {
             H->dev_bytes -= bytes;
         };
         release(H->d_tiled, H->tiled_size * (int64_t)sizeof(uint16_t));
-        release(H->d_tiled64, H->tiled64_size * (int64_t)sizeof(double));
+        release(H->d_op64, H->op64_len * (int64_t)sizeof(double));
         release(H->d_hi, H->pool_size * (int64_t)sizeof(uint16_t));
         release(H->d_lo, H->pool_size * (int64_t)sizeof(uint16_t));
-        H->d_tiled = nullptr; H->d_tiled64 = nullptr; H->d_hi = nullptr; H->d_lo = nullptr;
-        H->tiled_size = H->tiled64_size = 0;
+        H->d_tiled = nullptr; H->d_op64 = nullptr; H->d_hi = nullptr; H->d_lo = nullptr;
+        H->tiled_size = H->op64_len = 0;
         H->trimmed = true;
         return DMRG_OK;
     } catch (const Error& e) {
@@ -1204,12 +1198,13 @@ extern "C" dmrg_status dmrg_hop_autotune(dmrg_hop* H, int32_t precision, int32_t
         // The plan's settings, each with its candidate values (the current value is measured first).
         // Split: LDS item count and launch order, the task-mode tile (row tiles x column tiles per
         // wavefront: 1 x 2 / 2 x 2 / 1 x 4), the 64-wide stage classes, the six-wavefront (S, 2)
-        // classes, the copy and prefetch wavefronts. FP64: the LDS-staged kernel's item count, copy
-        // wavefront, single-tile sources and 7-wavefront register cap, the two-pass routing of large
-        // targets, and the one-wavefront kernel's tile width, item count and launch order.
+        // classes, the copy and prefetch wavefronts. FP64: the register-streamed kernel's item count and
+        // single-tile sources, the two-pass routing of large targets, and the one-wavefront kernel's tile
+        // width, item count and launch order.
         struct Knob { int* field; std::vector<int> cand; };
         std::vector<Knob> knobs;
         int small_shape = H->tune_small_nq > 2 ? 2 : H->tune_small_nr > 1 ? 1 : 0;
+        int one = 1;                             // settings that no longer exist keep their place in `chosen`
         const bool split = precision == DMRG_PREC_SPLIT2;
         if (split) {
             knobs.push_back({&H->tune_lds_items, {4096, 8192, 16384, 32768, 65536}});
@@ -1220,11 +1215,11 @@ extern "C" dmrg_status dmrg_hop_autotune(dmrg_hop* H, int32_t precision, int32_t
             knobs.push_back({&H->tune_lds_cw, {0, 0xF}});
             knobs.push_back({&H->tune_lds_pf, {0x4, 0}});
         } else {
-            const bool lds64 = H->tune_lds64 != 0;
+            const bool lds64 = H->tune_lds64 != 0;   // the register-streamed kernel
             knobs.push_back({&H->tune_lds64_items, lds64 ? std::vector<int>{8192, 16384, 32768, 65536} : std::vector<int>{}});
-            knobs.push_back({&H->tune_lds64_cw, lds64 ? std::vector<int>{1, 0} : std::vector<int>{}});
+            knobs.push_back({&one, {}});          // (the copy wavefront of the LDS-staged kernel it replaced)
             knobs.push_back({&H->tune_lds64_small, lds64 ? std::vector<int>{1, 0} : std::vector<int>{}});
-            knobs.push_back({&H->tune_lds64_w7, lds64 ? std::vector<int>{1, 0} : std::vector<int>{}});
+            knobs.push_back({&one, {}});          // (that kernel's register cap)
             knobs.push_back({&H->tune_big64, {1, 2}});
             knobs.push_back({&H->tune_max_tq, {2, 4, 8}});
             knobs.push_back({&H->tune_items, {8192, 32768, 65536}});

@@ -6,18 +6,15 @@
 // 16-wide column tile jc of the source, and per step:
 //   GEMM1  T'(rt, jc)^T = X^T(jc, :) . A(rt, :)^T   A's row tile stays in registers for the task
 //   GEMM2  Y(rt, :)   += f T'(rt, jc) . B(:, jc)^T  GEMM1's result layout is GEMM2's A-operand layout
-// The X^T and B tiles stream from the caches into register rings that are refilled as soon as a tile has
-// been used, up to a whole GEMM ahead of their next use (every load is unconditional: a tile outside
-// the block re-reads its first one, so that the compiler knows how many loads are in flight and never
-// waits for the newest). MFMAs run only on the 4-wide k steps that hold data.
+// X^T and B stream from the caches into register rings that are refilled as soon as an operand has been
+// used, up to a whole GEMM ahead of its next use (every load is unconditional: what lies outside the block
+// re-reads a part of it, so that the compiler knows how many loads are in flight and never waits for the
+// newest). MFMAs run only on the 4-wide k steps that hold data. Operands are read in the compact form of
+// internal.h, 16 bytes per lane and two k steps.
 //
-// Why: an FP64 16x16x4 MFMA takes 64 cycles, so one wavefront needs 2 KB per 256 cycles, half of what a
-// CU's vector cache delivers to four of them; what small sectors lack is work in flight. A workgroup of
-// seven wavefronts per target that steps behind barriers (hpsi_lds64.hip) leaves six of them idle on a
-// target of up to 16 rows.
-//
-// Tile format (internal.h, hpsi_big64.hip): a 16 x 16 tile holds M[16 rt + li][16 kt + 4 v + g] in
-// lane (li, g) = (l % 16, l / 16), value v.
+// What bounds it: an FP64 16x16x4 MFMA takes 64 cycles, so a wavefront needs 2 KB per 256 cycles, half of
+// what a CU's vector cache delivers to four of them: the matrix cores and the traffic between the L2s
+// and memory bound large sectors, latency (hidden by 8 .. 16 wavefronts per CU) and launches the small.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,13 +25,8 @@ namespace dmrg {
 namespace {
 
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kTileD = 256;   // doubles per 16 x 16 tile
-
-// 32 bytes per lane at a wave-uniform address
-__device__ __forceinline__ f64x4 ld4(const double* p, uint32_t lane_bytes) {
-    return *reinterpret_cast<const f64x4*>(reinterpret_cast<const char*>(p) + lane_bytes);
-}
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ int64_t uni64(int64_t v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
@@ -45,17 +37,19 @@ __device__ __forceinline__ double unid(double v) {
     return __builtin_bit_cast(double, uni64(__builtin_bit_cast(int64_t, v)));
 }
 
-// Task descriptor in scalar registers (offsets in doubles; pa16 / pd16: tile strides of the source's
-// rows / columns; ka4 / kd4: the 4-wide k steps of them that hold data).
-struct TD { int64_t x, a, b; double f; int pa16, pd16, ka4, kd4; };
+// 16 bytes per lane, lane_bytes after a wave-uniform address
+__device__ __forceinline__ f64x2 ld2(const double* p, uint32_t lane_bytes) {
+    return *reinterpret_cast<const f64x2*>(reinterpret_cast<const char*>(p) + lane_bytes);
+}
+
+// Task descriptor in scalar registers.
+struct TD { int64_t x, a, b; double f; int ka4, kd4; };
 __device__ __forceinline__ TD load_td(const LTask64* __restrict__ p) {
     TD d;
     d.x = uni64(p->x_off);
     d.a = uni64(p->a_off);
     d.b = uni64(p->b_off);
     d.f = unid(p->f);
-    d.pa16 = uni(p->pa16);
-    d.pd16 = uni(p->pd16);
     d.ka4 = uni(p->ka4);
     d.kd4 = uni(p->kd4);
     return d;
@@ -64,40 +58,55 @@ __device__ __forceinline__ TD load_td(const LTask64* __restrict__ p) {
 // keeps the loads before it from sinking to their uses and those after it from rising
 __device__ __forceinline__ void fence() { asm volatile("" ::: "memory"); }
 
-template <int KT, int QT>
+// KP: column groups (two k steps each) of the A row tile; QT: column tiles of the target; JP: column
+// groups of a source column tile that are read (1: every source has at most 8 columns).
+template <int KP, int QT, int JP>
 __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask64* __restrict__ tasks,
-                                        const double* __restrict__ pool_t, const double* __restrict__ xt,
+                                        const double* __restrict__ ops, const double* __restrict__ xt,
                                         double* __restrict__ y, double* __restrict__ part, int lane) {
-    constexpr int RX = KT == 8 ? 4 : KT, RB = QT == 8 ? 4 : QT;   // ring sizes (divisors of KT, QT)
-    const int rt = uni(ip->r0) >> 4, m_dp = uni(ip->m_dp);
-    const int tq = (m_dp + 15) >> 4;
+    constexpr int RX = KP == 16 ? 8 : KP, RB = QT == 8 ? 4 : QT;   // ring sizes (divisors of KP, QT)
+    const int rt = uni(ip->r0) >> 4, m_ap = uni(ip->m_ap), m_dp = uni(ip->m_dp);
+    const int ra4 = (m_ap + 3) >> 2, rb4 = (m_dp + 3) >> 2, tq = (m_dp + 15) >> 4;
     const int t_begin = uni(ip->t_begin), t_end = uni(ip->t_end);
-    const uint32_t lb = (uint32_t)lane * 32;
+    const uint32_t li = lane & 15, g = lane >> 4;
+    // byte offset of the lane in row tile t of an operand of r4 4-row groups (rows past the end of a
+    // ragged last tile read its last row)
+    auto lane_at = [&](int t, int r4) {
+        const uint32_t w = min(16, 4 * (r4 - 4 * t));
+        return (uint32_t)t * 1024u + (g * w + min(li, w - 1)) * 16u;
+    };
+    const uint32_t a_lane = lane_at(rt, ra4), b_full = (uint32_t)lane * 16u, b_last = lane_at(tq - 1, rb4);
 
-    f64x4 acc[QT], ar[KT], xr[RX], br[RB];
+    f64x4 acc[QT];
+    f64x2 ar[KP], xr[RX], br[RB][JP];
 #pragma unroll
     for (int q = 0; q < QT; ++q) acc[q] = f64x4{0.0, 0.0, 0.0, 0.0};
 
     auto load_a = [&](const TD& T) {
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt)
-            ar[kt] = ld4(pool_t + T.a + (int64_t)(rt * T.pa16 + (4 * kt < T.ka4 ? kt : 0)) * kTileD, lb);
+        for (int p = 0; p < KP; ++p) ar[p] = ld2(ops + T.a + (int64_t)((2 * p < T.ka4 ? p : 0) * ra4) * 32, a_lane);
     };
-    auto x_tile = [&](const TD& T, int jc, int kt) {
-        return ld4(xt + T.x + (int64_t)(jc * T.pa16 + (4 * kt < T.ka4 ? kt : 0)) * kTileD, lb);
+    auto x_pair = [&](const TD& T, uint32_t x_lane, int p) {
+        return ld2(xt + T.x + (int64_t)((2 * p < T.ka4 ? p : 0) * T.kd4) * 32, x_lane);
     };
-    auto b_tile = [&](const TD& T, int jc, int q) {
-        return ld4(pool_t + T.b + (int64_t)((q < tq ? q : 0) * T.pd16 + jc) * kTileD, lb);
+    auto b_tile = [&](const TD& T, int jc, int q, f64x2 (&b)[JP]) {
+        const uint32_t at = q < tq - 1 ? (uint32_t)q * 1024u + b_full : b_last;
+#pragma unroll
+        for (int h = 0; h < JP; ++h) {
+            const int p = 2 * jc + (4 * jc + 2 * h < T.kd4 ? h : 0);
+            b[h] = ld2(ops + T.b + (int64_t)(p * rb4) * 32, at);
+        }
     };
 
     int t = t_begin, jc = 0;
     TD T = load_td(tasks + t);
     TD Tnext = load_td(tasks + min(t + 1, t_end - 1));   // the following task, one ahead
     load_a(T);
+    uint32_t xl = lane_at(0, T.kd4);                      // the lane's place in X^T's row tile jc
 #pragma unroll
-    for (int i = 0; i < RX; ++i) xr[i] = x_tile(T, 0, i);
+    for (int i = 0; i < RX; ++i) xr[i] = x_pair(T, xl, i);
 #pragma unroll
-    for (int i = 0; i < RB; ++i) br[i] = b_tile(T, 0, i);
+    for (int i = 0; i < RB; ++i) b_tile(T, 0, i, br[i]);
     fence();
     for (;;) {
         const bool more_cols = 4 * (jc + 1) < T.kd4;
@@ -105,15 +114,15 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
         // the next step (the last step's successor is its own task's first step: loaded, never used)
         const int njc = more_cols ? jc + 1 : 0;
         const TD N = new_task ? Tnext : T;
+        const uint32_t nxl = lane_at(njc, N.kd4);
         f64x4 tt = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) {
+        for (int p = 0; p < KP; ++p) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (4 * kt + v < T.ka4)
-                    tt = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[kt % RX][v], ar[kt][v], tt, 0, 0, 0);
+            for (int u = 0; u < 2; ++u)
+                if (2 * p + u < T.ka4) tt = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[p % RX][u], ar[p][u], tt, 0, 0, 0);
             fence();
-            xr[kt % RX] = kt + RX < KT ? x_tile(T, jc, kt + RX) : x_tile(N, njc, kt + RX - KT);
+            xr[p % RX] = p + RX < KP ? x_pair(T, xl, p + RX) : x_pair(N, nxl, p + RX - KP);
             fence();
         }
         // tt[v] = T'[16 rt + li][16 jc + 4 v + g] (unscaled); the A rows are free now
@@ -128,15 +137,17 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
         for (int q = 0; q < QT; ++q) {
             if (q < tq) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (v < kd) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(tt[v], br[q % RB][v], acc[q], 0, 0, 0);
+                for (int v = 0; v < 2 * JP; ++v)
+                    if (v < kd) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(tt[v], br[q % RB][v >> 1][v & 1], acc[q], 0, 0, 0);
             }
             fence();
-            br[q % RB] = q + RB < QT ? b_tile(T, jc, q + RB) : b_tile(N, njc, q + RB - QT);
+            if (q + RB < QT) b_tile(T, jc, q + RB, br[q % RB]);
+            else b_tile(N, njc, q + RB - QT, br[q % RB]);
             fence();
         }
         if (!more_cols && !new_task) break;
         jc = njc;
+        xl = nxl;
         if (new_task) {
             ++t;
             T = Tnext;
@@ -145,8 +156,7 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
     }
     // store: lane (li, g) holds Y[16 rt + g + 4 v][16 q + li]
     const int64_t y_off = uni64(ip->y_off), part_off = uni64(ip->part_off);
-    const int m_ap = uni(ip->m_ap), tn = 16 * tq;
-    const int li = lane & 15, g = lane >> 4;
+    const int tn = 16 * tq;
 #pragma unroll
     for (int q = 0; q < QT; ++q) {
         if (q >= tq) continue;
@@ -162,14 +172,36 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
     }
 }
 
+template <int G, int K, int Q>
+__device__ __forceinline__ bool rs_try(int cls, const Item* __restrict__ ip, const LTask64* __restrict__ tasks,
+                                       const double* __restrict__ ops, const double* __restrict__ xt, double* __restrict__ y,
+                                       double* __restrict__ part, int lane) {
+    if constexpr (rs_group(K, Q) == G) {
+        if (cls == 8 * K + Q) {
+            rs_item<K == 0 ? 1 : 2 * kRsK[K], kRsQ[Q], K == 0 ? 1 : 2>(ip, tasks, ops, xt, y, part, lane);
+            return true;
+        }
+    }
+    return false;
+}
+
+template <int G, int K>
+__device__ __forceinline__ void rs_try_k(int cls, const Item* __restrict__ ip, const LTask64* __restrict__ tasks,
+                                         const double* __restrict__ ops, const double* __restrict__ xt, double* __restrict__ y,
+                                         double* __restrict__ part, int lane) {
+    if ((cls >> 3) != K) return;
+    (void)(rs_try<G, K, 0>(cls, ip, tasks, ops, xt, y, part, lane) || rs_try<G, K, 1>(cls, ip, tasks, ops, xt, y, part, lane) ||
+           rs_try<G, K, 2>(cls, ip, tasks, ops, xt, y, part, lane) || rs_try<G, K, 3>(cls, ip, tasks, ops, xt, y, part, lane) ||
+           rs_try<G, K, 4>(cls, ip, tasks, ops, xt, y, part, lane) || rs_try<G, K, 5>(cls, ip, tasks, ops, xt, y, part, lane));
+}
+
 }  // namespace
 
-// Group G runs the classes (KT, QT) of its register budget: 0: up to 2 x 2 tiles, 1: up to 3 x 3,
-// 2: up to 8 x 8. Item.c0 holds the class, kRsSizes indices 8 * k + q.
+// Group G runs the classes of its register budget (rs_group).
 template <int G, int MINW>
 __global__ __launch_bounds__(kRsWaves * 64, MINW) void k_hpsi_rs64(const Item* __restrict__ items, int n_items,
                                                                 const LTask64* __restrict__ tasks,
-                                                                const double* __restrict__ pool_t,
+                                                                const double* __restrict__ ops,
                                                                 const double* __restrict__ xt,
                                                                 double* __restrict__ y, double* __restrict__ part,
                                                                 const int32_t* __restrict__ mask) {
@@ -178,45 +210,31 @@ __global__ __launch_bounds__(kRsWaves * 64, MINW) void k_hpsi_rs64(const Item* _
     const Item* ip = items + w;
     if (uni(ip->t_begin) >= uni(ip->t_end)) return;              // filler of a workgroup
     if (mask && mask[uni(ip->part)] != kPartActive) return;
-    const int lane = threadIdx.x & 63;
-#define DMRG_RS(K_, Q_, KT_, QT_) \
-    case 8 * K_ + Q_: rs_item<KT_, QT_>(ip, tasks, pool_t, xt, y, part, lane); break;
-    const int cls = uni(ip->c0);
-    if constexpr (G == 0) {
-        switch (cls) {
-            DMRG_RS(0, 0, 1, 1) DMRG_RS(0, 1, 1, 2) DMRG_RS(1, 0, 2, 1)
-            default: rs_item<2, 2>(ip, tasks, pool_t, xt, y, part, lane); break;
-        }
-    } else if constexpr (G == 1) {
-        switch (cls) {
-            DMRG_RS(0, 2, 1, 3) DMRG_RS(1, 2, 2, 3) DMRG_RS(2, 0, 3, 1) DMRG_RS(2, 1, 3, 2)
-            default: rs_item<3, 3>(ip, tasks, pool_t, xt, y, part, lane); break;
-        }
-    } else {
-        switch (cls) {
-            DMRG_RS(0, 3, 1, 4) DMRG_RS(0, 4, 1, 6) DMRG_RS(0, 5, 1, 8)
-            DMRG_RS(1, 3, 2, 4) DMRG_RS(1, 4, 2, 6) DMRG_RS(1, 5, 2, 8)
-            DMRG_RS(2, 3, 3, 4) DMRG_RS(2, 4, 3, 6) DMRG_RS(2, 5, 3, 8)
-            DMRG_RS(3, 0, 4, 1) DMRG_RS(3, 1, 4, 2) DMRG_RS(3, 2, 4, 3) DMRG_RS(3, 3, 4, 4) DMRG_RS(3, 4, 4, 6) DMRG_RS(3, 5, 4, 8)
-            DMRG_RS(4, 0, 6, 1) DMRG_RS(4, 1, 6, 2) DMRG_RS(4, 2, 6, 3) DMRG_RS(4, 3, 6, 4) DMRG_RS(4, 4, 6, 6) DMRG_RS(4, 5, 6, 8)
-            DMRG_RS(5, 0, 8, 1) DMRG_RS(5, 1, 8, 2) DMRG_RS(5, 2, 8, 3) DMRG_RS(5, 3, 8, 4) DMRG_RS(5, 4, 8, 6)
-            default: rs_item<8, 8>(ip, tasks, pool_t, xt, y, part, lane); break;
-        }
-    }
-#undef DMRG_RS
+    const int lane = threadIdx.x & 63, cls = uni(ip->c0);
+    rs_try_k<G, 0>(cls, ip, tasks, ops, xt, y, part, lane);
+    rs_try_k<G, 1>(cls, ip, tasks, ops, xt, y, part, lane);
+    rs_try_k<G, 2>(cls, ip, tasks, ops, xt, y, part, lane);
+    rs_try_k<G, 3>(cls, ip, tasks, ops, xt, y, part, lane);
+    rs_try_k<G, 4>(cls, ip, tasks, ops, xt, y, part, lane);
+    rs_try_k<G, 5>(cls, ip, tasks, ops, xt, y, part, lane);
+    rs_try_k<G, 6>(cls, ip, tasks, ops, xt, y, part, lane);
 }
 
-hipError_t launch_hpsi_rs64(const RsPlan64& P, const LTask64* tasks, const double* pool_t, const double* xt, double* y,
-                            double* partial, hipStream_t s, const int32_t* active) {
+hipError_t launch_hpsi_rs64(const RsPlan64& P, const double* ops, const double* xt, double* y, hipStream_t s,
+                            const int32_t* active) {
+    if (P.n_items == 0) return hipSuccess;
     for (int g = kRsGroups - 1; g >= 0; --g) {   // the longest items first
         const int b = P.begin[g], n = P.begin[g + 1] - b;
         if (n <= 0) continue;
         const dim3 grid((n + kRsWaves - 1) / kRsWaves), block(kRsWaves * 64);
-        if (g == 0) hipLaunchKernelGGL((k_hpsi_rs64<0, 4>), grid, block, 0, s, P.items + b, n, tasks, pool_t, xt, y, partial, active);
-        else if (g == 1) hipLaunchKernelGGL((k_hpsi_rs64<1, 3>), grid, block, 0, s, P.items + b, n, tasks, pool_t, xt, y, partial, active);
-        else hipLaunchKernelGGL((k_hpsi_rs64<2, 2>), grid, block, 0, s, P.items + b, n, tasks, pool_t, xt, y, partial, active);
+        const Item* it = P.items + b;
+        if (g == 0) hipLaunchKernelGGL((k_hpsi_rs64<0, 4>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active);
+        else if (g == 1) hipLaunchKernelGGL((k_hpsi_rs64<1, 3>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active);
+        else hipLaunchKernelGGL((k_hpsi_rs64<2, 2>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active);
     }
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || P.n_reduces <= 0) return e;
+    return launch_reduce_partials(P.reduces, P.n_reduces, P.red_chunks, P.partial, y, s, active);
 }
 
 }  // namespace dmrg

@@ -70,7 +70,7 @@ constexpr int32_t kPartActive = 1;
 // v_mfma_f32_16x16x32_bf16. A pool block of rows_of(R) x ld_of(K) doubles at pool offset o occupies
 // exactly the u16 range [2 o, 2 o + 2 rows_of(R) ld_of(K)) of the tiled array.
 constexpr int kTileU16 = 1024;
-struct PoolBlock { int64_t off; int32_t r16, k32; };
+struct PoolBlock { int64_t off; int32_t r16, k32, rows, cols; };   // rows, cols: before padding
 
 // Task of the LDS-staged split kernel: Y_tile += f * A . X . B^T with every factor present (identity
 // factors point at tiled identity blocks). Offsets are u16 offsets into the tiled arrays.
@@ -186,59 +186,64 @@ struct LdsPlan {
                                         // two of the SIMDs (measured faster; (64,2) is not)
 };
 
-// Launch plan of the FP64 LDS-staged kernel (hpsi_lds64.hip): items (internal.h Item; r0 = c0 = 0)
-// each cover a whole target block of at most 112 x 112 and a range of its tasks, over the FP64 tiled
-// pool (identity factors point at its identity blocks) and the tiled FP64 X^T of the packed input
-// (offsets in doubles). Launch classes (KT, QT, W): c = 2 (KT == 6) + (QT == 6) for targets of at most
-// 96 x 96 and sources of at most 96 rows (W = 6; KT = 2 when every task of the item has at most 32
-// source rows, else 6; QT = 3 for targets of at most 48 columns, else 6), c = 4 (7, 7, 7) for the
-// rest (a target or a source of 97 .. 112 rows or columns).
-constexpr int kLds64Classes = 5;
-constexpr int kLds64MaxTiles = 7;       // target rows / columns and source rows, in 16-wide tiles
-struct LTask64 {
-    int64_t x_off, a_off, b_off;
-    double  f;
-    int32_t pa16, pd16;      // source rows / columns padded to 32, in 16-wide tiles (tile strides)
-    int32_t ka4, kd4;        // 4-wide k steps of the source rows / columns that hold data (the rest of
-                             // the padding is skipped; 16-wide tiles: rounded up)
-};
-// Items of the register-streamed FP64 kernel (hpsi_rs64.hip), one wavefront each: r0 = 16 x the row
-// tile, c0 = the class, 8 * k + q with the indices of its source-row and target-column tiles in
-// kRsSizes. begin[g] .. begin[g + 1]: the items of launch group g (register budgets, see there).
+// ---------------------------------------------------------------- FP64 operands of the MFMA kernels
+// Operand form of the FP64 kernels (hpsi_rs64.hip, hpsi_big64.hip): a matrix of R rows and K columns (K
+// the reduction index) is padded to R4 = ceil(R / 4) groups of 4 rows and ceil(K / 8) groups of 8
+// columns, zero-filled, and stored by column group p, inside it by 16-row tile, inside that as [g][li][u]
+// with element M[16 rt + li][8 p + 4 u + g], g < 4, li < the tile's rows, u < 2. So a lane (li, g) of
+// v_mfma_f64_16x16x4f64 reads its operands of two k steps as 16 contiguous bytes, a full tile's column
+// group is 1 KB in lane order, and a small block takes little more than its elements: 8 x 8 states are
+// 512 B where whole 16 x 16 tiles of a 32-padded matrix are 4 KB.
+inline int32_t k4_of(int32_t m) { return (m + 3) / 4; }
+inline int64_t op64_size(int32_t rows, int32_t cols) { return (int64_t)k4_of(rows) * ((cols + 7) / 8) * 32; }
+struct OpBlock64 { int64_t src, dst; int32_t ld, rows, cols, pad; };   // pool block -> operand form
+
+// Launch plan of the register-streamed FP64 kernel (hpsi_rs64.hip). Items (internal.h Item) are
+// wavefronts: r0 = 16 x the row tile, c0 = the class 8 k + q, with k an index into kRsK (source rows in
+// 16-wide tiles; 0: source rows and columns both within 8) and q one into kRsQ (target columns).
+// begin[g] .. begin[g + 1]: the items of launch group g (register budgets, see the kernel).
 constexpr int kRsWaves = 4;             // wavefronts (items) per workgroup
 constexpr int kRsGroups = 3;
-constexpr int kRsSizes[6] = {1, 2, 3, 4, 6, 8};
-constexpr int kRsMaxTiles = 8;
-inline int rs_class(int tiles) { int c = 0; while (kRsSizes[c] < tiles) ++c; return c; }
-inline int rs_group(int k, int q) { const int m = k > q ? k : q; return m <= 1 ? 0 : m <= 2 ? 1 : 2; }
+constexpr int kRsK[7] = {0, 1, 2, 3, 4, 6, 8};
+constexpr int kRsQ[6] = {1, 2, 3, 4, 6, 8};
+constexpr int kRsMaxTiles = 8;          // target rows are any; target columns, source rows and columns
+inline int rs_kclass(int ka4, int kd4) {
+    if (ka4 <= 2 && kd4 <= 2) return 0;
+    int c = 1;
+    while (4 * kRsK[c] < ka4) ++c;
+    return c;
+}
+inline int rs_qclass(int tiles) { int c = 0; while (kRsQ[c] < tiles) ++c; return c; }
+// Launch group of a class: the accumulators (8 registers a column tile), the A row tile (8 a source tile),
+// the two rings and about 45 more within 128 (group 0), 168 (1) or 256 (2) registers, i.e. 4, 3 or 2
+// wavefronts per SIMD.
+constexpr int rs_group(int k, int q) {
+    const int kp = k == 0 ? 1 : 2 * kRsK[k], qt = kRsQ[q], jp = k == 0 ? 1 : 2;
+    const int rx = kp == 16 ? 8 : kp, rb = qt == 8 ? 4 : qt;
+    const int regs = 8 * qt + 4 * (kp + rx + rb * jp) + 45;
+    return regs <= 117 ? 0 : regs <= 149 ? 1 : 2;
+}
+struct LTask64 {
+    int64_t x_off, a_off, b_off;        // doubles: X^T of the source in xt, A and B in the operand pool
+    double  f;
+    int32_t ka4, kd4;                   // source rows / columns in 4-wide k steps
+};
 struct RsPlan64 {
     const Item* items = nullptr;        // device
-    int begin[kRsGroups + 1] = {0, 0, 0, 0};
-};
-struct LdsPlan64 {
-    const Item* items = nullptr;        // device
     const LTask64* tasks = nullptr;     // device
-    const Reduce* reduces = nullptr;    // device; one record per target cut into several items (its
-    int n_reduces = 0;                  // items of both stage sizes), so one launch adds them all
+    const Reduce* reduces = nullptr;    // device; one record per target cut into several items
+    int n_reduces = 0;
     int red_chunks = 1;                 // 256-element chunks of the largest partial tile
-    int cls_begin[kLds64Classes + 1] = {0, 0, 0, 0, 0, 0};
+    int begin[kRsGroups + 1] = {0, 0, 0, 0};
     double* partial = nullptr;          // device, partial tiles of one vector
     int64_t partial_size = 0;
-    int n_items = 0;
-    int w7_min_waves = 1;               // 4: the (7, 7, 7) class held to 128 VGPRs (two workgroups per CU)
-    int copy_wave = 1;                  // 1: one more wavefront per workgroup issues every LDS copy
-    int three_slots = 0;                // with the copy wavefront: the KT = 2 classes stage two steps ahead
-    RsPlan64 rs;                        // items of the register-streamed kernel over the same tasks, partial
-                                        // tiles and reductions
+    int n_items = 0;                    // task ranges (each runs as one wavefront per row tile of its target)
 };
-// y (one vector) += the plan's targets of f A X B^T; xt = that vector's tiled FP64 X^T
-// (launch_pack_xt64 with the FP64 packing geometry)
-hipError_t launch_hpsi_lds64(const LdsPlan64& P, const double* pool_t, const double* xt, double* y, hipStream_t s,
-                             const int32_t* active = nullptr);
-// the register-streamed items of the same plan (launched by launch_hpsi_lds64 before its reductions)
-hipError_t launch_hpsi_rs64(const RsPlan64& P, const LTask64* tasks, const double* pool_t, const double* xt, double* y,
-                            double* partial, hipStream_t s, const int32_t* active = nullptr);
-// tiled FP64 X^T of every psi block (hpsi_big64.hip)
+// y (one vector) += the plan's targets of f A X B^T; xt = that vector's X^T in operand form
+hipError_t launch_hpsi_rs64(const RsPlan64& P, const double* ops, const double* xt, double* y, hipStream_t s,
+                            const int32_t* active = nullptr);
+// operand form of the pool's blocks, and of X^T of every psi block (hpsi_big64.hip)
+hipError_t launch_op64(const double* pool, const OpBlock64* blocks, int n_blocks, double* ops, hipStream_t s);
 hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x, double* xt, hipStream_t s);
 // y (one vector) += the partial tiles of each record, in order (hpsi_lds.hip)
 hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, const double* partial, double* y,
@@ -249,8 +254,9 @@ hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, cons
 // targets: pass 1 writes T = f A X of every task into a tiled hi/lo buffer (tile (rt, jc) of the
 // task's T at t_off + (rt * pd32 + jc) * kTileU16, in the A-operand fragment layout of pass 2),
 // pass 2 accumulates Y += sum_tasks T B^T per 128 x 128 output tile.
-// FP64 form (hpsi_big64.hip): 16 x 16 FP64 tiles, offsets in doubles, pa32 / pd32 / jb counted in
-// 16-wide tiles.
+// FP64 form (hpsi_big64.hip): offsets in doubles, A, B and X^T in the FP64 operand form, T in whole
+// 16 x 16 tiles of it; pa32 / pd32 / rb / jb counted in 16-wide tiles, ka / kd in 4-wide k steps, nrt in
+// 4-row groups.
 struct BigT1 {             // pass-1 group: one task, rows [16 rb, 16 rb + 128), T^T rows [32 jb, 32 jb + 128)
     int64_t xt, a, t;      // tiled X^T of the source, tiled A, output T (u16 offsets)
     double f;
@@ -281,6 +287,7 @@ struct BigPlan {                    // split or FP64 form (see BigT1)
     uint16_t* tbuf = nullptr;       // device, largest chunk's T (one vector at a time; doubles in the FP64 form)
     double* partial = nullptr;      // device, partial tiles of the largest chunk
     int64_t partial_size = 0;
+    int64_t zeros = 0;              // FP64 form: offset of 1 KB of zeros in the operand pool
 };
 
 // Launchers (kernels.hip). All asynchronous on `s`.
@@ -342,11 +349,9 @@ hipError_t launch_hpsi_lds(const LdsPlan& plan, const uint16_t* pool_t, const do
 hipError_t launch_hpsi_big(const BigPlan& plan, const uint16_t* pool_t, const uint16_t* xt, double* y,
                            hipStream_t s, const int32_t* active = nullptr);
 // FP64 large-block path (hpsi_big64.hip) for one vector: y += the large targets' part of H x, over the
-// FP64 tiled pool; packs x into xt (FP64 tiled X^T, packed_size doubles) first unless packs is null
-// (xt already holds it).
-hipError_t launch_tile_f64(const double* pool, const PoolBlock* blocks, int n_blocks, double* tiled, hipStream_t s);
-hipError_t launch_hpsi_big64(const BigPlan& plan, const double* pool_t, const PackBlock* packs, int n_packs,
-                             const double* x, double* xt, double* y, hipStream_t s, const int32_t* active = nullptr);
+// FP64 operand pool and that vector's X^T in operand form (launch_pack_xt64).
+hipError_t launch_hpsi_big64(const BigPlan& plan, const double* ops, const double* xt, double* y, hipStream_t s,
+                             const int32_t* active = nullptr);
 // Old-kernel split path over a plan without clearing y first.
 hipError_t launch_hpsi_split_acc(const HpsiPlan& plan, const uint16_t* hi, const uint16_t* lo, const double* x,
                                  double* y, int64_t n_coeff, int nvec, hipStream_t s,

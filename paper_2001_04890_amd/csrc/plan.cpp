@@ -1,6 +1,6 @@
 // Launch planning of the two-site H.psi (Eq. dgemm, Section 2.2.1): the owner-computes task list of
 // a handle cut into balanced work items for each kernel path -- FP64 one-wavefront tiles, the FP64
-// LDS-staged kernel, the split LDS-staged row-mode and task-mode kernels, the two-pass large-block
+// register-streamed kernel, the split LDS-staged row-mode and task-mode kernels, the two-pass large-block
 // path in both precisions -- with ordered reductions of the partial tiles of cut items (no atomics),
 // part tags for the part masks of merged handles, and the tiled operator copies these kernels read.
 #include <algorithm>
@@ -61,6 +61,13 @@ T* plan_alloc(dmrg_hop& H, size_t n) {
 
 // Bytes of a matrix definition as stored in the pool (all its sector blocks, padded).
 double mat_bytes(const dmrg_hop& H, int m) { return m < 0 ? 0.0 : H.mats[m].bytes; }
+
+// Operand-pool offset of a task's factor: matrix m at ket sector `sec`, or the identity of `dim` states.
+int64_t op64_of(const dmrg_hop& H, int m, int sec, int dim) {
+    const int64_t off = m >= 0 ? H.mats[m].op64_of_in[sec] : H.ident64_off[dmrg::k4_of(dim)];
+    if (off < 0) throw Error(DMRG_ERR_ARG, "internal: operator block missing from the operand pool");
+    return off;
+}
 
 // Launch plan of H.psi: packed input layout, phases, work items, reductions (see internal.h).
 //  * Phases: the distinct (left matrix, right matrix) pairs are sorted by (right, left) and cut into
@@ -616,19 +623,28 @@ void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bo
     const int64_t kBigTBudget = (int64_t)H.tune_big_tbudget_mb << (fp64 ? 18 : 19);   // T elements per chunk
     dmrg::BigPlan& plan = fp64 ? H.bplan64 : H.bplan;
     std::vector<dmrg::BigChunk>& chunks = fp64 ? H.big_chunks64 : H.big_chunks;
-    const std::vector<int64_t>& ident_tab = fp64 ? H.ident64_off : H.ident_off;
     plan = dmrg::BigPlan{};
     chunks.clear();
     const size_t nb = H.blk.size();
-    std::vector<int64_t> pk_off(nb);
-    {
+    std::vector<int64_t> pk_off = H.xt64_off;
+    if (!fp64) {
+        pk_off.resize(nb);
         int64_t ps = 0;
         for (size_t i = 0; i < nb; ++i) { pk_off[i] = ps; ps += (int64_t)dmrg::ld_of(H.blk_ma[i]) * dmrg::ld_of(H.blk_md[i]); }
     }
-    auto ident = [&](int p) -> int64_t {
-        const int k = p / 32 - 1;
-        if (k < 0 || k >= (int)ident_tab.size()) return -1;
-        return ident_tab[k];
+    // T tiles along a task's source columns (tile stride; the split form keeps its padding to 32)
+    auto t_cols = [&](int i) { return fp64 ? (H.blk_md[i] + 15) / 16 : dmrg::ld_of(H.blk_md[i]) / unit; };
+    if (fp64) plan.zeros = H.zeros64_off;
+    // operand offsets of a task (identity factors: identity blocks)
+    auto left_of = [&](const dmrg_hop::HTask& t) {
+        if (fp64) return op64_of(H, t.lm, H.blk[t.i][0], H.blk_ma[t.i]);
+        const int k = dmrg::ld_of(H.blk_ma[t.i]) / 32 - 1;
+        return t.lm >= 0 ? 2 * H.mats[t.lm].pool_of_in[H.blk[t.i][0]] : k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
+    };
+    auto right_of = [&](const dmrg_hop::HTask& t) {
+        if (fp64) return op64_of(H, t.rm, H.blk[t.i][3], H.blk_md[t.i]);
+        const int k = dmrg::ld_of(H.blk_md[t.i]) / 32 - 1;
+        return t.rm >= 0 ? 2 * H.mats[t.rm].pool_of_in[H.blk[t.i][3]] : k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
     };
     std::vector<dmrg::BigT1> t1;
     std::vector<dmrg::BigT2> t2;
@@ -715,7 +731,7 @@ void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bo
         const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16;
         int64_t need = 0;
         for (size_t k = trange[j].first; k < trange[j].second; ++k)
-            if (kept(k)) need += (int64_t)nrt * (dmrg::ld_of(H.blk_md[H.tasks[k].i]) / unit) * tile_el;
+            if (kept(k)) need += (int64_t)nrt * t_cols(H.tasks[k].i) * tile_el;
         if (need == 0) continue;                  // every task of the target runs elsewhere
         if (tsize > 0 && tsize + need > kBigTBudget) close_chunk();
         const int32_t b0 = (int32_t)t2.size();
@@ -724,20 +740,21 @@ void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bo
         for (size_t k = trange[j].first; k < trange[j].second; ++k) {
             if (!kept(k)) continue;
             const auto& ht = H.tasks[k];
-            const int a = H.blk[ht.i][0], d = H.blk[ht.i][3];
-            const int pa = dmrg::ld_of(H.blk_ma[ht.i]), pd = dmrg::ld_of(H.blk_md[ht.i]);
-            const int64_t a_off = ht.lm >= 0 ? esc * H.mats[ht.lm].pool_of_in[a] : ident(pa);
-            const int64_t b_off = ht.rm >= 0 ? esc * H.mats[ht.rm].pool_of_in[d] : ident(pd);
-            if (a_off < 0 || b_off < 0) throw Error(DMRG_ERR_ARG, "internal: no tiled identity block");
+            const int64_t a_off = left_of(ht), b_off = right_of(ht);
+            if (a_off < 0 || b_off < 0) throw Error(DMRG_ERR_ARG, "internal: no tiled operand block");
             const int64_t t_off = tsize;
-            tsize += (int64_t)nrt * (pd / unit) * tile_el;
+            const int pd = t_cols(ht.i);
+            tsize += (int64_t)nrt * pd * tile_el;
             const int ka = (H.blk_ma[ht.i] + unit - 1) / unit, kd = (H.blk_md[ht.i] + unit - 1) / unit;
+            // FP64 form: k loops in 16-wide tiles that hold data, ka / kd in k steps, nrt in row groups
+            const int pa = fp64 ? ka : dmrg::ld_of(H.blk_ma[ht.i]) / unit;
+            const int ks = fp64 ? dmrg::k4_of(H.blk_ma[ht.i]) : ka, ds = fp64 ? dmrg::k4_of(H.blk_md[ht.i]) : kd;
+            const int rows = fp64 ? dmrg::k4_of(H.blk_ma[j]) : nrt;
             for (int rb = 0; rb < nrt; rb += 8)
                 for (int jb = 0; jb < kd; jb += 128 / unit)
-                    t1.push_back({esc * pk_off[ht.i], a_off, t_off, ht.f, (int16_t)(pa / unit),
-                                  (int16_t)(pd / unit), (int16_t)nrt, (int16_t)rb, (int16_t)jb, 0, (int16_t)ka,
-                                  (int16_t)kd});
-            t2.push_back({t_off, b_off, pd / unit, kd});
+                    t1.push_back({esc * pk_off[ht.i], a_off, t_off, ht.f, (int16_t)pa, (int16_t)pd, (int16_t)rows, (int16_t)rb,
+                                  (int16_t)jb, 0, (int16_t)ks, (int16_t)ds});
+            t2.push_back({t_off, b_off, pd, ds});
         }
         H.big_t2_range[j] = {b0, (int32_t)t2.size()};
         for (size_t g = g_t1; g < t1.size(); ++g) t1[g].part = (int16_t)part_j;
@@ -789,11 +806,8 @@ void drop_graphs(dmrg_hop& H) {
 
 namespace {
 
-// Widest target or source of the FP64 kernels for small and middle sectors, in 16-wide tiles.
-int lds64_tiles(const dmrg_hop& H) { return H.tune_rs64 >> (dmrg::kRsGroups - 1) & 1 ? dmrg::kRsMaxTiles : dmrg::kLds64MaxTiles; }
-
 // Targets whose own or some source's dimension exceeds `limit` (the 96-wide LDS stages of the split
-// kernel; 112 for the FP64 LDS-staged kernel).
+// kernel; 128 for the FP64 register-streamed kernel).
 std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
     std::vector<int> smax(H.blk.size(), 0);
     for (size_t j = 0; j < H.blk.size(); ++j) smax[j] = std::max(H.blk_ma[j], H.blk_md[j]);
@@ -808,10 +822,10 @@ std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
 // one-wavefront kernel recomputes A.X for every 128-column output tile) divided by the fraction of
 // the FP64 MFMA rate it sustains (measured: two-pass ~0.65 of peak on its padded work, one-wavefront
 // ~0.3). mode 2: every target above the 96-wide LDS stages (as the split path).
-// Tasks already taken by the FP64 LDS-staged kernel (lds_task) are left out of the comparison.
+// Tasks already taken by the register-streamed kernel (lds_task) are left out of the comparison.
 std::vector<char> fp64_big_targets(const dmrg_hop& H, int mode, const std::vector<char>* lds_task) {
-    // with the LDS-staged kernel on, targets within its 112 x 112 tiles are its own
-    std::vector<char> big = large_targets(H, H.tune_lds64 ? 16 * lds64_tiles(H) : 96);
+    // with the register-streamed kernel on, targets within its 128 x 128 are its own
+    std::vector<char> big = large_targets(H, H.tune_lds64 ? 16 * dmrg::kRsMaxTiles : 96);
     if (mode == 2) return big;
     auto up = [](double m, double q) { return std::ceil(m / q) * q; };
     std::vector<double> c_big(H.blk.size(), 0.0), c_one(H.blk.size(), 0.0);
@@ -832,223 +846,196 @@ std::vector<char> fp64_big_targets(const dmrg_hop& H, int mode, const std::vecto
     return big;
 }
 
-// FP64 tiled copy of the whole pool (16 x 16 tiles of hpsi_big64.hip, same offsets as the pool)
-// followed by FP64 tiled identity blocks of sizes 32, 64, ... up to the widest padded block, which
-// stand in for identity factors. Made once, on the first plan that routes targets to the FP64
-// large-block path.
-void make_tiled_f64(dmrg_hop& H, hipStream_t s) {
-    if (H.d_tiled64) return;
-    const int64_t n = H.pool_size;
-    int pmax = 96;
-    for (size_t i = 0; i < H.blk.size(); ++i)
-        pmax = std::max({pmax, dmrg::ld_of(H.blk_ma[i]), dmrg::ld_of(H.blk_md[i])});
-    std::vector<double> id;
-    H.ident64_off.assign(pmax / 32, -1);
-    for (int k = 0; k < pmax / 32; ++k) {
-        const int p = 32 * (k + 1), k16 = p / 16;
-        H.ident64_off[k] = n + (int64_t)id.size();
-        const size_t base = id.size();
-        id.resize(base + (size_t)p * p, 0.0);
-        for (int i = 0; i < p; ++i) {
-            // element (i, i): tile (i / 16, i / 16), lane (i % 16) + 16 ((i % 16) % 4), value (i % 16) / 4
-            const int t = i / 16, c = i % 16, lane = c + 16 * (c % 4), v = c / 4;
-            id[base + (size_t)(t * k16 + t) * 256 + lane * 4 + v] = 1.0;
+// Operand pool of the FP64 MFMA kernels: every pool block in the operand form of internal.h (offsets per
+// matrix and ket sector in MatDef::op64_of_in), identity blocks of the psi blocks' sizes (by 4-row
+// groups), which stand in for identity factors, and 1 KB of zeros. Made once. Also the places of the
+// packed X^T of every psi block.
+void make_op64(dmrg_hop& H, hipStream_t s) {
+    if (H.d_op64) return;
+    std::vector<dmrg::OpBlock64> ob;
+    ob.reserve(H.pool_blocks.size());
+    int64_t n = 0;
+    for (const auto& pb : H.pool_blocks) {       // ascending pool offsets
+        ob.push_back({pb.off, n, 32 * pb.k32, pb.rows, pb.cols, 0});
+        n += dmrg::op64_size(pb.rows, pb.cols);
+    }
+    for (MatDef& m : H.mats) {
+        m.op64_of_in.assign(m.pool_of_in.size(), -1);
+        for (size_t q = 0; q < m.pool_of_in.size(); ++q) {
+            if (m.pool_of_in[q] < 0) continue;
+            // the last block at this offset: empty blocks take no room and share it with their successor
+            auto it = std::upper_bound(ob.begin(), ob.end(), m.pool_of_in[q],
+                                       [](int64_t off, const dmrg::OpBlock64& o) { return off < o.src; });
+            if (it == ob.begin() || (it - 1)->src != m.pool_of_in[q]) throw Error(DMRG_ERR_ARG, "internal: not a pool block");
+            m.op64_of_in[q] = (it - 1)->dst;
         }
     }
-    H.tiled64_size = n + (int64_t)id.size();
-    H.d_tiled64 = dev_alloc<double>(H, H.tiled64_size);
-    dmrg::PoolBlock* d_pb = dev_alloc<dmrg::PoolBlock>(H, H.pool_blocks.size());
-    HIPCHK(hipMemcpyAsync(d_pb, H.pool_blocks.data(), H.pool_blocks.size() * sizeof(dmrg::PoolBlock),
-                          hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(H.d_tiled64 + n, id.data(), id.size() * sizeof(double), hipMemcpyHostToDevice, s));
-    HIPCHK(dmrg::launch_tile_f64(H.d_pool, d_pb, (int)H.pool_blocks.size(), H.d_tiled64, s));
-    HIPCHK(hipStreamSynchronize(s));   // the staging vector goes out of scope
+    int widest = 0;
+    for (size_t i = 0; i < H.blk.size(); ++i) widest = std::max({widest, dmrg::k4_of(H.blk_ma[i]), dmrg::k4_of(H.blk_md[i])});
+    H.ident64_off.assign(widest + 1, -1);
+    std::vector<double> tail(128, 0.0);          // zeros, then the identity blocks
+    H.zeros64_off = n;
+    auto add_ident = [&](int m) {
+        const int r4 = dmrg::k4_of(m);
+        if (H.ident64_off[r4] >= 0) return;
+        const size_t base = tail.size();
+        H.ident64_off[r4] = n + (int64_t)base;
+        tail.resize(base + (size_t)dmrg::op64_size(4 * r4, 4 * r4), 0.0);
+        for (int i = 0; i < 4 * r4; ++i) {       // element (i, i): group p, row tile, g, li, u
+            const int p = i / 8, rt = i / 16, w = std::min(16, 4 * r4 - 16 * rt), g = i % 4, u = (i % 8) / 4;
+            tail[base + (size_t)p * r4 * 32 + rt * 128 + (g * w + i % 16) * 2 + u] = 1.0;
+        }
+    };
+    for (const auto& t : H.tasks) {
+        if (t.lm < 0) add_ident(H.blk_ma[t.i]);
+        if (t.rm < 0) add_ident(H.blk_md[t.i]);
+    }
+    H.op64_len = n + (int64_t)tail.size();
+    H.d_op64 = dev_alloc<double>(H, H.op64_len);
+    dmrg::OpBlock64* d_ob = dev_alloc<dmrg::OpBlock64>(H, ob.size());
+    HIPCHK(hipMemcpyAsync(d_ob, ob.data(), ob.size() * sizeof(ob[0]), hipMemcpyHostToDevice, s));
+    HIPCHK(hipMemcpyAsync(H.d_op64 + n, tail.data(), tail.size() * sizeof(double), hipMemcpyHostToDevice, s));
+    HIPCHK(dmrg::launch_op64(H.d_pool, d_ob, (int)ob.size(), H.d_op64, s));
+    HIPCHK(hipStreamSynchronize(s));   // the staging vectors go out of scope
 }
 
-// Launch plan of the FP64 LDS-staged kernel (hpsi_lds64.hip) for the target blocks whose own and
-// sources' padded dimensions are at most 96 (targets flagged in `large` are skipped, and so are tasks
-// whose source is a single 32 x 32 tile unless tune_lds64_small; `lds` marks the tasks taken). A
-// target's tasks (source order) go to the KT = 2 classes when the source has at most 32 rows, else to
-// KT = 6; each run is cut into items of bounded cost (the MFMA instructions of one wavefront plus a
-// per-step and per-task overhead), and a target covered by several items gets partial tiles that a
-// reduction adds in item order. The packed input has the geometry of the other FP64 plans (every psi
-// block padded to multiples of 32).
-void build_lds64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large, std::vector<char>& lds) {
-    const size_t nb = H.blk.size();
-    lds.assign(H.tasks.size(), 0);
-    std::vector<int64_t> pk_off(nb);
-    int64_t psize = 0;
-    for (size_t i = 0; i < nb; ++i) {
-        pk_off[i] = psize;
-        psize += (int64_t)dmrg::ld_of(H.blk_ma[i]) * dmrg::ld_of(H.blk_md[i]);
+// Packing of X^T into operand form (every psi block).
+void build_pack64(dmrg_hop& H, hipStream_t s) {
+    std::vector<dmrg::PackBlock> packs;
+    H.xt64_off.resize(H.blk.size());
+    int64_t n = 0;
+    for (size_t i = 0; i < H.blk.size(); ++i) {
+        H.xt64_off[i] = n;
+        packs.push_back({H.blk_off[i], n, H.blk_ma[i], H.blk_md[i], 0, 0});
+        n += dmrg::op64_size(H.blk_md[i], H.blk_ma[i]);
     }
-    auto ident = [&](int p) -> int64_t {
-        const int k = p / 32 - 1;
-        if (k < 0 || k >= (int)H.ident64_off.size() || H.ident64_off[k] < 0)
-            throw Error(DMRG_ERR_ARG, "internal: no FP64 tiled identity block");
-        return H.ident64_off[k];
-    };
-    // every operand block the kernel reads must be a pool block of the task's shape (rows in 16-row
-    // tiles, at least the rows read; columns exactly the source's padded dimension) or an identity block
-    std::unordered_map<int64_t, std::pair<int, int>> shape;   // offset -> (row tiles, 16-wide k tiles)
-    for (const auto& pb : H.pool_blocks) shape[pb.off] = {pb.r16, 2 * pb.k32};
-    for (size_t q = 0; q < H.ident64_off.size(); ++q)
-        if (H.ident64_off[q] >= 0) shape[H.ident64_off[q]] = {2 * (int)(q + 1), 2 * (int)(q + 1)};
-    auto check = [&](int64_t off, int rows16, int k16) {
-        auto it = shape.find(off);
-        if (it == shape.end() || it->second.first < rows16 || it->second.second != k16)
-            throw Error(DMRG_ERR_ARG, "internal: FP64 LDS task operand does not match its pool block");
-    };
-    // MFMA instructions of one wavefront (per source column tile: GEMM1 over ka16 k tiles, GEMM2 over
-    // tq column tiles) + per-step and per-task overhead
+    dmrg::PackBlock* d = plan_alloc<dmrg::PackBlock>(H, packs.size());
+    HIPCHK(hipMemcpyAsync(d, packs.data(), packs.size() * sizeof(packs[0]), hipMemcpyHostToDevice, s));
+    H.xt64 = plan_alloc<double>(H, (size_t)std::max<int64_t>(n, 1));
+    H.packs64 = d;
+    H.n_packs64 = (int)packs.size();
+    HIPCHK(hipStreamSynchronize(s));
+}
+
+// Launch plan of the register-streamed FP64 kernel (hpsi_rs64.hip) for the targets and sources within its
+// 128 x 128 (targets flagged in `large` are skipped, and so are tasks whose source is a single 32 x 32
+// tile unless tune_lds64_small; `taken` marks the tasks taken). A target's tasks (source order) form up
+// to three runs, sources of at most 32 rows, of more, and those of blocks above 96; each run is cut into
+// items of bounded cost (the MFMAs of one wavefront over whole 16-wide tiles plus a per-step and per-task
+// overhead), an item is run by one wavefront per row tile, its class the least that holds its tasks, and
+// a target covered by several items gets partial tiles that a reduction adds in item order. Runs, cuts
+// and orders fix the order of every sum: results do not depend on the classes.
+void build_rs64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large, std::vector<char>& taken) {
+    const size_t nb = H.blk.size();
+    taken.assign(H.tasks.size(), 0);
     auto k16 = [](int k4) { return (k4 + 3) / 4; };
     auto cost = [&](const dmrg::LTask64& L, int tq) { return k16(L.kd4) * (4.0 * (k16(L.ka4) + tq) + 6.0) + 4.0; };
-    // the same of the register-streamed kernel, which runs the k steps that hold data only
-    auto rs_cost = [&](const dmrg::LTask64& L, int tq) {
-        return k16(L.kd4) * (L.ka4 + 4.0) + (double)L.kd4 * tq + 4.0;
-    };
-    struct Run { int j, cls, tq, rs; int32_t tb, te; };   // rs: class of the register-streamed kernel or -1
+    struct Run { int j, bucket, tq; int32_t tb, te; };
     std::vector<dmrg::LTask64> lt;
     lt.reserve(H.tasks.size());
     std::vector<Run> runs;
-    CostCaps caps(H), rs_caps(H);
+    CostCaps caps(H);
+    constexpr int kMax = dmrg::kRsMaxTiles;
+    std::vector<dmrg::LTask64> v[3];
     size_t k = 0;
     for (size_t j = 0; j < nb; ++j) {
         const size_t kb = k;
         while (k < H.tasks.size() && H.tasks[k].j == (int)j) ++k;
         if (k == kb || large[j]) continue;
         const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16, tq = dmrg::rows_of(H.blk_md[j]) / 16;
-        const int kMax = lds64_tiles(H);
-        if (nrt > kMax || tq > kMax) throw Error(DMRG_ERR_ARG, "internal: FP64 LDS target beyond its tiles");
-        const bool wide = nrt > 6 || tq > 6;      // the (7, 7, 7) class takes every task of the target
-        const int qcls = tq <= 3 ? 0 : 1;
-        std::vector<dmrg::LTask64> v[3 + 6];      // LDS-staged: KT = 2, 6, 7; register-streamed: by kRsSizes
+        if (nrt > kMax || tq > kMax) throw Error(DMRG_ERR_ARG, "internal: FP64 target beyond 128 x 128");
+        const bool wide = nrt > 6 || tq > 6;
         for (size_t t = kb; t < k; ++t) {
             const auto& ht = H.tasks[t];
-            const int a = H.blk[ht.i][0], d = H.blk[ht.i][3];
-            const int pa = dmrg::ld_of(H.blk_ma[ht.i]), pd = dmrg::ld_of(H.blk_md[ht.i]);
-            if (!H.tune_lds64_small && pa <= 32 && pd <= 32) continue;   // single-tile source: one-wave kernel
-            if (std::max(H.blk_ma[ht.i], H.blk_md[ht.i]) > 16 * kMax) continue;   // source above the tiles: other paths
-            lds[t] = 1;
-            dmrg::LTask64 L;
-            L.x_off = pk_off[ht.i];
-            L.a_off = ht.lm >= 0 ? H.mats[ht.lm].pool_of_in[a] : ident(pa);
-            L.b_off = ht.rm >= 0 ? H.mats[ht.rm].pool_of_in[d] : ident(pd);
-            if (L.a_off < 0 || L.b_off < 0) throw Error(DMRG_ERR_ARG, "internal: operator block missing from the pool");
-            L.f = ht.f;
-            L.pa16 = pa / 16;
-            L.pd16 = pd / 16;
-            L.ka4 = (H.blk_ma[ht.i] + 3) / 4;
-            L.kd4 = (H.blk_md[ht.i] + 3) / 4;
-            const int ka16 = k16(L.ka4);
-            if (ka16 > kMax || k16(L.kd4) > kMax || L.x_off + (int64_t)pa * pd > psize)
-                throw Error(DMRG_ERR_ARG, "internal: FP64 LDS task beyond its sources");
-            check(L.a_off, nrt, L.pa16);
-            check(L.b_off, tq, L.pd16);
-            const int kc = dmrg::rs_class(ka16);
-            const bool rs = (H.tune_rs64 >> dmrg::rs_group(kc, dmrg::rs_class(tq))) & 1;
-            v[rs ? 3 + kc : wide || ka16 > 6 ? 2 : ka16 <= 2 ? 0 : 1].push_back(L);
+            const int ma = H.blk_ma[ht.i], md = H.blk_md[ht.i];
+            if (!H.tune_lds64_small && ma <= 32 && md <= 32) continue;   // single-tile source: one-wave kernel
+            if (std::max(ma, md) > 16 * kMax) continue;                  // source above the tiles: other paths
+            taken[t] = 1;
+            const dmrg::LTask64 L{H.xt64_off[ht.i], op64_of(H, ht.lm, H.blk[ht.i][0], ma),
+                                  op64_of(H, ht.rm, H.blk[ht.i][3], md), ht.f, dmrg::k4_of(ma), dmrg::k4_of(md)};
+            v[wide || L.ka4 > 24 ? 2 : L.ka4 <= 8 ? 0 : 1].push_back(L);
         }
-        for (int kc = 0; kc < 9; ++kc) {
-            if (v[kc].empty()) continue;
-            const bool rs = kc >= 3;
-            const int size = rs ? dmrg::kRsSizes[kc - 3] : 0;
-            const int lc = rs ? (wide || size > 6 ? 2 : size <= 2 ? 0 : 1) : kc;   // stage-size bucket (trace)
-            Run R{(int)j, lc == 2 ? 4 : 2 * lc + qcls, tq, rs ? 8 * (kc - 3) + dmrg::rs_class(tq) : -1, (int32_t)lt.size(), 0};
-            for (const auto& L : v[kc]) {
+        for (int c = 0; c < 3; ++c) {
+            if (v[c].empty()) continue;
+            Run R{(int)j, c == 2 ? 4 : 2 * c + (tq > 3), tq, (int32_t)lt.size(), 0};   // bucket: plan trace
+            for (const auto& L : v[c]) {
                 lt.push_back(L);
-                if (rs) rs_caps.add((int)j, rs_cost(L, tq) * nrt);
-                else caps.add((int)j, cost(L, tq));
+                caps.add((int)j, cost(L, tq));
             }
             R.te = (int32_t)lt.size();
             runs.push_back(R);
+            v[c].clear();
         }
     }
-    H.lplan64 = dmrg::LdsPlan64{};
-    struct It { dmrg::Item item; double cost; int cls, rs; };
-    std::vector<It> its, rs_its;
+    H.rplan64 = dmrg::RsPlan64{};
+    struct It { dmrg::Item item; double cost; int cls; };
+    std::vector<It> its;
     std::vector<dmrg::Reduce> reds;
     int64_t part = 0;
-    int most = 1;
-    auto put = [&](const It& x) { (x.rs >= 0 ? rs_its : its).push_back(x); };
-    // the runs of one target (one per stage size) are consecutive; all their chunks share one
+    int most = 1, bucket[5] = {0};
+    // the runs of one target are consecutive; all their chunks share one
     // reduction record, so that no two records of the one reduction launch add into the same tile
     for (size_t r0 = 0, r1; r0 < runs.size(); r0 = r1) {
         r1 = r0;
         while (r1 < runs.size() && runs[r1].j == runs[r0].j) ++r1;
-        struct Chunk { int32_t b, e; double cost; int cls, rs; };
+        struct Chunk { int32_t b, e; double cost; int cls; };
         std::vector<Chunk> chunks;
         for (size_t r = r0; r < r1; ++r) {
             const Run& R = runs[r];
             int32_t b = R.tb;
             double c = 0.0;
-            const double cmax = R.rs >= 0 ? rs_caps.cap(R.j, H.tune_lds64_items, 64.0) : caps.cap(R.j, H.tune_lds64_items, 200.0);
+            const double cmax = caps.cap(R.j, H.tune_lds64_items, 200.0);
+            auto close = [&](int32_t e) {
+                int ka4 = 0, kd4 = 0;
+                for (int32_t t = b; t < e; ++t) { ka4 = std::max(ka4, lt[t].ka4); kd4 = std::max(kd4, lt[t].kd4); }
+                chunks.push_back({b, e, c, 8 * dmrg::rs_kclass(ka4, kd4) + dmrg::rs_qclass(R.tq)});
+                bucket[R.bucket]++;
+            };
             for (int32_t t = R.tb; t < R.te; ++t) {
-                const double tc = R.rs >= 0 ? rs_cost(lt[t], R.tq) : cost(lt[t], R.tq);
-                if (c + tc > cmax && t > b) { chunks.push_back({b, t, c, R.cls, R.rs}); b = t; c = 0.0; }
+                const double tc = cost(lt[t], R.tq);
+                if (c + tc > cmax && t > b) { close(t); b = t; c = 0.0; }
                 c += tc;
             }
-            chunks.push_back({b, R.te, c, R.cls, R.rs});
+            close(R.te);
         }
         const int j = runs[r0].j, tm = dmrg::rows_of(H.blk_ma[j]), tn = 16 * runs[r0].tq;
-        if (chunks.size() == 1) {
-            const Chunk& q = chunks[0];
-            put({{H.blk_off[j], -1, H.blk_ma[j], H.blk_md[j], 0, 0, q.b, q.e}, q.cost, q.cls, q.rs});
-            continue;
+        const bool cut = chunks.size() > 1;
+        if (cut) {
+            reds.push_back({H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 0, 0, tm, tn, (int32_t)chunks.size(), 0});
+            most = std::max(most, tm * tn);
         }
-        reds.push_back({H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 0, 0, tm, tn, (int32_t)chunks.size(), 0});
-        most = std::max(most, tm * tn);
         for (const Chunk& q : chunks) {
-            put({{H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 0, 0, q.b, q.e}, q.cost, q.cls, q.rs});
-            part += (int64_t)tm * tn;
+            its.push_back({{H.blk_off[j], cut ? part : -1, H.blk_ma[j], H.blk_md[j], 0, q.cls, q.b, q.e}, q.cost, q.cls});
+            if (cut) part += (int64_t)tm * tn;
         }
     }
-    // register-streamed items: per launch group, the chunks (heaviest first) are dealt to the XCDs by
-    // load; a chunk's row tiles follow one another in its XCD's workgroups and share the tiles they read
-    // in that XCD's caches. Workgroup b runs on XCD b % 8.
-    std::stable_sort(rs_its.begin(), rs_its.end(), [](const It& a, const It& b) { return a.cost > b.cost; });
-    int bucket[dmrg::kLds64Classes] = {0};
-    std::vector<dmrg::Item> rs_items;
+    // per launch group, the items (heaviest first) are dealt to the XCDs by load; an item's row tiles
+    // follow one another in its XCD's workgroups and share the operands they read in that XCD's caches.
+    // Workgroup b runs on XCD b % 8.
+    std::stable_sort(its.begin(), its.end(), [](const It& a, const It& b) { return a.cost > b.cost; });
+    std::vector<dmrg::Item> items;
     for (int g = 0; g < dmrg::kRsGroups; ++g) {
         constexpr int kXcds = 8;
         std::vector<dmrg::Item> list[kXcds];
         double load[kXcds] = {0.0};
-        for (const It& x : rs_its) {
-            if (dmrg::rs_group(x.rs / 8, x.rs % 8) != g) continue;
-            bucket[x.cls]++;
+        for (const It& x : its) {
+            if (dmrg::rs_group(x.cls / 8, x.cls % 8) != g) continue;
             const int to = (int)(std::min_element(load, load + kXcds) - load);
             for (int rt = 0; rt < dmrg::rows_of(x.item.m_ap) / 16; ++rt) {
-                dmrg::Item it = x.item;
-                it.r0 = 16 * rt;
-                it.c0 = x.rs;
-                list[to].push_back(it);
+                list[to].push_back(x.item);
+                list[to].back().r0 = 16 * rt;
                 load[to] += x.cost;
             }
         }
         size_t wgs = 0;
-        for (const auto& v : list) wgs = std::max(wgs, (v.size() + dmrg::kRsWaves - 1) / dmrg::kRsWaves);
+        for (const auto& l : list) wgs = std::max(wgs, (l.size() + dmrg::kRsWaves - 1) / dmrg::kRsWaves);
         dmrg::Item none{};
         none.part_off = -1;                      // t_begin == t_end: no work
         for (size_t w = 0; w < wgs; ++w)
-            for (const auto& v : list)
-                for (size_t i = w * dmrg::kRsWaves; i < (w + 1) * dmrg::kRsWaves; ++i) rs_items.push_back(i < v.size() ? v[i] : none);
-        H.lplan64.rs.begin[g + 1] = (int)rs_items.size();
+            for (const auto& l : list)
+                for (size_t i = w * dmrg::kRsWaves; i < (w + 1) * dmrg::kRsWaves; ++i) items.push_back(i < l.size() ? l[i] : none);
+        H.rplan64.begin[g + 1] = (int)items.size();
     }
-    tag_parts(H, rs_items);
-    dmrg::Item* d_rs = plan_alloc<dmrg::Item>(H, rs_items.size());
-    if (!rs_items.empty())
-        HIPCHK(hipMemcpyAsync(d_rs, rs_items.data(), rs_items.size() * sizeof(dmrg::Item), hipMemcpyHostToDevice, s));
-    H.lplan64.rs.items = d_rs;
-    // LDS-staged items: class, then heaviest item first
-    std::stable_sort(its.begin(), its.end(), [](const It& a, const It& b) {
-        if (a.cls != b.cls) return a.cls < b.cls;
-        return a.cost > b.cost;
-    });
-    std::vector<dmrg::Item> items;
-    items.reserve(its.size());
-    int cnt[dmrg::kLds64Classes] = {0};
-    for (const It& x : its) { items.push_back(x.item); cnt[x.cls]++; }
-    for (int c = 0; c < dmrg::kLds64Classes; ++c) H.lplan64.cls_begin[c + 1] = H.lplan64.cls_begin[c] + cnt[c];
     tag_parts(H, items);
     tag_parts(H, reds);
     dmrg::Item* d_items = plan_alloc<dmrg::Item>(H, items.size());
@@ -1058,23 +1045,20 @@ void build_lds64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large
         HIPCHK(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(items[0]), hipMemcpyHostToDevice, s));
     if (!lt.empty()) HIPCHK(hipMemcpyAsync(d_lt, lt.data(), lt.size() * sizeof(lt[0]), hipMemcpyHostToDevice, s));
     if (!reds.empty()) HIPCHK(hipMemcpyAsync(d_red, reds.data(), reds.size() * sizeof(reds[0]), hipMemcpyHostToDevice, s));
-    H.lplan64.items = d_items;
-    H.lplan64.tasks = d_lt;
-    H.lplan64.reduces = d_red;
-    H.lplan64.n_reduces = (int)reds.size();
-    H.lplan64.red_chunks = (most + 255) / 256;
-    H.lplan64.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part, 1));
-    H.lplan64.partial_size = part;
-    H.lplan64.n_items = (int)(items.size() + rs_its.size());
-    H.lplan64.w7_min_waves = H.tune_lds64_w7 ? 4 : 1;
-    H.lplan64.copy_wave = H.tune_lds64_cw;
-    H.lplan64.three_slots = H.tune_lds64_ns3;
+    H.rplan64.items = d_items;
+    H.rplan64.tasks = d_lt;
+    H.rplan64.reduces = d_red;
+    H.rplan64.n_reduces = (int)reds.size();
+    H.rplan64.red_chunks = (most + 255) / 256;
+    H.rplan64.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part, 1));
+    H.rplan64.partial_size = part;
+    H.rplan64.n_items = (int)its.size();
     if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
         if (e[0] == '1') {
-            std::fprintf(stderr, "[dmrg lds64 plan] items %d classes", H.lplan64.n_items);
-            for (int c = 0; c < dmrg::kLds64Classes; ++c) std::fprintf(stderr, " %d", cnt[c] + bucket[c]);
-            std::fprintf(stderr, " reduces %zu partial %.1f MB register-streamed wavefronts", reds.size(), part * 8e-6);
-            for (int g = 0; g < dmrg::kRsGroups; ++g) std::fprintf(stderr, " %d", H.lplan64.rs.begin[g + 1] - H.lplan64.rs.begin[g]);
+            std::fprintf(stderr, "[dmrg lds64 plan] items %zu classes", its.size());
+            for (int c = 0; c < 5; ++c) std::fprintf(stderr, " %d", bucket[c]);
+            std::fprintf(stderr, " reduces %zu partial %.1f MB wavefronts", reds.size(), part * 8e-6);
+            for (int g = 0; g < dmrg::kRsGroups; ++g) std::fprintf(stderr, " %d", H.rplan64.begin[g + 1] - H.rplan64.begin[g]);
             std::fprintf(stderr, "\n");
         }
     HIPCHK(hipStreamSynchronize(s));
@@ -1089,37 +1073,39 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
     for (void* p : H.plan_allocations) (void)hipFree(p);
     H.plan_allocations.clear();
     H.plan_bytes = 0;
-    // FP64: targets within the 96-wide LDS stages take the LDS-staged kernel; larger ones the
+    // FP64: targets and sources within 128 x 128 take the register-streamed kernel; larger ones the
     // two-pass path where it is cheaper, the one-wave kernel otherwise
     H.bplan64 = dmrg::BigPlan{};
     H.big_chunks64.clear();
-    H.lplan64 = dmrg::LdsPlan64{};
+    H.rplan64 = dmrg::RsPlan64{};
     H.xt64 = nullptr;
+    H.n_packs64 = 0;
     const size_t nb = H.blk.size();
-    std::vector<char> big64(nb, 0), lds64;   // targets of the two-pass path; tasks of the LDS kernel
-    bool any_big = false, any_lds = false;
+    std::vector<char> big64(nb, 0), rs64;   // targets of the two-pass path; tasks of the register-streamed kernel
+    bool any_big = false, any_rs = false;
+    if (H.tune_lds64 || H.tune_big64) {
+        make_op64(H, s);
+        build_pack64(H, s);
+    }
     if (H.tune_lds64) {
-        // the LDS-staged kernel takes the targets within its 112 x 112 tiles: with task routing every
-        // task of such a target whose source fits too, otherwise only targets whose sources all fit
-        make_tiled_f64(H, s);
-        std::vector<char> lds_large = large_targets(H, 16 * lds64_tiles(H));
+        // with task routing a target within 128 x 128 keeps its tasks whose source fits too, otherwise only
+        // targets whose sources all fit are taken
+        std::vector<char> large = large_targets(H, 16 * dmrg::kRsMaxTiles);
         if (H.tune_lds64_task_route)
-            for (size_t j = 0; j < nb; ++j) lds_large[j] = std::max(H.blk_ma[j], H.blk_md[j]) > 16 * lds64_tiles(H);
-        build_lds64_plan(H, s, lds_large, lds64);
-        for (char b : lds64) any_lds |= b != 0;
+            for (size_t j = 0; j < nb; ++j) large[j] = std::max(H.blk_ma[j], H.blk_md[j]) > 16 * dmrg::kRsMaxTiles;
+        build_rs64_plan(H, s, large, rs64);
+        for (char b : rs64) any_rs |= b != 0;
     }
     if (H.tune_big64) {
-        big64 = fp64_big_targets(H, H.tune_big64, &lds64);
+        big64 = fp64_big_targets(H, H.tune_big64, &rs64);
         for (char b : big64) any_big |= b != 0;
     }
-    if (any_big) make_tiled_f64(H, s);
-    if (any_big || any_lds) {
+    if (any_big || any_rs) {
         std::vector<char> rest(nb), rest_tasks(H.tasks.size(), 1);
         for (size_t j = 0; j < nb; ++j) rest[j] = !big64[j];
-        for (size_t t = 0; t < lds64.size(); ++t) rest_tasks[t] = !lds64[t];
+        for (size_t t = 0; t < rs64.size(); ++t) rest_tasks[t] = !rs64[t];
         build_plan_core(H, s, &rest, false, H.plan, H.launches, H.phases, &rest_tasks);
         if (any_big) build_big_plan(H, s, big64, true, &rest_tasks);
-        H.xt64 = plan_alloc<double>(H, (size_t)std::max<int64_t>(H.plan.packed_size, 1));
     } else {
         build_plan_core(H, s, nullptr, false, H.plan, H.launches, H.phases);
     }
