@@ -323,22 +323,22 @@ struct RdmItem {
     int64_t rho_off;
     int32_t ld, ma, ma2, g, g2, cd, n_cd, pad;
 };
-hipError_t launch_rdm_left(const RdmItem* items, int n_items, const int64_t* gblk, const int32_t* cdmd,
-                           const double* psi, double* rho, hipStream_t s);
-// rho^R = psi^T psi with the same items: here ma, ma2 are the column counts of the two psi blocks of
-// each term (their m_d), cdmd[cd + k] the k-th row count (m_a), and the sum runs over rows.
-hipError_t launch_rdm_right(const RdmItem* items, int n_items, const int64_t* gblk, const int32_t* cdmd,
-                            const double* psi, double* rho, hipStream_t s);
+// units: the 32 x 32 tiles of every item (row-major tile index). right: rho^R = psi^T psi with the same
+// items: ma, ma2 are then the column counts of the two psi blocks of each term (their m_d), cdmd[cd + k]
+// the k-th row count (m_a), and the sum runs over rows.
+struct RdmUnit { int32_t item, tile; };
+hipError_t launch_rdm(bool right, const RdmItem* items, const RdmUnit* units, int n_units, const int64_t* gblk,
+                      const int32_t* cdmd, const double* psi, double* rho, hipStream_t s);
 
-// Eq. renorm_mat per sector block, out = O_out^T A O_in, in two passes over the same items:
-// pass 1 T = A O_in (rows_a x k_in, at t_off), pass 2 out = O_out^T T (k_out x k_in, at out_off).
-// A is rows_a x cols_a (= O_out rows x O_in rows), row-major; O matrices are row-major (rows x k).
+// Eq. renorm_mat per sector block, out = O_out^T A O_in (renorm.hip). A is rows x cols (= O_out rows x
+// O_in rows), row-major; O matrices are row-major (rows x k). max_in / max_out: most columns of O_in /
+// O_out of one item.
 struct RenormItem {
-    int64_t a_off, t_off, out_off, oo_off, oi_off;
+    int64_t a_off, out_off, oo_off, oi_off;
     int32_t rows, cols, k_out, k_in;
 };
-hipError_t launch_renormalize(const RenormItem* items, int n_items, int64_t max_t, int64_t max_out, const double* A,
-                              const double* O, double* T, double* out, hipStream_t s);
+hipError_t launch_renormalize(const RenormItem* items, int n_items, int max_in, int max_out, const double* A, const double* O,
+                              double* out, hipStream_t s);
 // Tiled split-BF16 kernels (hpsi_lds.hip).
 hipError_t launch_split_tiled(const double* pool, const PoolBlock* blocks, int n_blocks, uint16_t* tiled, hipStream_t s);
 // y (+)= H x over the LDS plan's targets; zero_y: clear y first (else accumulate into it).

@@ -707,112 +707,4 @@ hipError_t launch_scale(double* x, double a, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------ reduced density matrix
-// rho^L = psi psi^T per enlarged-left sector (Section 2.1), FP64, one workgroup per item; each
-// thread owns output elements and sums over the column groups and columns in a fixed order.
-__global__ void k_rdm_left(const RdmItem* __restrict__ items, const int64_t* __restrict__ gblk,
-                           const int32_t* __restrict__ cdmd, const double* __restrict__ psi,
-                           double* __restrict__ rho) {
-    const RdmItem it = items[blockIdx.x];
-    const int n = it.ma * it.ma2;
-    for (int e = (int)threadIdx.x; e < n; e += (int)blockDim.x) {
-        const int l = e / it.ma2, l2 = e - (e / it.ma2) * it.ma2;
-        double acc = 0.0;
-        for (int k = 0; k < it.n_cd; ++k) {
-            const int md = cdmd[it.cd + k];
-            const double* x = psi + gblk[it.g + k] + (int64_t)l * md;
-            const double* y = psi + gblk[it.g2 + k] + (int64_t)l2 * md;
-            for (int r = 0; r < md; ++r) acc = fma(x[r], y[r], acc);
-        }
-        rho[it.rho_off + (int64_t)l * it.ld + l2] = acc;
-    }
-}
-
-hipError_t launch_rdm_left(const RdmItem* items, int n_items, const int64_t* gblk, const int32_t* cdmd,
-                           const double* psi, double* rho, hipStream_t s) {
-    if (n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rdm_left, dim3((unsigned)n_items), dim3(256), 0, s, items, gblk, cdmd, psi, rho);
-    return hipGetLastError();
-}
-
-// rho^R = psi^T psi per enlarged-right sector: element (r, r2) sums X_k[l][r] X2_k[l][r2] over the
-// sector's row groups k and their rows l (columns r of blocks with ma columns, r2 of blocks with ma2).
-__global__ void k_rdm_right(const RdmItem* __restrict__ items, const int64_t* __restrict__ gblk,
-                            const int32_t* __restrict__ rows, const double* __restrict__ psi,
-                            double* __restrict__ rho) {
-    const RdmItem it = items[blockIdx.x];
-    const int n = it.ma * it.ma2;
-    for (int e = (int)threadIdx.x; e < n; e += (int)blockDim.x) {
-        const int r = e / it.ma2, r2 = e - (e / it.ma2) * it.ma2;
-        double acc = 0.0;
-        for (int k = 0; k < it.n_cd; ++k) {
-            const int ml = rows[it.cd + k];
-            const double* x = psi + gblk[it.g + k] + r;
-            const double* y = psi + gblk[it.g2 + k] + r2;
-            for (int l = 0; l < ml; ++l) acc = fma(x[(int64_t)l * it.ma], y[(int64_t)l * it.ma2], acc);
-        }
-        rho[it.rho_off + (int64_t)r * it.ld + r2] = acc;
-    }
-}
-
-hipError_t launch_rdm_right(const RdmItem* items, int n_items, const int64_t* gblk, const int32_t* cdmd,
-                            const double* psi, double* rho, hipStream_t s) {
-    if (n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_rdm_right, dim3((unsigned)n_items), dim3(256), 0, s, items, gblk, cdmd, psi, rho);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ renormalized operator blocks
-// Eq. renorm_mat, FP64, one workgroup per sector block and pass; each thread owns output elements and
-// sums in a fixed order.
-__global__ void k_renorm_t(const RenormItem* __restrict__ items, const double* __restrict__ A,
-                           const double* __restrict__ O, double* __restrict__ T, int chunk) {
-    const RenormItem it = items[blockIdx.x];
-    const int n = it.rows * it.k_in;
-    const int e0 = (int)blockIdx.y * chunk, e1 = min(n, e0 + chunk);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += (int)blockDim.x) {
-        const int r = e / it.k_in, j = e - (e / it.k_in) * it.k_in;
-        const double* a = A + it.a_off + (int64_t)r * it.cols;
-        const double* o = O + it.oi_off + j;                    // column j of O_in, stride k_in
-        double acc = 0.0;
-        for (int c = 0; c < it.cols; ++c) acc = fma(a[c], o[(int64_t)c * it.k_in], acc);
-        T[it.t_off + e] = acc;
-    }
-}
-
-__global__ void k_renorm_out(const RenormItem* __restrict__ items, const double* __restrict__ O,
-                             const double* __restrict__ T, double* __restrict__ out, int chunk) {
-    const RenormItem it = items[blockIdx.x];
-    const int n = it.k_out * it.k_in;
-    const int e0 = (int)blockIdx.y * chunk, e1 = min(n, e0 + chunk);
-    for (int e = e0 + (int)threadIdx.x; e < e1; e += (int)blockDim.x) {
-        const int i = e / it.k_in, j = e - (e / it.k_in) * it.k_in;
-        const double* o = O + it.oo_off + i;                    // column i of O_out, stride k_out
-        const double* t = T + it.t_off + j;                     // column j of T, stride k_in
-        double acc = 0.0;
-        for (int r = 0; r < it.rows; ++r) acc = fma(o[(int64_t)r * it.k_out], t[(int64_t)r * it.k_in], acc);
-        out[it.out_off + e] = acc;
-    }
-}
-
-// Output elements of one item are cut into chunks of at least 1024 (grid.y <= 65535), so that a few
-// large sector blocks still spread over the chip; max_t / max_out: most elements of one item per pass.
-hipError_t launch_renormalize(const RenormItem* items, int n_items, int64_t max_t, int64_t max_out, const double* A,
-                              const double* O, double* T, double* out, hipStream_t s) {
-    if (n_items <= 0) return hipSuccess;
-    auto grid = [&](int64_t most, int& chunk) {
-        int64_t c = std::max<int64_t>(1024, (most + 65534) / 65535);
-        c = (c + 255) / 256 * 256;
-        chunk = (int)c;
-        return dim3((unsigned)n_items, (unsigned)std::max<int64_t>(1, (most + c - 1) / c));
-    };
-    int ct = 0, co = 0;
-    const dim3 gt = grid(max_t, ct), go = grid(max_out, co);
-    hipLaunchKernelGGL(k_renorm_t, gt, dim3(256), 0, s, items, A, O, T, ct);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_renorm_out, go, dim3(256), 0, s, items, O, T, out, co);
-    return hipGetLastError();
-}
-
 }  // namespace dmrg

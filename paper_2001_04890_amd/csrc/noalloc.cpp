@@ -1,6 +1,6 @@
 // dmrg_renormalize_blocks_noalloc: Eq. renorm_mat per sector block (the work of
 // dmrg_renormalize_blocks, same kernels and summation order) for callers that cannot allocate device
-// memory. Its work list and the intermediate T = A O_in live in one fixed device array, `scratch`,
+// memory. Its work list lives in one fixed device array, `scratch`,
 // of kScratchBytes per GPU, held until the process ends.
 //
 // `scratch` is a device symbol: its name in host code is a host-side stand-in, not a device address.
@@ -23,6 +23,8 @@ using dmrg::Error;
 
 constexpr size_t kScratchBytes = size_t(64) << 20;   // 64 MiB per GPU
 constexpr size_t kAlign = 256;
+constexpr size_t kListBytes = 56;                    // per block, in the limit (an item takes no more)
+static_assert(sizeof(dmrg::RenormItem) <= kListBytes, "work list within the limit");
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
@@ -56,10 +58,10 @@ extern "C" dmrg_status dmrg_renormalize_blocks_noalloc(int32_t device, int32_t n
         const dmrg::RenormWork wk = dmrg::renorm_work(n_sec, dims, kept, o_off, O, o_len, n_blk, sec_out, sec_in,
                                                       a_off, A, a_len, out_off, out, out_len);
         if (wk.items.empty()) return DMRG_OK;
-        // [items | pad to 256 B | T]: every byte the kernels read is written first (items by the copy,
-        // T by the first pass), so nothing is cleared
+        // the documented limit counts [items | pad to 256 B | T = A O_in]; the kernel keeps T in LDS, so
+        // only the items are written
         const size_t items_bytes = wk.items.size() * sizeof(dmrg::RenormItem);
-        const size_t t_at = (items_bytes + kAlign - 1) / kAlign * kAlign;
+        const size_t t_at = (wk.items.size() * kListBytes + kAlign - 1) / kAlign * kAlign;
         if ((uint64_t)wk.t_len > (kScratchBytes - std::min(kScratchBytes, t_at)) / sizeof(double))
             throw Error(DMRG_ERR_NOMEM, "work list + intermediate (" + std::to_string(t_at + wk.t_len * sizeof(double)) +
                                             " bytes) exceed the fixed scratch of " +
@@ -68,10 +70,9 @@ extern "C" dmrg_status dmrg_renormalize_blocks_noalloc(int32_t device, int32_t n
         unsigned char* base = scratch_on(device);
         hipStream_t s = (hipStream_t)stream;
         auto* d_items = reinterpret_cast<dmrg::RenormItem*>(base);
-        auto* d_t = reinterpret_cast<double*>(base + t_at);
         try {
             HIPCHK(hipMemcpyAsync(d_items, wk.items.data(), items_bytes, hipMemcpyHostToDevice, s));
-            HIPCHK(dmrg::launch_renormalize(d_items, (int)wk.items.size(), wk.max_t, wk.max_out, A, O, d_t, out, s));
+            HIPCHK(dmrg::launch_renormalize(d_items, (int)wk.items.size(), wk.max_in, wk.max_out, A, O, out, s));
             HIPCHK(hipStreamSynchronize(s));   // the host work list is read by the copy until here
         } catch (...) {
             (void)hipStreamSynchronize(s);

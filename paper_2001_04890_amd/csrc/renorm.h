@@ -7,11 +7,13 @@
 
 namespace dmrg {
 
-// Work list of Eq. renorm_mat per sector block (out = O_out^T A O_in, two passes through T = A O_in):
-// one item per block that keeps states on both sides, T offsets packed one after another.
+// Work list of Eq. renorm_mat per sector block (out = O_out^T A O_in): one item per block that keeps
+// states on both sides, longest first; t_len: elements of T = A O_in over all items (the scratch limit of
+// dmrg_renormalize_blocks_noalloc is stated in them; the kernel keeps T in LDS).
 struct RenormWork {
     std::vector<RenormItem> items;
-    int64_t t_len = 0, max_t = 0, max_out = 0;
+    int max_in = 0, max_out = 0;                 // most columns of O_in, O_out of one item
+    int64_t t_len = 0;
 };
 
 // Checks every argument of dmrg_renormalize_blocks against the buffer lengths (throws Error with the

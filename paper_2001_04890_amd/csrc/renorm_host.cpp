@@ -148,34 +148,35 @@ dmrg_status rdm_entry(dmrg_hop* H, bool right, const double* psi, double* rho, i
         if (items.size() > (size_t)INT32_MAX) throw Error(DMRG_ERR_UNSUPPORTED, "too many density-matrix items");
         HIPCHK(hipSetDevice(H->device));
         hipStream_t s = (hipStream_t)stream;
-        void *d_items = nullptr, *d_g = nullptr, *d_c = nullptr;
-        auto release = [&]() {
-            if (d_items) (void)hipFree(d_items);
-            if (d_g) (void)hipFree(d_g);
-            if (d_c) (void)hipFree(d_c);
-        };
+        std::vector<dmrg::RdmUnit> units;
+        for (size_t k = 0; k < items.size(); ++k) {
+            const int64_t nt = (int64_t)((items[k].ma + 31) / 32) * ((items[k].ma2 + 31) / 32);
+            for (int64_t t = 0; t < nt; ++t) units.push_back({(int32_t)k, (int32_t)t});
+        }
+        if (units.size() > (size_t)INT32_MAX) throw Error(DMRG_ERR_UNSUPPORTED, "too many density-matrix items");
+        // one allocation and one copy: [gblk | items | units | inner], in decreasing alignment
+        const size_t at_items = gblk.size() * sizeof(int64_t), at_units = at_items + items.size() * sizeof(dmrg::RdmItem),
+                     at_inner = at_units + units.size() * sizeof(dmrg::RdmUnit);
+        std::vector<unsigned char> list(at_inner + inner.size() * sizeof(int32_t));
+        auto put = [&](size_t at, const void* p, size_t n) { if (n) std::memcpy(list.data() + at, p, n); };
+        put(0, gblk.data(), at_items);
+        put(at_items, items.data(), at_units - at_items);
+        put(at_units, units.data(), at_inner - at_units);
+        put(at_inner, inner.data(), list.size() - at_inner);
+        unsigned char* d = nullptr;
         try {
-            HIPCHK(hipMalloc(&d_items, std::max<size_t>(1, items.size()) * sizeof(dmrg::RdmItem)));
-            HIPCHK(hipMalloc(&d_g, std::max<size_t>(1, gblk.size()) * sizeof(int64_t)));
-            HIPCHK(hipMalloc(&d_c, std::max<size_t>(1, inner.size()) * sizeof(int32_t)));
-            if (!items.empty())
-                HIPCHK(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(dmrg::RdmItem), hipMemcpyHostToDevice, s));
-            if (!gblk.empty())
-                HIPCHK(hipMemcpyAsync(d_g, gblk.data(), gblk.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
-            if (!inner.empty())
-                HIPCHK(hipMemcpyAsync(d_c, inner.data(), inner.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-            const auto* di = static_cast<const dmrg::RdmItem*>(d_items);
-            const auto* dg = static_cast<const int64_t*>(d_g);
-            const auto* dc = static_cast<const int32_t*>(d_c);
-            if (right) HIPCHK(dmrg::launch_rdm_right(di, (int)items.size(), dg, dc, psi, rho, s));
-            else HIPCHK(dmrg::launch_rdm_left(di, (int)items.size(), dg, dc, psi, rho, s));
+            HIPCHK(hipMalloc((void**)&d, std::max<size_t>(1, list.size())));
+            if (!list.empty()) HIPCHK(hipMemcpyAsync(d, list.data(), list.size(), hipMemcpyHostToDevice, s));
+            HIPCHK(dmrg::launch_rdm(right, reinterpret_cast<const dmrg::RdmItem*>(d + at_items),
+                                    reinterpret_cast<const dmrg::RdmUnit*>(d + at_units), (int)units.size(),
+                                    reinterpret_cast<const int64_t*>(d), reinterpret_cast<const int32_t*>(d + at_inner), psi, rho, s));
             HIPCHK(hipStreamSynchronize(s));   // the host work lists and scratch end here
         } catch (...) {
             (void)hipStreamSynchronize(s);
-            release();
+            if (d) (void)hipFree(d);
             throw;
         }
-        release();
+        (void)hipFree(d);
         return DMRG_OK;
     } catch (const Error& e) {
         return dmrg::record_error(e);
@@ -326,7 +327,6 @@ dmrg::RenormWork dmrg::renorm_work(int32_t n_sec, const int32_t* dims, const int
         if (ko == 0 || ki == 0) continue;                  // nothing kept on one side: empty block
         RenormItem it{};
         it.a_off = a_off[b];
-        it.t_off = w.t_len;
         it.out_off = out_off[b];
         it.oo_off = o_off[so];
         it.oi_off = o_off[si];
@@ -335,11 +335,14 @@ dmrg::RenormWork dmrg::renorm_work(int32_t n_sec, const int32_t* dims, const int
         it.k_out = (int32_t)ko;
         it.k_in = (int32_t)ki;
         w.items.push_back(it);
+        w.max_in = std::max(w.max_in, it.k_in);
+        w.max_out = std::max(w.max_out, it.k_out);
         w.t_len += rows * ki;
-        w.max_t = std::max(w.max_t, rows * ki);
-        w.max_out = std::max(w.max_out, ko * ki);
     }
     if (w.items.size() > (size_t)INT32_MAX) throw Error(DMRG_ERR_UNSUPPORTED, "too many blocks");
+    std::sort(w.items.begin(), w.items.end(), [](const RenormItem& x, const RenormItem& y) {
+        return (int64_t)x.rows * (x.cols + x.k_out) > (int64_t)y.rows * (y.cols + y.k_out);
+    });
     return w;
 }
 
@@ -352,26 +355,21 @@ extern "C" dmrg_status dmrg_renormalize_blocks(int32_t device, int32_t n_sec, co
     try {
         const dmrg::RenormWork wk = dmrg::renorm_work(n_sec, dims, kept, o_off, O, o_len, n_blk, sec_out, sec_in,
                                                       a_off, A, a_len, out_off, out, out_len);
-        const auto& items = wk.items;
-        if (items.empty()) return DMRG_OK;
+        if (wk.items.empty()) return DMRG_OK;
         HIPCHK(hipSetDevice(device));
         hipStream_t s = (hipStream_t)stream;
-        void *d_items = nullptr, *d_t = nullptr;
+        RenormItem* d = nullptr;
         try {
-            HIPCHK(hipMalloc(&d_items, items.size() * sizeof(dmrg::RenormItem)));
-            HIPCHK(hipMalloc(&d_t, (size_t)std::max<int64_t>(1, wk.t_len) * sizeof(double)));
-            HIPCHK(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(dmrg::RenormItem), hipMemcpyHostToDevice, s));
-            HIPCHK(dmrg::launch_renormalize(static_cast<const dmrg::RenormItem*>(d_items), (int)items.size(), wk.max_t,
-                                            wk.max_out, A, O, static_cast<double*>(d_t), out, s));
-            HIPCHK(hipStreamSynchronize(s));   // the work list and T end here
+            HIPCHK(hipMalloc((void**)&d, wk.items.size() * sizeof(RenormItem)));
+            HIPCHK(hipMemcpyAsync(d, wk.items.data(), wk.items.size() * sizeof(RenormItem), hipMemcpyHostToDevice, s));
+            HIPCHK(dmrg::launch_renormalize(d, (int)wk.items.size(), wk.max_in, wk.max_out, A, O, out, s));
+            HIPCHK(hipStreamSynchronize(s));   // the work list ends here
         } catch (...) {
             (void)hipStreamSynchronize(s);
-            if (d_items) (void)hipFree(d_items);
-            if (d_t) (void)hipFree(d_t);
+            if (d) (void)hipFree(d);
             throw;
         }
-        (void)hipFree(d_items);
-        (void)hipFree(d_t);
+        (void)hipFree(d);
         return DMRG_OK;
     } catch (const Error& e) {
         return dmrg::record_error(e);
