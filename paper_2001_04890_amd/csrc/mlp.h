@@ -69,11 +69,12 @@ hipError_t launch_mlp_pack(const float* p, uint16_t* w1p, uint16_t* w2p, uint16_
 // forward that keeps the hidden activations (FP32, n x 256 each).
 hipError_t launch_mlp_forward(const MlpDev& W, const float* feat, int64_t n, float* out, float* h1, float* h2,
                               double* t_apply, hipStream_t s);
+// loss_part: mlp_loss_parts(n) floats, written by the backward pass and summed into loss by launch_mlp_wgrad
+int mlp_loss_parts(int64_t n);
 hipError_t launch_mlp_backward(const MlpDev& W, const float* aux, const float* m, const float* h1, const float* h2,
-                               int64_t n, float* g, float* d1, float* d2, float* loss_part, float* loss,
-                               hipStream_t s);
+                               int64_t n, float* g, float* d1, float* d2, float* loss_part, hipStream_t s);
 hipError_t launch_mlp_wgrad(const float* x, const float* h1, const float* h2, const float* d1, const float* d2,
-                            const float* g, int64_t n, float* grad, hipStream_t s);
+                            const float* g, int64_t n, const float* loss_part, float* grad, float* loss, hipStream_t s);
 hipError_t launch_mlp_adam(float* p, const float* grad, float* m1, float* m2, float lr, int step, hipStream_t s);
 // out[0..3] = sum of squares of r, u, t and D - theta; part: 4 * mlp_reduce_blocks(n) doubles
 hipError_t launch_mlp_norms(const double* r, const double* u, const double* t, const double* d, double theta,

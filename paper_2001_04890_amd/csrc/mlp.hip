@@ -22,6 +22,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+
 #include "mlp.h"
 
 namespace dmrg {
@@ -41,13 +42,18 @@ __device__ __forceinline__ uint16_t f32_to_bf16_bits(float f) {
     return (uint16_t)(u >> 16);
 }
 
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-    return (uint32_t)f32_to_bf16_bits(a) | ((uint32_t)f32_to_bf16_bits(b) << 16);
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack2(float a, float b) {   // (one v_cvt_pk_bf16_f32, nearest even)
+    return __builtin_bit_cast(uint32_t, bf16x2{(__bf16)a, (__bf16)b});
 }
 
 __device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
                                                   0, 0);
+}
+
+__device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
 unsigned grid_of(int64_t n, int per) {
@@ -161,16 +167,17 @@ __global__ void k_mlp_pack(const float* __restrict__ p, uint16_t* __restrict__ w
 }
 
 // ------------------------------------------------------------------ forward (BF16, matrix cores)
-template <bool TRAIN>
-__global__ __launch_bounds__(64) void k_mlp_fwd_mfma(const MlpDev W, const float* __restrict__ feat, int64_t n,
-                                                     float* __restrict__ out, float* __restrict__ h1o,
-                                                     float* __restrict__ h2o, double* __restrict__ t_apply) {
-    const int l = threadIdx.x, g = l >> 4, c = l & 15;
-    const int64_t row0 = (int64_t)blockIdx.x * 64;
+// m of rows row0 .. row0 + 16 RT - 1 by one wavefront, weights in LDS.
+template <int RT>
+__device__ __forceinline__ void mlp_rows(const u32x4* w1p, const u32x4* w2p, const float4* b1v, const float4* b2v,
+                                         const float4* w3v, float b3, const float* __restrict__ feat, int64_t n, int64_t row0,
+                                         int l, float* __restrict__ out, double* __restrict__ t_apply) {
+    asm volatile("" ::: "memory");   // keeps the weights' reads here (the registers hold h1)
+    const int g = l >> 4, c = l & 15;
     // layer-1 B operand (X^T, K padded to 32): lane holds X[row][8g .. 8g+7] for g < 2
-    u32x4 xb[4];
+    u32x4 xb[RT];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
         const int64_t row = row0 + 16 * rt + c;
         xb[rt] = u32x4{0u, 0u, 0u, 0u};
         if (g < 2 && row < n) {
@@ -179,62 +186,45 @@ __global__ __launch_bounds__(64) void k_mlp_fwd_mfma(const MlpDev W, const float
             xb[rt] = u32x4{pack2(a.x, a.y), pack2(a.z, a.w), pack2(b.x, b.y), pack2(b.z, b.w)};
         }
     }
-    const u32x4* w1p = reinterpret_cast<const u32x4*>(W.w1p);
-    const u32x4* w2p = reinterpret_cast<const u32x4*>(W.w2p);
-    const float4* b1v = reinterpret_cast<const float4*>(W.p + kOffB1);
-    const float4* b2v = reinterpret_cast<const float4*>(W.p + kOffB2);
-    const float4* w3v = reinterpret_cast<const float4*>(W.p + kOffW3);
-    // layer 1 -> h1 as BF16 pairs: h1p[u][rt] = units 16u + 4g + {0,1 | 2,3} of row 16rt + c
-    uint32_t h1p[16][4][2];
+    // layer 1 -> h1 as BF16 pairs: hb[u / 2][rt], halves u % 2 = units 16u + 4g + {0,1 | 2,3} of row 16rt + c
+    u32x4 hb[8][RT];
 #pragma unroll
     for (int uu = 0; uu < 16; ++uu) {
         const u32x4 a = w1p[uu * 64 + l];
         const float4 bb = b1v[4 * uu + g];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
-            f32x4 acc = mfma_bf16(a, xb[rt], f32x4{0.f, 0.f, 0.f, 0.f});
-            const float h0 = fmaxf(acc[0] + bb.x, 0.f), h1 = fmaxf(acc[1] + bb.y, 0.f);
-            const float h2 = fmaxf(acc[2] + bb.z, 0.f), h3 = fmaxf(acc[3] + bb.w, 0.f);
-            h1p[uu][rt][0] = pack2(h0, h1);
-            h1p[uu][rt][1] = pack2(h2, h3);
-            if (TRAIN) {
-                const int64_t row = row0 + 16 * rt + c;
-                if (row < n) *reinterpret_cast<float4*>(h1o + row * kMlpHidden + 16 * uu + 4 * g) = make_float4(h0, h1, h2, h3);
-            }
+        for (int rt = 0; rt < RT; ++rt) {
+            const f32x4 acc = mfma_bf16(a, xb[rt], f32x4{0.f, 0.f, 0.f, 0.f});
+            hb[uu >> 1][rt][2 * (uu & 1)] = pack2(fmaxf(acc[0] + bb.x, 0.f), fmaxf(acc[1] + bb.y, 0.f));
+            hb[uu >> 1][rt][2 * (uu & 1) + 1] = pack2(fmaxf(acc[2] + bb.z, 0.f), fmaxf(acc[3] + bb.w, 0.f));
         }
     }
     // layer 2 and the output dot product
-    float part[4] = {0.f, 0.f, 0.f, 0.f};
+    float part[RT];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) part[rt] = 0.f;
 #pragma unroll 1
     for (int o = 0; o < 16; ++o) {
-        f32x4 acc[4];
+        f32x4 acc[RT];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const u32x4 a = w2p[(o * 8 + q) * 64 + l];
 #pragma unroll
-            for (int rt = 0; rt < 4; ++rt) {
-                const u32x4 b = u32x4{h1p[2 * q][rt][0], h1p[2 * q][rt][1], h1p[2 * q + 1][rt][0], h1p[2 * q + 1][rt][1]};
-                acc[rt] = mfma_bf16(a, b, acc[rt]);
-            }
+            for (int rt = 0; rt < RT; ++rt) acc[rt] = mfma_bf16(a, hb[q][rt], acc[rt]);
         }
         const float4 bb = b2v[4 * o + g];
         const float4 ww = w3v[4 * o + g];
 #pragma unroll
-        for (int rt = 0; rt < 4; ++rt) {
+        for (int rt = 0; rt < RT; ++rt) {
             const float h0 = fmaxf(acc[rt][0] + bb.x, 0.f), h1 = fmaxf(acc[rt][1] + bb.y, 0.f);
             const float h2 = fmaxf(acc[rt][2] + bb.z, 0.f), h3 = fmaxf(acc[rt][3] + bb.w, 0.f);
             part[rt] += h0 * ww.x + h1 * ww.y + h2 * ww.z + h3 * ww.w;
-            if (TRAIN) {
-                const int64_t row = row0 + 16 * rt + c;
-                if (row < n) *reinterpret_cast<float4*>(h2o + row * kMlpHidden + 16 * o + 4 * g) = make_float4(h0, h1, h2, h3);
-            }
         }
     }
-    const float b3 = W.p[kOffB3];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
         float v = part[rt];
         v += __shfl_xor(v, 16, 64);
         v += __shfl_xor(v, 32, 64);
@@ -244,6 +234,105 @@ __global__ __launch_bounds__(64) void k_mlp_fwd_mfma(const MlpDev W, const float
             if (out) out[row] = m;
             if (t_apply) t_apply[row] *= 1.0 + (double)m;
         }
+    }
+}
+
+// Inference over many rows: one workgroup of eight wavefronts per CU keeps the weights (147 KB, W1 and W2 in
+// fragment order) in LDS and takes 64 rows per wavefront at a time. 64 rows are 512 MFMAs of 16 cycles and about as many
+// cycles of vector work, against 128 KB of W2: from the L2s that traffic bound the kernel (660,770 rows in
+// 116 us with a wavefront per workgroup).
+constexpr int kFwdWaves = 8, kFwdLds = (16 * 64 + 16 * 8 * 64) * 16 + 3 * kMlpHidden * 4;   // bytes: W1, W2, b1, b2, w3
+__global__ __launch_bounds__(kFwdWaves * 64, 2) void k_mlp_fwd_mfma(const MlpDev W, const float* __restrict__ feat, int64_t n,
+                                                                 float* __restrict__ out, double* __restrict__ t_apply) {
+    extern __shared__ u32x4 wl[];
+    u32x4 *w1p = wl, *w2p = wl + 16 * 64;
+    float4 *b1v = reinterpret_cast<float4*>(w2p + 16 * 8 * 64), *b2v = b1v + kMlpHidden / 4, *w3v = b2v + kMlpHidden / 4;
+    const int j = (int)threadIdx.x;
+    for (int i = j; i < 16 * 64; i += kFwdWaves * 64) w1p[i] = reinterpret_cast<const u32x4*>(W.w1p)[i];
+#pragma unroll 4
+    for (int i = j; i < 16 * 8 * 64; i += kFwdWaves * 64) w2p[i] = reinterpret_cast<const u32x4*>(W.w2p)[i];
+    if (j < kMlpHidden / 4) {
+        b1v[j] = reinterpret_cast<const float4*>(W.p + kOffB1)[j];
+        b2v[j] = reinterpret_cast<const float4*>(W.p + kOffB2)[j];
+        w3v[j] = reinterpret_cast<const float4*>(W.p + kOffW3)[j];
+    }
+    const int l = j & 63;
+    const float b3 = W.p[kOffB3];
+    __syncthreads();
+    // whole rounds of 64 rows per wavefront, then what is left in pieces of 16 (a round of few 64-row chunks
+    // would take as long as a full one)
+    const int64_t stride = (int64_t)gridDim.x * kFwdWaves, first = (int64_t)(j >> 6) * gridDim.x + blockIdx.x;
+    const int64_t rounds = n / (64 * stride);
+    for (int64_t k = 0; k < rounds; ++k)
+        mlp_rows<4>(w1p, w2p, b1v, b2v, w3v, b3, feat, n, 64 * (first + k * stride), l, out, t_apply);
+    for (int64_t row0 = 64 * stride * rounds + 16 * first; row0 < n; row0 += 16 * stride)
+        mlp_rows<1>(w1p, w2p, b1v, b2v, w3v, b3, feat, n, row0, l, out, t_apply);
+}
+
+// Minibatches (TRAIN: keeping the hidden activations) and small inference calls: 16 rows per workgroup of four
+// wavefronts, which each compute layer 1 for themselves and a quarter of layer 2's units; the output's terms
+// meet in LDS and are added in unit order, so m is that of k_mlp_fwd_mfma bit for bit. 4096 rows are 256
+// workgroups here; as 64 wavefronts of 64 rows, each walking all of W2 alone, they took 38 us.
+template <bool TRAIN>
+__global__ __launch_bounds__(256) void k_mlp_fwd_rows(const MlpDev W, const float* __restrict__ feat, int64_t n,
+                                                      float* __restrict__ out, float* __restrict__ h1o,
+                                                      float* __restrict__ h2o, double* __restrict__ t_apply) {
+    __shared__ float terms[16][64];
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, g = l >> 4, c = l & 15;
+    const int64_t row = (int64_t)blockIdx.x * 16 + c;
+    const u32x4* w1p = reinterpret_cast<const u32x4*>(W.w1p);
+    const u32x4* w2p = reinterpret_cast<const u32x4*>(W.w2p);
+    const float4* b1v = reinterpret_cast<const float4*>(W.p + kOffB1);
+    const float4* b2v = reinterpret_cast<const float4*>(W.p + kOffB2);
+    const float4* w3v = reinterpret_cast<const float4*>(W.p + kOffW3);
+    u32x4 w2f[4][8];                                   // the wavefront's quarter of W2
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) w2f[i][q] = w2p[((4 * wave + i) * 8 + q) * 64 + l];
+    u32x4 xb = u32x4{0u, 0u, 0u, 0u};
+    if (g < 2 && row < n) {
+        const float4* src = reinterpret_cast<const float4*>(feat + row * kMlpIn + 8 * g);
+        const float4 a = src[0], b = src[1];
+        xb = u32x4{pack2(a.x, a.y), pack2(a.z, a.w), pack2(b.x, b.y), pack2(b.z, b.w)};
+    }
+    uint32_t h1p[16][2];
+#pragma unroll
+    for (int uu = 0; uu < 16; ++uu) {
+        const float4 bb = b1v[4 * uu + g];
+        const f32x4 acc = mfma_bf16(w1p[uu * 64 + l], xb, f32x4{0.f, 0.f, 0.f, 0.f});
+        const float h0 = fmaxf(acc[0] + bb.x, 0.f), h1 = fmaxf(acc[1] + bb.y, 0.f);
+        const float h2 = fmaxf(acc[2] + bb.z, 0.f), h3 = fmaxf(acc[3] + bb.w, 0.f);
+        h1p[uu][0] = pack2(h0, h1);
+        h1p[uu][1] = pack2(h2, h3);
+        if (TRAIN && (uu >> 2) == wave && row < n)
+            *reinterpret_cast<float4*>(h1o + row * kMlpHidden + 16 * uu + 4 * g) = make_float4(h0, h1, h2, h3);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int o = 4 * wave + i;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            acc = mfma_bf16(w2f[i][q], u32x4{h1p[2 * q][0], h1p[2 * q][1], h1p[2 * q + 1][0], h1p[2 * q + 1][1]}, acc);
+        const float4 bb = b2v[4 * o + g];
+        const float4 ww = w3v[4 * o + g];
+        const float h0 = fmaxf(acc[0] + bb.x, 0.f), h1 = fmaxf(acc[1] + bb.y, 0.f);
+        const float h2 = fmaxf(acc[2] + bb.z, 0.f), h3 = fmaxf(acc[3] + bb.w, 0.f);
+        terms[o][l] = h0 * ww.x + h1 * ww.y + h2 * ww.z + h3 * ww.w;
+        if (TRAIN && row < n) *reinterpret_cast<float4*>(h2o + row * kMlpHidden + 16 * o + 4 * g) = make_float4(h0, h1, h2, h3);
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    float v = 0.f;
+#pragma unroll
+    for (int o = 0; o < 16; ++o) v += terms[o][l];
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (g == 0 && row < n) {
+        const float m = v + W.p[kOffB3];
+        if (out) out[row] = m;
+        if (t_apply) t_apply[row] *= 1.0 + (double)m;
     }
 }
 
@@ -298,16 +387,22 @@ __global__ __launch_bounds__(256) void k_mlp_fwd_f32(const MlpDev W, const float
 
 // ------------------------------------------------------------------ backward
 // loss = (1/B) sum_r w_r (a_r (1 + m_r) - b_r)^2 over the B rows of the minibatch.
-// Per row: g = dloss/dm, d2 = g w3 [h2 > 0], d1 = (d2 W2^T) [h1 > 0]; thread j owns unit j.
+// Per row: g = dloss/dm, d2 = g w3 [h2 > 0], d1 = (d2 W2^T) [h1 > 0].
+// The contractions run on v_mfma_f32_16x16x4_f32 (FP32 throughout), which adds its four products one after
+// another, so every sum is the same chain of fused multiply-adds as a scalar loop over its index.
+//
+// Workgroup: 64 rows (four wavefronts of 16) and 64 of layer 1's units (blockIdx.y; the first column writes
+// g and the loss). D2 and the units' rows of W2 are staged in LDS as FP32.
 __global__ __launch_bounds__(256) void k_mlp_backward(const MlpDev W, const float* __restrict__ aux,
                                                       const float* __restrict__ m, const float* __restrict__ h1,
                                                       const float* __restrict__ h2, int64_t n, float inv_b,
                                                       float* __restrict__ g_out, float* __restrict__ d1,
                                                       float* __restrict__ d2, float* __restrict__ loss_part) {
     __shared__ float D2[kRows][kMlpHidden + 1];
+    __shared__ float W2[64][kMlpHidden + 1];
     __shared__ float G[kRows];
     __shared__ float Lp[kRows];
-    const int j = threadIdx.x;
+    const int j = threadIdx.x, cg = (int)blockIdx.y;
     const int64_t row0 = (int64_t)blockIdx.x * kRows;
     if (j < kRows) {
         float gg = 0.f, ll = 0.f;
@@ -316,35 +411,52 @@ __global__ __launch_bounds__(256) void k_mlp_backward(const MlpDev W, const floa
             const float e = a * (1.f + m[row0 + j]) - b;
             gg = 2.f * inv_b * w * a * e;
             ll = inv_b * w * e * e;
-            g_out[row0 + j] = gg;
+            if (cg == 0) g_out[row0 + j] = gg;
         }
         G[j] = gg;
         Lp[j] = ll;
     }
     const float w3 = W.p[kOffW3 + j];
+    if (W.fp32) {
+#pragma unroll 16
+        for (int u = 0; u < 64; ++u) W2[u][j] = W.p[kOffW2 + (64 * cg + u) * kMlpHidden + j];
+    } else {
+#pragma unroll 32
+        for (int u = 0; u < 64; ++u) W2[u][j] = bf16_bits_to_f32(W.w2[(64 * cg + u) * kMlpHidden + j]);
+    }
     __syncthreads();
+#pragma unroll 32
+    for (int r = 0; r < kRows; ++r) {
+        const int64_t row = row0 + r, rc = row < n ? row : n - 1;
+        D2[r][j] = h2[rc * kMlpHidden + j];
+    }
+#pragma unroll 8
     for (int r = 0; r < kRows; ++r) {
         const int64_t row = row0 + r;
-        float v = 0.f;
-        if (row < n) {
-            v = h2[row * kMlpHidden + j] > 0.f ? G[r] * w3 : 0.f;
-            d2[row * kMlpHidden + j] = v;
-        }
+        const float v = row < n && D2[r][j] > 0.f ? G[r] * w3 : 0.f;
+        if (row < n && (j >> 6) == cg) d2[row * kMlpHidden + j] = v;
         D2[r][j] = v;
     }
     __syncthreads();
-    for (int r = 0; r < kRows; ++r) {
-        const int64_t row = row0 + r;
-        if (row >= n) break;
-        float s = 0.f;
-        if (W.fp32) {
-            for (int q = 0; q < kMlpHidden; ++q) s += D2[r][q] * W.p[kOffW2 + j * kMlpHidden + q];
-        } else {
-            for (int q = 0; q < kMlpHidden; ++q) s += D2[r][q] * bf16_bits_to_f32(W.w2[j * kMlpHidden + q]);
-        }
-        d1[row * kMlpHidden + j] = h1[row * kMlpHidden + j] > 0.f ? s : 0.f;
+    const int wave = j >> 6, l = j & 63, li = l & 15, g = l >> 4;
+    f32x4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int q = 0; q < kMlpHidden; q += 4) {
+        const float a = D2[16 * wave + li][q + g];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[t] = mfma_f32(a, W2[16 * t + li][q + g], acc[t]);
     }
-    if (j == 0) {
+    // acc[t][v] = d1 before its mask at row 16 wave + 4 g + v, unit 64 cg + 16 t + li
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t row = row0 + 16 * wave + 4 * g + v, at = row * kMlpHidden + 64 * cg + 16 * t + li;
+            if (row < n) d1[at] = h1[at] > 0.f ? acc[t][v] : 0.f;
+        }
+    if (j == 0 && cg == 0) {
         float s = 0.f;
         for (int r = 0; r < kRows; ++r) s += Lp[r];
         loss_part[blockIdx.x] = s;
@@ -353,32 +465,99 @@ __global__ __launch_bounds__(256) void k_mlp_backward(const MlpDev W, const floa
 
 // Parameter gradients, each a sum over the minibatch rows in row order:
 //   dW1[k][j] = sum_r x[r][k] d1[r][j], db1 = sum d1, dW2[k][j] = sum_r h1[r][k] d2[r][j], db2 = sum d2,
-//   dw3[j] = sum_r g[r] h2[r][j], db3 = sum g.
-__global__ void k_mlp_wgrad(const float* __restrict__ x, const float* __restrict__ h1, const float* __restrict__ h2,
-                            const float* __restrict__ d1, const float* __restrict__ d2, const float* __restrict__ g,
-                            int64_t n, float* __restrict__ grad) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= kMlpParams) return;
-    float s = 0.f;
-    if (p < kOffB1) {
-        const int k = (int)(p / kMlpHidden), jj = (int)(p % kMlpHidden);
-        for (int64_t r = 0; r < n; ++r) s += x[r * kMlpIn + k] * d1[r * kMlpHidden + jj];
-    } else if (p < kOffW2) {
-        const int jj = (int)(p - kOffB1);
-        for (int64_t r = 0; r < n; ++r) s += d1[r * kMlpHidden + jj];
-    } else if (p < kOffB2) {
-        const int k = (int)((p - kOffW2) / kMlpHidden), jj = (int)((p - kOffW2) % kMlpHidden);
-        for (int64_t r = 0; r < n; ++r) s += h1[r * kMlpHidden + k] * d2[r * kMlpHidden + jj];
-    } else if (p < kOffW3) {
-        const int jj = (int)(p - kOffB2);
-        for (int64_t r = 0; r < n; ++r) s += d2[r * kMlpHidden + jj];
-    } else if (p < kOffB3) {
-        const int jj = (int)(p - kOffW3);
-        for (int64_t r = 0; r < n; ++r) s += g[r] * h2[r * kMlpHidden + jj];
-    } else {
-        for (int64_t r = 0; r < n; ++r) s += g[r];
+//   dw3[j] = sum_r g[r] h2[r][j], db3 = sum g,
+// and the loss, the sum of its workgroup parts. Workgroup: a 32 x 32 tile of a product left^T right over the
+// rows (2 x 2 MFMA tiles, one a wavefront), where left is h1, [x | 1], 1 or g and right d2, d1, h2, g or the
+// parts. Bound by the chain of n / 4 MFMAs of 32 cycles (14 us at n = 4096), if the rows arrive in time: only
+// some 90 of the CUs have a workgroup, so each keeps four stages of 128 rows in flight in its registers (loads
+// of single k steps left 274 us, one thread per parameter took 1.0 ms).
+constexpr int kWgStage = 128, kWgLd = 80, kWgAhead = 4;   // rows a stage; LDS row stride (rows g: 16 banks apart)
+constexpr int kWgW2 = 64, kWgUnits = kWgW2 + 8 + 8 + 8 + 2;
+struct WgIn {
+    const float *x, *h1, *h2, *d1, *d2, *g, *loss_part;
+    int64_t n;
+    int n_part;
+};
+
+// KIND: 0 dW2, 1 dW1 and db1, 2 db2, 3 dw3, 4 db3, 5 the loss; k0, j0: first row and column of the tile.
+// Loads go straight to registers (vectors, or the scalars g and parts); constants, zeros and the end of the
+// rows come in on the way to LDS, so that nothing waits for a load before its stage.
+template <int KIND>
+__device__ __forceinline__ void wgrad_tile(const WgIn& in, int k0, int j0, float (*lds)[kWgStage * kWgLd],
+                                           float* __restrict__ grad, float* __restrict__ loss) {
+    constexpr bool VEC = KIND < 4, SCALAR = KIND >= 3;
+    const int j = (int)threadIdx.x;
+    const int64_t rows = KIND == 5 ? in.n_part : in.n;
+    // thread j stages columns c4 .. c4 + 3 (left factor 0 .. 31, right 32 .. 63) of rows r0 + 16 i
+    const int c4 = 4 * (j & 15), r0 = j >> 4;
+    const bool is_left = c4 < 32, is_x = KIND == 1 && c4 < kMlpIn;
+    const float* right = KIND == 1 ? in.d1 : KIND == 3 ? in.h2 : in.d2;
+    const float* vec = is_x ? in.x + c4 : KIND == 0 && is_left ? in.h1 + k0 + c4 : right + j0 + (is_left ? 0 : c4 - 32);
+    const int ld = is_x ? kMlpIn : kMlpHidden;
+    const float* sc = KIND == 5 ? in.loss_part : in.g;
+    const float one = c4 == (KIND == 1 ? kMlpIn : 0) ? 1.f : 0.f;
+    constexpr int kLoads = kWgStage / 16;
+    float4 vb[kWgAhead][kLoads];
+    float sb[kWgAhead][kLoads];
+    auto load = [&](int64_t stage, float4 (&v)[kLoads], float (&f)[kLoads]) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) {
+            const int64_t row = stage * kWgStage + r0 + 16 * i, r = row < rows ? row : rows - 1;
+            if constexpr (VEC) v[i] = *reinterpret_cast<const float4*>(vec + r * ld);
+            if constexpr (SCALAR) f[i] = sc[r];
+        }
+    };
+    auto value = [&](int64_t row, const float4& v, float f) {
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (row >= rows) return t;
+        if constexpr (KIND == 0) return v;
+        if constexpr (KIND == 1) { if (is_x || !is_left) return v; t.x = one; }
+        if constexpr (KIND == 2) { if (!is_left) return v; t.x = one; }
+        if constexpr (KIND == 3) { if (!is_left) return v; t.x = c4 == 0 ? f : 0.f; }
+        if constexpr (KIND >= 4) t.x = is_left ? one : c4 == 32 ? f : 0.f;
+        return t;
+    };
+    const int wave = j >> 6, l = j & 63, li = l & 15, g = l >> 4, ti = wave >> 1, tj = wave & 1;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const int64_t stages = (rows + kWgStage - 1) / kWgStage;
+#pragma unroll
+    for (int s = 0; s < kWgAhead; ++s) load(s, vb[s], sb[s]);
+    for (int64_t s0 = 0; s0 < stages; s0 += kWgAhead) {
+#pragma unroll
+        for (int k = 0; k < kWgAhead; ++k) {       // past the last stage: zeros
+            float* t = lds[k & 1];
+#pragma unroll
+            for (int i = 0; i < kLoads; ++i)
+                *reinterpret_cast<float4*>(t + (r0 + 16 * i) * kWgLd + c4) = value((s0 + k) * kWgStage + r0 + 16 * i, vb[k][i], sb[k][i]);
+            load(s0 + kWgAhead + k, vb[k], sb[k]);
+            __syncthreads();                       // (the other half is read until the next barrier)
+            const float *pa = t + g * kWgLd + 16 * ti + li, *pb = t + g * kWgLd + 32 + 16 * tj + li;
+#pragma unroll
+            for (int q = 0; q < kWgStage / 4; ++q) acc = mfma_f32(pa[4 * q * kWgLd], pb[4 * q * kWgLd], acc);
+        }
     }
-    grad[p] = s;
+    // acc[v] = row 16 ti + 4 g + v, column 16 tj + li of the workgroup's tile
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int row = 16 * ti + 4 * g + v, col = j0 + 16 * tj + li;
+        if (KIND == 0) grad[kOffW2 + (k0 + row) * kMlpHidden + col] = acc[v];
+        else if (KIND == 1 && row < kMlpIn) grad[row * kMlpHidden + col] = acc[v];
+        else if (KIND == 1 && row == kMlpIn) grad[kOffB1 + col] = acc[v];
+        else if (KIND == 2 && row == 0) grad[kOffB2 + col] = acc[v];
+        else if (KIND == 3 && row == 0) grad[kOffW3 + col] = acc[v];
+        else if (KIND >= 4 && row == 0 && col == 0) *(KIND == 4 ? grad + kOffB3 : loss) = acc[v];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_mlp_wgrad(const WgIn in, float* __restrict__ grad, float* __restrict__ loss) {
+    __shared__ __attribute__((aligned(16))) float lds[2][kWgStage * kWgLd];
+    const int u = (int)blockIdx.x, j0 = 32 * (u & 7);
+    if (u < kWgW2) wgrad_tile<0>(in, 32 * (u >> 3), j0, lds, grad, loss);
+    else if (u < kWgW2 + 8) wgrad_tile<1>(in, 0, j0, lds, grad, loss);
+    else if (u < kWgW2 + 16) wgrad_tile<2>(in, 0, j0, lds, grad, loss);
+    else if (u < kWgW2 + 24) wgrad_tile<3>(in, 0, j0, lds, grad, loss);
+    else if (u == kWgUnits - 2) wgrad_tile<4>(in, 0, 0, lds, grad, loss);
+    else wgrad_tile<5>(in, 0, 0, lds, grad, loss);
 }
 
 // Adam (bias-corrected moments) on the FP32 parameters.
@@ -392,15 +571,6 @@ __global__ void k_mlp_adam(float* __restrict__ p, const float* __restrict__ grad
     m1[i] = a;
     m2[i] = v;
     p[i] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
-}
-
-// out[0] = sum of the per-workgroup partial losses (fixed order)
-__global__ void k_mlp_sum(const float* __restrict__ v, int n, float* __restrict__ out) {
-    if (threadIdx.x == 0) {
-        float s = 0.f;
-        for (int i = 0; i < n; ++i) s += v[i];
-        out[0] = s;
-    }
 }
 
 // ------------------------------------------------------------------ launchers
@@ -432,6 +602,11 @@ hipError_t launch_mlp_pack(const float* p, uint16_t* w1p, uint16_t* w2p, uint16_
     return hipGetLastError();
 }
 
+constexpr int kCus = 256;
+// From here on inference keeps the weights in LDS: filling 147 KB costs 12 us, below 11 us the row kernel is
+// done (700 rows: 4.5 us against 11.9; 16,384: 11.3 against 12.5; 32,768: 20.1 against 12.8).
+constexpr int64_t kLdsRows = 18000;
+
 hipError_t launch_mlp_forward(const MlpDev& W, const float* feat, int64_t n, float* out, float* h1, float* h2,
                               double* t_apply, hipStream_t s) {
     if (n == 0) return hipSuccess;
@@ -443,29 +618,36 @@ hipError_t launch_mlp_forward(const MlpDev& W, const float* feat, int64_t n, flo
         else
             hipLaunchKernelGGL(k_mlp_fwd_f32<false>, dim3(nb), dim3(256), 0, s, W, feat, n, out, h1, h2, t_apply);
     } else {
-        const unsigned nb = (unsigned)((n + 63) / 64);
-        if (train)
-            hipLaunchKernelGGL(k_mlp_fwd_mfma<true>, dim3(nb), dim3(64), 0, s, W, feat, n, out, h1, h2, t_apply);
-        else
-            hipLaunchKernelGGL(k_mlp_fwd_mfma<false>, dim3(nb), dim3(64), 0, s, W, feat, n, out, h1, h2, t_apply);
+        // the row kernel reads W2 once per 16 rows from the L2s, the other fills 144 KB of LDS first
+        const unsigned nr = (unsigned)((n + 15) / 16);
+        if (train) {
+            hipLaunchKernelGGL(k_mlp_fwd_rows<true>, dim3(nr), dim3(256), 0, s, W, feat, n, out, h1, h2, t_apply);
+        } else if (n < kLdsRows) {
+            hipLaunchKernelGGL(k_mlp_fwd_rows<false>, dim3(nr), dim3(256), 0, s, W, feat, n, out, nullptr, nullptr, t_apply);
+        } else {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_mlp_fwd_mfma),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, kFwdLds);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(k_mlp_fwd_mfma, dim3(kCus), dim3(kFwdWaves * 64), kFwdLds, s, W, feat, n, out, t_apply);
+        }
     }
     return hipGetLastError();
 }
 
+int mlp_loss_parts(int64_t n) { return (int)((n + kRows - 1) / kRows); }
+
 hipError_t launch_mlp_backward(const MlpDev& W, const float* aux, const float* m, const float* h1, const float* h2,
-                               int64_t n, float* g, float* d1, float* d2, float* loss_part, float* loss,
-                               hipStream_t s) {
-    const unsigned nb = (unsigned)((n + kRows - 1) / kRows);
-    if (nb == 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_mlp_backward, dim3(nb), dim3(256), 0, s, W, aux, m, h1, h2, n, 1.f / (float)n, g, d1, d2,
-                       loss_part);
-    hipLaunchKernelGGL(k_mlp_sum, dim3(1), dim3(64), 0, s, loss_part, (int)nb, loss);
+                               int64_t n, float* g, float* d1, float* d2, float* loss_part, hipStream_t s) {
+    if (n <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_mlp_backward, dim3((unsigned)mlp_loss_parts(n), kMlpHidden / 64), dim3(256), 0, s, W, aux, m, h1, h2, n,
+                       1.f / (float)n, g, d1, d2, loss_part);
     return hipGetLastError();
 }
 
 hipError_t launch_mlp_wgrad(const float* x, const float* h1, const float* h2, const float* d1, const float* d2,
-                            const float* g, int64_t n, float* grad, hipStream_t s) {
-    hipLaunchKernelGGL(k_mlp_wgrad, dim3((kMlpParams + 255) / 256), dim3(256), 0, s, x, h1, h2, d1, d2, g, n, grad);
+                            const float* g, int64_t n, const float* loss_part, float* grad, float* loss, hipStream_t s) {
+    hipLaunchKernelGGL(k_mlp_wgrad, dim3(kWgUnits), dim3(256), 0, s, WgIn{x, h1, h2, d1, d2, g, loss_part, n, mlp_loss_parts(n)},
+                       grad, loss);
     return hipGetLastError();
 }
 

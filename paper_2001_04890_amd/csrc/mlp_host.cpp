@@ -105,9 +105,9 @@ void grad_step(dmrg_mlp* M, const float* x, const float* aux, int64_t n, float l
     const MlpDev W = M->dev();
     HIPCHK(launch_mlp_forward(W, x, n, M->m.get<float>(), M->h1.get<float>(), M->h2.get<float>(), nullptr, s));
     HIPCHK(launch_mlp_backward(W, aux, M->m.get<float>(), M->h1.get<float>(), M->h2.get<float>(), n, M->g.get<float>(),
-                               M->d1.get<float>(), M->d2.get<float>(), M->lpart.get<float>(), loss, s));
+                               M->d1.get<float>(), M->d2.get<float>(), M->lpart.get<float>(), s));
     HIPCHK(launch_mlp_wgrad(x, M->h1.get<float>(), M->h2.get<float>(), M->d1.get<float>(), M->d2.get<float>(),
-                            M->g.get<float>(), n, grad, s));
+                            M->g.get<float>(), n, M->lpart.get<float>(), grad, loss, s));
     if (lr > 0.f) {
         ++M->step;
         HIPCHK(launch_mlp_adam(M->p, grad, M->m1, M->m2, lr, M->step, s));
