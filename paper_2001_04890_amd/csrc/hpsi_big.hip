@@ -301,21 +301,6 @@ __global__ __launch_bounds__(256) void k_big_y(const Item* __restrict__ items, c
     }
 }
 
-__global__ void k_reduce_big(const Reduce* __restrict__ red, const double* __restrict__ part, double* __restrict__ y,
-                             const int32_t* __restrict__ mask) {
-    const Reduce R = red[blockIdx.x];
-    if (mask && mask[R.part] != kPartActive) return;
-    const int n = R.tm * R.tn;
-    const int e = blockIdx.y * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    const int rr = e / R.tn, cc = e - (e / R.tn) * R.tn;
-    const int row = R.r0 + rr, col = R.c0 + cc;
-    if (row >= R.m_ap || col >= R.m_dp) return;
-    double s = 0.0;
-    for (int k = 0; k < R.n_parts; ++k) s += part[R.part_off + (int64_t)k * n + e];
-    y[R.y_off + (int64_t)row * R.m_dp + col] += s;
-}
-
 hipError_t launch_hpsi_big(const BigPlan& P, const uint16_t* pool_t, const uint16_t* xt, double* y, hipStream_t s,
                            const int32_t* active) {
     for (int c = 0; c < P.n_chunks; ++c) {
@@ -326,9 +311,9 @@ hipError_t launch_hpsi_big(const BigPlan& P, const uint16_t* pool_t, const uint1
         if (C.item_end > C.item_begin)
             hipLaunchKernelGGL(k_big_y, dim3(C.item_end - C.item_begin), dim3(256), 0, s, P.items + C.item_begin, P.t2,
                                pool_t, P.tbuf, y, P.partial, active);
-        if (C.red_end > C.red_begin)
-            hipLaunchKernelGGL(k_reduce_big, dim3(C.red_end - C.red_begin, P.red_chunks), dim3(256), 0, s,
-                               P.reduces + C.red_begin, P.partial, y, active);
+        const hipError_t e = launch_reduce_partials(P.reduces + C.red_begin, C.red_end - C.red_begin, P.red_chunks,
+                                                    P.partial, y, s, active);
+        if (e != hipSuccess) return e;
     }
     return hipGetLastError();
 }

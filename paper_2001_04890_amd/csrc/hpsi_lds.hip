@@ -586,10 +586,12 @@ __global__ __launch_bounds__(64) void k_hpsi_small(const Item* __restrict__ item
 }
 
 // y_tile += sum of its partial tiles, in item order; block (record, 256-element chunk), one element
-// per thread
+// per thread. Bound by the latency of its loads: 16 of them are in flight at a time (issued one after
+// another, a target of 100 partials waited 100 times).
 __global__ void k_reduce_lds(const Reduce* __restrict__ red, const double* __restrict__ partall,
                              double* __restrict__ yall, int64_t n_coeff, int64_t part_stride,
                              const int32_t* __restrict__ mask) {
+    constexpr int B = 16;
     const Reduce R = red[blockIdx.x];
     if (mask && mask[R.part] != kPartActive) return;
     const int n = R.tm * R.tn;
@@ -598,10 +600,19 @@ __global__ void k_reduce_lds(const Reduce* __restrict__ red, const double* __res
     const int rr = e / R.tn, cc = e - (e / R.tn) * R.tn;
     const int row = R.r0 + rr, col = R.c0 + cc;
     if (row >= R.m_ap || col >= R.m_dp) return;
-    const double* __restrict__ part = partall + (int64_t)blockIdx.y * part_stride + R.part_off;
+    const double* __restrict__ part = partall + (int64_t)blockIdx.y * part_stride + R.part_off + e;
+    double* const y = yall + (int64_t)blockIdx.y * n_coeff + R.y_off + (int64_t)row * R.m_dp + col;
+    const double y0 = *y;
     double s = 0.0;
-    for (int k = 0; k < R.n_parts; ++k) s += part[(int64_t)k * n + e];
-    yall[(int64_t)blockIdx.y * n_coeff + R.y_off + (int64_t)row * R.m_dp + col] += s;
+    for (int k = 0; k < R.n_parts; k += B) {
+        double v[B];
+#pragma unroll
+        for (int u = 0; u < B; ++u) v[u] = part[(int64_t)min(k + u, R.n_parts - 1) * n];
+#pragma unroll
+        for (int u = 0; u < B; ++u)
+            if (k + u < R.n_parts) s += v[u];
+    }
+    *y = y0 + s;
 }
 
 hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, const double* partial, double* y,

@@ -569,12 +569,67 @@ int multidot_parts(int64_t n) {
     return (int)(p < 1 ? 1 : p);
 }
 
+// v of the lane that DPP control CTRL selects
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+// v + v of lane ^ 32 (H = 32) or ^ 16
+template <int H>
+__device__ __forceinline__ double add_swapped(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t l = (uint32_t)b, h = (uint32_t)(b >> 32);
+    uint32_t lo[2], hi[2];
+    if constexpr (H == 32) {
+        const auto p = __builtin_amdgcn_permlane32_swap(l, l, false, false), q = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+        lo[0] = p[0], lo[1] = p[1], hi[0] = q[0], hi[1] = q[1];
+    } else {
+        const auto p = __builtin_amdgcn_permlane16_swap(l, l, false, false), q = __builtin_amdgcn_permlane16_swap(h, h, false, false);
+        lo[0] = p[0], lo[1] = p[1], hi[0] = q[0], hi[1] = q[1];
+    }
+    return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+// Sum over the wavefront, adding lanes 32, 16, 8, 4, 2 and 1 apart in turn. In registers: through LDS
+// (__shfl_xor) each of the six steps waits for a round trip.
 __device__ __forceinline__ double wave_sum(double v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v = add_swapped<32>(v);
+    v = add_swapped<16>(v);
+    v += dpp<0x128>(v);              // row_ror:8 = lane ^ 8
+    v += dpp<0x1B>(dpp<0x141>(v));   // row_half_mirror, then the quad reversed = lane ^ 7 ^ 3
+    v += dpp<0x4E>(v);               // quad_perm [2, 3, 0, 1] = lane ^ 2
+    v += dpp<0xB1>(v);               // quad_perm [1, 0, 3, 2] = lane ^ 1
     return v;
 }
 
-// partial[j * n_part + b] = sum over chunk b of V[j] . w
+// The NJ dot products of one chunk; the loads of all of the thread's elements are in flight at once.
+template <int NJ>
+__device__ __forceinline__ void chunk_dots(const double* __restrict__ V, int64_t n, const double* __restrict__ w, int64_t lo,
+                                           int64_t hi, double (*red)[kDotVecs]) {
+    constexpr int E = kDotChunk / 256;
+    double wi[E], v[NJ][E];
+#pragma unroll
+    for (int u = 0; u < E; ++u) {
+        const int64_t i = min(lo + threadIdx.x + 256 * u, hi - 1);
+        wi[u] = w[i];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) v[j][u] = V[(int64_t)j * n + i];
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        double acc = 0.0;
+#pragma unroll
+        for (int u = 0; u < E; ++u)
+            if (lo + threadIdx.x + 256 * u < hi) acc += v[j][u] * wi[u];
+        acc = wave_sum(acc);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = acc;
+    }
+}
+
+// partial[j * n_part + b] = sum over chunk b of V[j] . w. Bound by latency in an ordinary solve (a few
+// hundred short launches per solve).
 __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V, int nv, int64_t n,
                                                   const double* __restrict__ w, double* __restrict__ partial,
                                                   int n_part) {
@@ -583,19 +638,20 @@ __global__ __launch_bounds__(256) void k_multidot(const double* __restrict__ V, 
     const int64_t hi = lo + kDotChunk < n ? lo + kDotChunk : n;
     const int j0 = blockIdx.y * kDotVecs;
     const int nj = nv - j0 < kDotVecs ? nv - j0 : kDotVecs;
-    double acc[kDotVecs];
-#pragma unroll
-    for (int j = 0; j < kDotVecs; ++j) acc[j] = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x) {
-        const double wi = w[i];
-#pragma unroll
-        for (int j = 0; j < kDotVecs; ++j)
-            if (j < nj) acc[j] += V[(int64_t)(j0 + j) * n + i] * wi;
+    if (hi <= lo) {   // no elements
+        if ((int)threadIdx.x < nj) partial[(int64_t)(j0 + threadIdx.x) * n_part + blockIdx.x] = 0.0;
+        return;
     }
-#pragma unroll
-    for (int j = 0; j < kDotVecs; ++j) {
-        const double v = wave_sum(acc[j]);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][j] = v;
+    const double* Vj = V + (int64_t)j0 * n;
+    switch (nj) {
+        case 1: chunk_dots<1>(Vj, n, w, lo, hi, red); break;
+        case 2: chunk_dots<2>(Vj, n, w, lo, hi, red); break;
+        case 3: chunk_dots<3>(Vj, n, w, lo, hi, red); break;
+        case 4: chunk_dots<4>(Vj, n, w, lo, hi, red); break;
+        case 5: chunk_dots<5>(Vj, n, w, lo, hi, red); break;
+        case 6: chunk_dots<6>(Vj, n, w, lo, hi, red); break;
+        case 7: chunk_dots<7>(Vj, n, w, lo, hi, red); break;
+        default: chunk_dots<8>(Vj, n, w, lo, hi, red); break;
     }
     __syncthreads();
     if ((int)threadIdx.x < nj)
