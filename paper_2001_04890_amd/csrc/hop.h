@@ -185,10 +185,9 @@ struct dmrg_hop {
                                                 // with sources that fit them; 0: any larger source sends
                                                 // the whole target to the two-pass path
     // FP64 two-pass path (hpsi_big64.hip) for the same large targets
-    int tune_big64 = 1;                         // FP64 two-pass path: 0 off, 1 where cheaper, 2 every target above 96
-    double* d_op64 = nullptr;                   // FP64 operand pool + zeros + identity blocks (made on first use)
+    int tune_big64 = 1;                         // FP64 two-pass path for them: 0 off, 1 or 2 on
+    double* d_op64 = nullptr;                   // FP64 operand pool + identity blocks (made on first use)
     int64_t op64_len = 0;
-    int64_t zeros64_off = 0;                    // 1 KB of zeros in it
     std::vector<int64_t> ident64_off;           // identity block by 4-row groups, or -1
     std::vector<int64_t> xt64_off;              // X^T of every psi block in xt64
     const dmrg::PackBlock* packs64 = nullptr;   // its packing (plan allocation)

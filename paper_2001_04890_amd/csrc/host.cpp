@@ -1220,7 +1220,7 @@ extern "C" dmrg_status dmrg_hop_autotune(dmrg_hop* H, int32_t precision, int32_t
             knobs.push_back({&one, {}});          // (the copy wavefront of the LDS-staged kernel it replaced)
             knobs.push_back({&H->tune_lds64_small, lds64 ? std::vector<int>{1, 0} : std::vector<int>{}});
             knobs.push_back({&one, {}});          // (that kernel's register cap)
-            knobs.push_back({&H->tune_big64, {1, 2}});
+            knobs.push_back({&H->tune_big64, {1}});
             knobs.push_back({&H->tune_max_tq, {2, 4, 8}});
             knobs.push_back({&H->tune_items, {8192, 32768, 65536}});
             knobs.push_back({&H->tune_order, {0, 2}});

@@ -254,9 +254,6 @@ hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, cons
 // targets: pass 1 writes T = f A X of every task into a tiled hi/lo buffer (tile (rt, jc) of the
 // task's T at t_off + (rt * pd32 + jc) * kTileU16, in the A-operand fragment layout of pass 2),
 // pass 2 accumulates Y += sum_tasks T B^T per 128 x 128 output tile.
-// FP64 form (hpsi_big64.hip): offsets in doubles, A, B and X^T in the FP64 operand form, T in whole
-// 16 x 16 tiles of it; pa32 / pd32 / rb / jb counted in 16-wide tiles, ka / kd in 4-wide k steps, nrt in
-// 4-row groups.
 struct BigT1 {             // pass-1 group: one task, rows [16 rb, 16 rb + 128), T^T rows [32 jb, 32 jb + 128)
     int64_t xt, a, t;      // tiled X^T of the source, tiled A, output T (u16 offsets)
     double f;
@@ -264,19 +261,36 @@ struct BigT1 {             // pass-1 group: one task, rows [16 rb, 16 rb + 128),
     int16_t nrt;           // row tiles of the target block
     int16_t rb, jb;        // first row tile, first 32-column chunk
     int16_t part;          // merged problem of the target (masks use part < 32768)
-    int16_t ka, kd;        // source rows / cols holding data, in k tiles (FP64 form: the k loop of
-                           // pass 1 and the T tiles it writes stop there)
+    int16_t ka, kd;        // source rows / cols holding data, in k tiles
 };
+// FP64 form (hpsi_big64.hip): offsets in doubles, A, B and X^T in the FP64 operand form, T in whole 16 x 16
+// tiles of it (tile (rt, jt) at t + (rt * pd + jt) * 256). One wavefront's part of a task's T; ka4 = 0: none.
+struct Big64T {
+    int64_t xt, a, t;
+    double f;
+    int32_t ka4, kd4, ra4; // source rows / columns and target rows in 4-wide groups
+    int32_t pd;            // T tiles along the source columns
+    int16_t rb, nr, jb, nj;   // row tiles [rb, rb + nr) and T column tiles [jb, jb + nj), at most 4 each
+    int32_t part;          // merged problem of the target
+    int32_t pad;
+};
+// n tiles are cut into ceil(n / 4) parts, the longer ones first: length of the one that starts at tile t
+constexpr int big64_len(int n, int t) {
+    const int parts = (n + 3) / 4, len = n / parts, more = n % parts;
+    return t < more * (len + 1) ? len + 1 : len;
+}
 struct BigT2 {             // pass-2 task: T of the task and its B block
     int64_t t, b;
     int32_t pd32;
-    int32_t kd;            // T tiles holding data along k (FP64 form: the k loop of pass 2 stops there)
+    int32_t kd;            // T tiles holding data along k (FP64 form: 4-wide k steps holding data)
 };
 // Chunk c: pass-1 workgroups [t1_begin, t1_end) (workgroup w runs groups t1_ranges[w] ..
 // t1_ranges[w + 1] - 1), pass-2 items [item_begin, item_end), reductions [red_begin, red_end).
 struct BigChunk { int t1_begin, t1_end, item_begin, item_end, red_begin, red_end; };
-struct BigPlan {                    // split or FP64 form (see BigT1)
-    const BigT1* t1 = nullptr;      // device
+// FP64 form: pass-1 work [t1_begin, t1_end) of w1, one wavefront each.
+struct BigPlan {                    // split or FP64 form
+    const BigT1* t1 = nullptr;      // device, split form
+    const Big64T* w1 = nullptr;     // device, FP64 form
     const int32_t* t1_ranges = nullptr;   // device, one entry per pass-1 workgroup plus one
     const BigT2* t2 = nullptr;      // device
     const Item* items = nullptr;    // device: pass-2 items (r0 = 16 rb, c0 = 16 qb, task range in t2)
@@ -287,7 +301,6 @@ struct BigPlan {                    // split or FP64 form (see BigT1)
     uint16_t* tbuf = nullptr;       // device, largest chunk's T (one vector at a time; doubles in the FP64 form)
     double* partial = nullptr;      // device, partial tiles of the largest chunk
     int64_t partial_size = 0;
-    int64_t zeros = 0;              // FP64 form: offset of 1 KB of zeros in the operand pool
 };
 
 // Launchers (kernels.hip). All asynchronous on `s`.

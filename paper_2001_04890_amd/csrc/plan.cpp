@@ -607,42 +607,61 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
     HIPCHK(hipStreamSynchronize(s));
 }
 
-// Launch plan of the two-pass large-block path for the targets flagged in `big`, split (hpsi_big.hip,
-// fp64 = false: 16 x 32 hi/lo tiles, u16 offsets) or FP64 (hpsi_big64.hip: 16 x 16 tiles, offsets
-// in doubles). Targets are grouped into chunks whose T buffers (one per task: target rows x source
+// Work dealt to the 8 XCDs (workgroups go to them in turn, so entries at positions of one residue modulo 8
+// share an L2): the entries of a unit stay on one XCD, the least loaded when the unit opens.
+template <class T>
+struct XcdDeal {
+    T none;                      // filler of the shorter lists
+    std::vector<T> list[8];
+    double load[8] = {0.0};
+    int x = 0;
+    void open(double cost) {
+        x = (int)(std::min_element(load, load + 8) - load);
+        load[x] += cost;
+    }
+    void add(const T& v) { list[x].push_back(v); }
+    void take(std::vector<T>& out) {
+        size_t n = 0;
+        for (const auto& l : list) n = std::max(n, l.size());
+        for (size_t i = 0; i < n; ++i)
+            for (const auto& l : list) out.push_back(i < l.size() ? l[i] : none);
+        for (auto& l : list) l.clear();
+        std::fill(load, load + 8, 0.0);
+    }
+};
+
+// f(first tile, tiles) of the parts that n tiles are cut into
+template <class F>
+void for_parts(int n, F&& f) {
+    for (int t = 0; t < n; t += dmrg::big64_len(n, t)) f(t, dmrg::big64_len(n, t));
+}
+
+// Launch plan of the split two-pass large-block path (hpsi_big.hip: 16 x 32 hi/lo tiles, u16 offsets) for
+// the targets flagged in `big`. Targets are grouped into chunks whose T buffers (one per task: target rows x source
 // columns, tiled) stay below the T budget; per chunk, pass 1 has one group per (task, 8 row tiles,
 // 128 T columns), consecutive groups packed into workgroups of about tune_big_stages1 k steps, and
 // pass 2 one item per (target, 8 row tiles, 8 column tiles, task range), the task lists cut into
 // items of about tune_big_stages k steps whose partial tiles a reduction adds in order.
-void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bool fp64,
-                    const std::vector<char>* task_keep = nullptr) {
+void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big,
+                    const std::vector<char>* task_keep) {
     auto kept = [&](size_t k) { return !task_keep || (*task_keep)[k]; };
-    const int unit = fp64 ? 16 : 32;                 // k-tile width
-    const int64_t esc = fp64 ? 1 : 2;                // tiled-array elements per pool element
-    const int64_t tile_el = fp64 ? 256 : dmrg::kTileU16;
-    const int64_t kBigTBudget = (int64_t)H.tune_big_tbudget_mb << (fp64 ? 18 : 19);   // T elements per chunk
-    dmrg::BigPlan& plan = fp64 ? H.bplan64 : H.bplan;
-    std::vector<dmrg::BigChunk>& chunks = fp64 ? H.big_chunks64 : H.big_chunks;
+    const int unit = 32;                             // k-tile width
+    const int64_t tile_el = dmrg::kTileU16;
+    const int64_t kBigTBudget = (int64_t)H.tune_big_tbudget_mb << 19;   // T elements per chunk
+    dmrg::BigPlan& plan = H.bplan;
+    std::vector<dmrg::BigChunk>& chunks = H.big_chunks;
     plan = dmrg::BigPlan{};
     chunks.clear();
     const size_t nb = H.blk.size();
-    std::vector<int64_t> pk_off = H.xt64_off;
-    if (!fp64) {
-        pk_off.resize(nb);
-        int64_t ps = 0;
-        for (size_t i = 0; i < nb; ++i) { pk_off[i] = ps; ps += (int64_t)dmrg::ld_of(H.blk_ma[i]) * dmrg::ld_of(H.blk_md[i]); }
-    }
-    // T tiles along a task's source columns (tile stride; the split form keeps its padding to 32)
-    auto t_cols = [&](int i) { return fp64 ? (H.blk_md[i] + 15) / 16 : dmrg::ld_of(H.blk_md[i]) / unit; };
-    if (fp64) plan.zeros = H.zeros64_off;
+    std::vector<int64_t> pk_off(nb);
+    int64_t ps = 0;
+    for (size_t i = 0; i < nb; ++i) { pk_off[i] = ps; ps += (int64_t)dmrg::ld_of(H.blk_ma[i]) * dmrg::ld_of(H.blk_md[i]); }
     // operand offsets of a task (identity factors: identity blocks)
     auto left_of = [&](const dmrg_hop::HTask& t) {
-        if (fp64) return op64_of(H, t.lm, H.blk[t.i][0], H.blk_ma[t.i]);
         const int k = dmrg::ld_of(H.blk_ma[t.i]) / 32 - 1;
         return t.lm >= 0 ? 2 * H.mats[t.lm].pool_of_in[H.blk[t.i][0]] : k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
     };
     auto right_of = [&](const dmrg_hop::HTask& t) {
-        if (fp64) return op64_of(H, t.rm, H.blk[t.i][3], H.blk_md[t.i]);
         const int k = dmrg::ld_of(H.blk_md[t.i]) / 32 - 1;
         return t.rm >= 0 ? 2 * H.mats[t.rm].pool_of_in[H.blk[t.i][3]] : k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
     };
@@ -731,7 +750,7 @@ void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bo
         const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16;
         int64_t need = 0;
         for (size_t k = trange[j].first; k < trange[j].second; ++k)
-            if (kept(k)) need += (int64_t)nrt * t_cols(H.tasks[k].i) * tile_el;
+            if (kept(k)) need += (int64_t)nrt * dmrg::ld_of(H.blk_md[H.tasks[k].i]) / unit * tile_el;
         if (need == 0) continue;                  // every task of the target runs elsewhere
         if (tsize > 0 && tsize + need > kBigTBudget) close_chunk();
         const int32_t b0 = (int32_t)t2.size();
@@ -743,18 +762,15 @@ void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bo
             const int64_t a_off = left_of(ht), b_off = right_of(ht);
             if (a_off < 0 || b_off < 0) throw Error(DMRG_ERR_ARG, "internal: no tiled operand block");
             const int64_t t_off = tsize;
-            const int pd = t_cols(ht.i);
+            const int pd = dmrg::ld_of(H.blk_md[ht.i]) / unit;
             tsize += (int64_t)nrt * pd * tile_el;
             const int ka = (H.blk_ma[ht.i] + unit - 1) / unit, kd = (H.blk_md[ht.i] + unit - 1) / unit;
-            // FP64 form: k loops in 16-wide tiles that hold data, ka / kd in k steps, nrt in row groups
-            const int pa = fp64 ? ka : dmrg::ld_of(H.blk_ma[ht.i]) / unit;
-            const int ks = fp64 ? dmrg::k4_of(H.blk_ma[ht.i]) : ka, ds = fp64 ? dmrg::k4_of(H.blk_md[ht.i]) : kd;
-            const int rows = fp64 ? dmrg::k4_of(H.blk_ma[j]) : nrt;
+            const int pa = dmrg::ld_of(H.blk_ma[ht.i]) / unit;
             for (int rb = 0; rb < nrt; rb += 8)
                 for (int jb = 0; jb < kd; jb += 128 / unit)
-                    t1.push_back({esc * pk_off[ht.i], a_off, t_off, ht.f, (int16_t)pa, (int16_t)pd, (int16_t)rows, (int16_t)rb,
-                                  (int16_t)jb, 0, (int16_t)ks, (int16_t)ds});
-            t2.push_back({t_off, b_off, pd, ds});
+                    t1.push_back({2 * pk_off[ht.i], a_off, t_off, ht.f, (int16_t)pa, (int16_t)pd, (int16_t)nrt, (int16_t)rb,
+                                  (int16_t)jb, 0, (int16_t)ka, (int16_t)kd});
+            t2.push_back({t_off, b_off, pd, kd});
         }
         H.big_t2_range[j] = {b0, (int32_t)t2.size()};
         for (size_t g = g_t1; g < t1.size(); ++g) t1[g].part = (int16_t)part_j;
@@ -782,14 +798,14 @@ void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bo
     plan.chunks = chunks.data();
     plan.n_chunks = (int)chunks.size();
     plan.red_chunks = (red_max + 255) / 256;
-    const size_t tbytes = (size_t)std::max<int64_t>(tbuf_max, 1) * (fp64 ? sizeof(double) : sizeof(uint16_t));
+    const size_t tbytes = (size_t)std::max<int64_t>(tbuf_max, 1) * sizeof(uint16_t);
     plan.tbuf = plan_alloc<uint16_t>(H, tbytes / sizeof(uint16_t));
     plan.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part_max, 1));
     plan.partial_size = part_max;
     if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
         if (e[0] == '1')
-            std::fprintf(stderr, "[dmrg big plan%s] chunks %zu pass-1 groups %zu pass-2 items %zu reduces %zu T %.1f MB "
-                         "partial %.1f MB\n", fp64 ? " fp64" : "", chunks.size(), t1.size(), items.size(), reds.size(),
+            std::fprintf(stderr, "[dmrg big plan] chunks %zu pass-1 groups %zu pass-2 items %zu reduces %zu T %.1f MB "
+                         "partial %.1f MB\n", chunks.size(), t1.size(), items.size(), reds.size(),
                          tbytes * 1e-6, part_max * 8e-6);
     HIPCHK(hipStreamSynchronize(s));
 }
@@ -817,38 +833,146 @@ std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
     return big;
 }
 
-// Targets of the FP64 H.psi that take the two-pass path. The one-wavefront kernel has no size limit,
-// so this is a cost choice: per target, the MFMA work each path executes (padded to its tiles; the
-// one-wavefront kernel recomputes A.X for every 128-column output tile) divided by the fraction of
-// the FP64 MFMA rate it sustains (measured: two-pass ~0.65 of peak on its padded work, one-wavefront
-// ~0.3). mode 2: every target above the 96-wide LDS stages (as the split path).
-// Tasks already taken by the register-streamed kernel (lds_task) are left out of the comparison.
-std::vector<char> fp64_big_targets(const dmrg_hop& H, int mode, const std::vector<char>* lds_task) {
-    // with the register-streamed kernel on, targets within its 128 x 128 are its own
-    std::vector<char> big = large_targets(H, H.tune_lds64 ? 16 * dmrg::kRsMaxTiles : 96);
-    if (mode == 2) return big;
-    auto up = [](double m, double q) { return std::ceil(m / q) * q; };
-    std::vector<double> c_big(H.blk.size(), 0.0), c_one(H.blk.size(), 0.0);
-    for (size_t k = 0; k < H.tasks.size(); ++k) {
-        const auto& t = H.tasks[k];
-        if (!big[t.j] || (lds_task && !lds_task->empty() && (*lds_task)[k])) continue;
-        const double ma = H.blk_ma[t.i], md = H.blk_md[t.i], mj = H.blk_ma[t.j], nj = H.blk_md[t.j];
-        const double r16 = up(mj, 16), nrt = r16 / 16, nq = up(nj, 16) / 16;
-        const double ka = up(ma, 16), kd = up(md, 16);
-        // two-pass: pass 1 (8 x 8 tiles of 16 per group, k over the source rows holding data), pass 2
-        // (the output tiles inside the target, k over the T tiles holding data)
-        c_big[t.j] += (2.0 * up(nrt, 8) * 16 * up(kd / 16, 8) * 16 * ka + 2.0 * r16 * up(nj, 16) * kd) / 0.65;
-        // one wavefront per 32 x 128 tile: A.X per column tile, then (A.X).B^T
-        const double ncol = std::ceil(nj / 128.0);
-        c_one[t.j] += (2.0 * up(mj, 32) * up(ma, 16) * up(md, 16) * ncol + 2.0 * up(mj, 32) * up(md, 16) * up(nj, 16)) / 0.3;
+// Launch plan of the FP64 two-pass path (hpsi_big64.hip) for the targets flagged in `big`, without the tasks
+// that run elsewhere. Targets are grouped into chunks whose T buffers (one per task: target rows x source
+// columns, in 16 x 16 tiles) stay below the T budget. A wavefront owns up to 4 x 4 tiles: both extents are
+// cut into equal parts of at most four tiles, so that the parts of one block differ by a tile at most. Per
+// chunk, pass 1 has one piece of work per task and part of its T; pass 2 one item per part of a target and
+// task range, the task lists cut into ranges of about tune_big_stages T tiles whose partial sums a reduction
+// adds in order. The pieces of one task, and those of one range of a target, read the same operands: they
+// are dealt together to one XCD, the least loaded so far.
+void build_big64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, const std::vector<char>& task_keep) {
+    dmrg::BigPlan& plan = H.bplan64;
+    std::vector<dmrg::BigChunk>& chunks = H.big_chunks64;
+    plan = dmrg::BigPlan{};
+    chunks.clear();
+    const int64_t t_budget = (int64_t)H.tune_big_tbudget_mb << 18;   // T doubles per chunk (twice the split form's bytes)
+    std::vector<dmrg::Big64T> t1;
+    std::vector<dmrg::BigT2> t2;
+    std::vector<dmrg::Item> items;
+    std::vector<dmrg::Reduce> reds;
+    XcdDeal<dmrg::Big64T> deal1{dmrg::Big64T{}};
+    dmrg::Item none{};
+    none.part_off = -1;
+    XcdDeal<dmrg::Item> deal2{none};
+    int64_t part_max = 0, tbuf_max = 0, tsize = 0, part = 0;
+    int red_max = 1;
+    size_t pieces = 0, ranges = 0;
+    dmrg::BigChunk cur{0, 0, 0, 0, 0, 0};
+    bool open = false;
+    auto close_chunk = [&]() {
+        if (!open) return;
+        cur.t1_begin = (int)t1.size();
+        deal1.take(t1);
+        cur.t1_end = (int)t1.size();
+        cur.item_begin = (int)items.size();
+        deal2.take(items);
+        cur.item_end = (int)items.size();
+        cur.red_end = (int)reds.size();
+        chunks.push_back(cur);
+        cur = dmrg::BigChunk{0, 0, 0, 0, (int)reds.size(), 0};
+        part_max = std::max(part_max, part);
+        tbuf_max = std::max(tbuf_max, tsize);
+        tsize = part = 0;
+        open = false;
+    };
+    size_t k = 0;
+    for (size_t j = 0; j < H.blk.size(); ++j) {
+        const size_t kb = k;
+        while (k < H.tasks.size() && H.tasks[k].j == (int)j) ++k;
+        if (!big[j]) continue;
+        const int ma = H.blk_ma[j], md = H.blk_md[j], nrt = (ma + 15) / 16, nq = (md + 15) / 16;
+        auto t_tiles = [&](const dmrg_hop::HTask& t) { return (int64_t)nrt * ((H.blk_md[t.i] + 15) / 16); };
+        int64_t need = 0;
+        for (size_t t = kb; t < k; ++t)
+            if (task_keep[t]) need += t_tiles(H.tasks[t]) * 256;
+        if (need == 0) continue;                  // every task of the target runs elsewhere
+        if (tsize > 0 && tsize + need > t_budget) close_chunk();
+        open = true;
+        const int32_t part_j = H.n_parts > 1 ? part_of(H, H.blk_off[j]) : 0;
+        std::vector<std::pair<int32_t, int32_t>> cuts;   // ranges of t2
+        std::vector<double> cost;
+        int32_t b0 = (int32_t)t2.size();
+        int c = 0;
+        for (size_t t = kb; t < k; ++t) {
+            if (!task_keep[t]) continue;
+            const auto& ht = H.tasks[t];
+            const int sa = H.blk_ma[ht.i], sd = H.blk_md[ht.i], pd = (sd + 15) / 16;
+            const int64_t a = op64_of(H, ht.lm, H.blk[ht.i][0], sa), b = op64_of(H, ht.rm, H.blk[ht.i][3], sd);
+            if (a < 0 || b < 0) throw Error(DMRG_ERR_ARG, "internal: no operand block");
+            deal1.open((double)nrt * pd * dmrg::k4_of(sa));
+            for_parts(nrt, [&](int rb, int nr) {
+                for_parts(pd, [&](int jb, int nj) {
+                    deal1.add({H.xt64_off[ht.i], a, tsize, ht.f, dmrg::k4_of(sa), dmrg::k4_of(sd), dmrg::k4_of(ma), pd,
+                               (int16_t)rb, (int16_t)nr, (int16_t)jb, (int16_t)nj, part_j, 0});
+                    ++pieces;
+                });
+            });
+            if (c >= H.tune_big_stages) {
+                cuts.push_back({b0, (int32_t)t2.size()});
+                b0 = (int32_t)t2.size();
+                c = 0;
+            }
+            if (c == 0) cost.push_back(0.0);
+            c += pd;
+            cost.back() += (double)nrt * nq * dmrg::k4_of(sd);
+            t2.push_back({tsize, b, pd, dmrg::k4_of(sd)});
+            tsize += t_tiles(ht) * 256;
+        }
+        cuts.push_back({b0, (int32_t)t2.size()});
+        const int64_t part0 = part;
+        for (size_t q = 0; q < cuts.size(); ++q) {
+            deal2.open(cost[q]);
+            int64_t at = part0;                  // the records' partial tiles of this target, n_parts each
+            for_parts(nrt, [&](int rb, int nr) {
+                for_parts(nq, [&](int qb, int nqw) {
+                    const int tm = 16 * nr, tn = 16 * nqw;
+                    dmrg::Item it{H.blk_off[j], -1, ma, md, 16 * rb, 16 * qb, cuts[q].first, cuts[q].second};
+                    if (cuts.size() > 1) {
+                        it.part_off = at + (int64_t)q * tm * tn;
+                        if (q == 0) {
+                            reds.push_back({H.blk_off[j], at, ma, md, 16 * rb, 16 * qb, tm, tn, (int32_t)cuts.size(), 0});
+                            red_max = std::max(red_max, tm * tn);
+                        }
+                        at += (int64_t)cuts.size() * tm * tn;
+                    }
+                    deal2.add(it);
+                    ++ranges;
+                });
+            });
+            part = std::max(part, at);
+        }
     }
-    for (size_t j = 0; j < big.size(); ++j) big[j] = big[j] && c_big[j] < c_one[j];
-    return big;
+    close_chunk();
+    if (t2.empty()) return;
+    tag_parts(H, items);
+    tag_parts(H, reds);
+    auto upload = [&](const auto& v) {
+        using T = typename std::decay_t<decltype(v)>::value_type;
+        T* d = plan_alloc<T>(H, std::max<size_t>(v.size(), 1));
+        if (!v.empty()) HIPCHK(hipMemcpyAsync(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
+        return d;
+    };
+    plan.w1 = upload(t1);
+    plan.t2 = upload(t2);
+    plan.items = upload(items);
+    plan.reduces = upload(reds);
+    plan.chunks = chunks.data();
+    plan.n_chunks = (int)chunks.size();
+    plan.red_chunks = (red_max + 255) / 256;
+    plan.tbuf = reinterpret_cast<uint16_t*>(plan_alloc<double>(H, (size_t)std::max<int64_t>(tbuf_max, 1)));
+    plan.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part_max, 1));
+    plan.partial_size = part_max;
+    if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
+        if (e[0] == '1')
+            std::fprintf(stderr, "[dmrg big plan fp64] chunks %zu pass-1 groups %zu pass-2 items %zu reduces %zu T %.1f MB "
+                         "partial %.1f MB\n", chunks.size(), pieces, ranges, reds.size(), tbuf_max * 8e-6, part_max * 8e-6);
+    HIPCHK(hipStreamSynchronize(s));
 }
 
 // Operand pool of the FP64 MFMA kernels: every pool block in the operand form of internal.h (offsets per
 // matrix and ket sector in MatDef::op64_of_in), identity blocks of the psi blocks' sizes (by 4-row
-// groups), which stand in for identity factors, and 1 KB of zeros. Made once. Also the places of the
+// groups), which stand in for identity factors. Made once. Also the places of the
 // packed X^T of every psi block.
 void make_op64(dmrg_hop& H, hipStream_t s) {
     if (H.d_op64) return;
@@ -873,8 +997,7 @@ void make_op64(dmrg_hop& H, hipStream_t s) {
     int widest = 0;
     for (size_t i = 0; i < H.blk.size(); ++i) widest = std::max({widest, dmrg::k4_of(H.blk_ma[i]), dmrg::k4_of(H.blk_md[i])});
     H.ident64_off.assign(widest + 1, -1);
-    std::vector<double> tail(128, 0.0);          // zeros, then the identity blocks
-    H.zeros64_off = n;
+    std::vector<double> tail;                    // the identity blocks
     auto add_ident = [&](int m) {
         const int r4 = dmrg::k4_of(m);
         if (H.ident64_off[r4] >= 0) return;
@@ -894,7 +1017,8 @@ void make_op64(dmrg_hop& H, hipStream_t s) {
     H.d_op64 = dev_alloc<double>(H, H.op64_len);
     dmrg::OpBlock64* d_ob = dev_alloc<dmrg::OpBlock64>(H, ob.size());
     HIPCHK(hipMemcpyAsync(d_ob, ob.data(), ob.size() * sizeof(ob[0]), hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(H.d_op64 + n, tail.data(), tail.size() * sizeof(double), hipMemcpyHostToDevice, s));
+    if (!tail.empty())
+        HIPCHK(hipMemcpyAsync(H.d_op64 + n, tail.data(), tail.size() * sizeof(double), hipMemcpyHostToDevice, s));
     HIPCHK(dmrg::launch_op64(H.d_pool, d_ob, (int)ob.size(), H.d_op64, s));
     HIPCHK(hipStreamSynchronize(s));   // the staging vectors go out of scope
 }
@@ -1073,8 +1197,8 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
     for (void* p : H.plan_allocations) (void)hipFree(p);
     H.plan_allocations.clear();
     H.plan_bytes = 0;
-    // FP64: targets and sources within 128 x 128 take the register-streamed kernel; larger ones the
-    // two-pass path where it is cheaper, the one-wave kernel otherwise
+    // FP64: targets and sources within 128 x 128 take the register-streamed kernel, larger ones the two-pass
+    // path; what is switched off, and single-tile sources on request, the one-wave kernel
     H.bplan64 = dmrg::BigPlan{};
     H.big_chunks64.clear();
     H.rplan64 = dmrg::RsPlan64{};
@@ -1097,7 +1221,10 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
         for (char b : rs64) any_rs |= b != 0;
     }
     if (H.tune_big64) {
-        big64 = fp64_big_targets(H, H.tune_big64, &rs64);
+        // Every target above the limit: with tiles cut to the block no extent is too small for the two-pass
+        // path. 76 orbitals at bond dimension 6000 (one share): 25.3 ms; 30.4 ms when the few percent of the
+        // work in targets within 128 x 128 with a larger source ran on the one-wavefront kernel.
+        big64 = large_targets(H, H.tune_lds64 ? 16 * dmrg::kRsMaxTiles : 96);
         for (char b : big64) any_big |= b != 0;
     }
     if (any_big || any_rs) {
@@ -1105,7 +1232,7 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
         for (size_t j = 0; j < nb; ++j) rest[j] = !big64[j];
         for (size_t t = 0; t < rs64.size(); ++t) rest_tasks[t] = !rs64[t];
         build_plan_core(H, s, &rest, false, H.plan, H.launches, H.phases, &rest_tasks);
-        if (any_big) build_big_plan(H, s, big64, true, &rest_tasks);
+        if (any_big) build_big64_plan(H, s, big64, rest_tasks);
     } else {
         build_plan_core(H, s, nullptr, false, H.plan, H.launches, H.phases);
     }
@@ -1119,7 +1246,7 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
     H.bplan = dmrg::BigPlan{};
     if (H.n_fallback_targets > 0) {
         if (H.tune_big) {
-            build_big_plan(H, s, fb, false, &fb_task);
+            build_big_plan(H, s, fb, &fb_task);
             H.n_fallback_targets = 0;
         } else {
             if (!H.d_hi) throw Error(DMRG_ERR_ARG, "internal: row-major split operators missing");
