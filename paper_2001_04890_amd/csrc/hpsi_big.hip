@@ -31,12 +31,24 @@ constexpr int kStageTiles = 16;
 constexpr int kStageU16 = kStageTiles * kTileU16;
 constexpr int kFlushBig = 8;
 
-__device__ __forceinline__ unsigned short bf16_rne(float f) {
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (unsigned short)(u >> 16);
+// hi and lo parts of eight values (v_cvt_pk_bf16_f32 rounds two at a time to nearest even; rounding in integer
+// arithmetic took as long as the MFMAs around it)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
-__device__ __forceinline__ float bf16_f32(unsigned short h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
+__device__ __forceinline__ void split8(const float (&v)[8], u16x8& hi, u16x8& lo) {
+    u32x4 h, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h[i] = pack2(v[2 * i], v[2 * i + 1]);
+        l[i] = pack2(v[2 * i] - __builtin_bit_cast(float, h[i] << 16), v[2 * i + 1] - __builtin_bit_cast(float, h[i] & 0xffff0000u));
+    }
+    hi = __builtin_bit_cast(u16x8, h);
+    lo = __builtin_bit_cast(u16x8, l);
+}
 __device__ __forceinline__ bf16x8 as_bf(u16x8 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ f32x4 mma3(u16x8 ah, u16x8 al, u16x8 bh, u16x8 bl, f32x4 c) {
     c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(ah), as_bf(bh), c, 0, 0, 0);
@@ -117,13 +129,10 @@ __global__ __launch_bounds__(256) void k_big_t(const BigT1* __restrict__ work, c
                 if (jc < d.pd32 && rt < d.nrt) {
                     // acc[jj][h2][rr][v] = T'[row 16 rt + li][col 32 jc + 8 g + 4 h2 + v]
                     u16x8 th, tl;
+                    float v[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const float v = d.f * acc[jj][u >> 2][rr][u & 3];
-                        const unsigned short hh = bf16_rne(v);
-                        th[u] = hh;
-                        tl[u] = bf16_rne(v - bf16_f32(hh));
-                    }
+                    for (int u = 0; u < 8; ++u) v[u] = d.f * acc[jj][u >> 2][rr][u & 3];
+                    split8(v, th, tl);
                     uint16_t* dst = tbuf + d.t + (int64_t)(rt * d.pd32 + jc) * kTileU16 + ln * 8;
                     *reinterpret_cast<u16x8*>(dst) = th;
                     *reinterpret_cast<u16x8*>(dst + 512) = tl;

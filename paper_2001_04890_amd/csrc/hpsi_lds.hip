@@ -40,6 +40,24 @@ __device__ __forceinline__ unsigned short bf16_rne(float f) {
     return (unsigned short)(u >> 16);
 }
 __device__ __forceinline__ float bf16_f32(unsigned short h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
+// hi and lo parts of eight values (v_cvt_pk_bf16_f32 rounds two at a time to nearest even; rounding in integer
+// arithmetic took as long as the MFMAs around it)
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+__device__ __forceinline__ void split8(const float (&v)[8], u16x8& hi, u16x8& lo) {
+    u32x4 h, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        h[i] = pack2(v[2 * i], v[2 * i + 1]);
+        l[i] = pack2(v[2 * i] - __builtin_bit_cast(float, h[i] << 16), v[2 * i + 1] - __builtin_bit_cast(float, h[i] & 0xffff0000u));
+    }
+    hi = __builtin_bit_cast(u16x8, h);
+    lo = __builtin_bit_cast(u16x8, l);
+}
 
 __device__ __forceinline__ bf16x8 as_bf(u16x8 v) { return __builtin_bit_cast(bf16x8, v); }
 __device__ __forceinline__ f32x4 mma3(u16x8 ah, u16x8 al, u16x8 bh, u16x8 bl, f32x4 c) {
@@ -372,14 +390,12 @@ __global__ __launch_bounds__(NW * 64 + PF * 64 + CW * 64) void k_hpsi_lds(const 
                 // tt[h2][p][v] = T'[row 16 (rt0 + p) + li][col 32 jc + 8 g + 4 h2 + v] (unscaled)
                 u16x8 th[TP], tlo[TP];
 #pragma unroll
-                for (int p = 0; p < TP; ++p)
+                for (int p = 0; p < TP; ++p) {
+                    float v[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const float v = f * tt[u >> 2][p][u & 3];
-                        const unsigned short hh = bf16_rne(v);
-                        th[p][u] = hh;
-                        tlo[p][u] = bf16_rne(v - bf16_f32(hh));
-                    }
+                    for (int u = 0; u < 8; ++u) v[u] = f * tt[u >> 2][p][u & 3];
+                    split8(v, th[p], tlo[p]);
+                }
 #pragma unroll
                 for (int q = 0; q < QS; ++q) {
                     if (q < tq) {
@@ -552,14 +568,12 @@ __global__ __launch_bounds__(64) void k_hpsi_small(const Item* __restrict__ item
         u16x8 th[NR], tlo[NR];
         const float f = T.f;
 #pragma unroll
-        for (int p = 0; p < NR; ++p)
+        for (int p = 0; p < NR; ++p) {
+            float v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float v = f * tt[u >> 2][p][u & 3];
-                const unsigned short hh = bf16_rne(v);
-                th[p][u] = hh;
-                tlo[p][u] = bf16_rne(v - bf16_f32(hh));
-            }
+            for (int u = 0; u < 8; ++u) v[u] = f * tt[u >> 2][p][u & 3];
+            split8(v, th[p], tlo[p]);
+        }
         // GEMM2: Y += T' B^T
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
