@@ -144,8 +144,8 @@ struct dmrg_hop {
     dmrg::HpsiPlan plan{};
     std::vector<dmrg::HpsiLaunch> launches;
     std::vector<dmrg::HpsiPhase> phases;
-    // split path: LDS-staged kernel over tiled operands, plus the one-wave kernel (row-major hi/lo
-    // operands, plan_fb) for targets whose blocks exceed the LDS stage size
+    // split path: row-mode and task-mode kernels over tiled operands, plus the one-wave kernel (row-major
+    // hi/lo operands, plan_fb) for targets whose blocks exceed 96
     std::vector<dmrg::PoolBlock> pool_blocks;   // every block of the FP64 pool (for the tiled split)
     uint16_t* d_tiled = nullptr;                // tiled hi/lo operators + identity blocks
     int64_t tiled_size = 0;
@@ -166,22 +166,16 @@ struct dmrg_hop {
     int tune_lds_order = 0;                     // 0: heaviest item first; 1: XCD-aware by left sector;
                                                 // 2: merged handle, each problem's items together
     int tune_lds_task_order = 0;                // 0: tasks by source; 1: by operator pair
-    int tune_lds_split64 = 1;                   // 1: tasks fitting 64-wide stages run in the S = 64 classes
-    int tune_lds_pf = 0x4;                      // row-mode classes with a prefetch wavefront (bit mask)
-    int tune_lds_w6 = 0x8;                      // (S, 2) row-mode classes run as six one-row-tile wavefronts
-    int tune_lds_cw = 0;                        // row-mode classes with a copy wavefront (bit mask; measured
-                                                // slower for the split kernels, whose tasks are short)
-    int tune_big = 1;                           // 1: targets above the LDS stages take the two-pass GEMM path
+    int tune_lds_split64 = 1;                   // 1: tasks within 64 run in the S = 64 classes
+    int tune_big = 1;                           // 1: targets above 96 take the two-pass GEMM path
     int tune_big_stages = 64;                   // pass-2 item size in 32-wide k steps
-    int tune_big_stages1 = 16;                  // pass-1 workgroup size in 32-wide k steps
     int tune_big_tbudget_mb = 1024;             // T buffer of one chunk of large targets (MB)
     dmrg::BigPlan bplan{};
     std::vector<dmrg::BigChunk> big_chunks;
-    std::vector<std::pair<int32_t, int32_t>> big_t2_range;
     int tune_small_nq = 2;                      // task mode: least column-tile bound (2, 4 or 6)
     int tune_part_items = 1;                    // merged handles: 1 item cost caps per merged problem (from
                                                 // its own total), 0 one cap from the whole handle's total
-    int tune_split_task_route = 1;              // 1: a target within the split LDS stages keeps its tasks
+    int tune_split_task_route = 1;              // 1: a target within the split kernel's 96 keeps its tasks
                                                 // with sources that fit them; 0: any larger source sends
                                                 // the whole target to the two-pass path
     // FP64 two-pass path (hpsi_big64.hip) for the same large targets

@@ -658,7 +658,7 @@ void upload(dmrg_hop& H, const dmrg_build_opts* opts) {
         HIPCHK(dmrg::launch_presum(d_pb, (int)pblocks.size(), d_pt, H.d_pool, s));
     }
     phase("pre-summation");
-    // 4. split copies: tiled hi/lo for the LDS-staged kernel; row-major hi/lo only when some target
+    // 4. split copies: tiled hi/lo; row-major hi/lo only when some target
     //    needs the one-wave kernel
     if (H.has_split) {
         make_tiled_split(H, s);
@@ -771,20 +771,16 @@ extern "C" dmrg_status dmrg_build_blocks(const dmrg_problem* p, const dmrg_block
         if (const char* e = std::getenv("DMRG_SMALL_NR")) H->tune_small_nr = std::max(1, std::min(2, std::atoi(e)));
         if (const char* e = std::getenv("DMRG_LDS_ORDER")) H->tune_lds_order = std::max(0, std::min(2, std::atoi(e)));
         if (const char* e = std::getenv("DMRG_LDS_SPLIT64")) H->tune_lds_split64 = std::atoi(e) != 0;
-        if (const char* e = std::getenv("DMRG_LDS_PF")) H->tune_lds_pf = std::atoi(e) & 0xF;
-        if (const char* e = std::getenv("DMRG_LDS_W6")) H->tune_lds_w6 = std::atoi(e) & 0xA;
         if (const char* e = std::getenv("DMRG_BIG")) H->tune_big = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_BIG64")) H->tune_big64 = std::max(0, std::min(2, std::atoi(e)));
         if (const char* e = std::getenv("DMRG_LDS64")) H->tune_lds64 = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_ITEMS")) H->tune_lds64_items = std::max(64, std::atoi(e));
         if (const char* e = std::getenv("DMRG_LDS64_SMALL")) H->tune_lds64_small = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_LDS64_TASK_ROUTE")) H->tune_lds64_task_route = std::atoi(e) != 0;
-        if (const char* e = std::getenv("DMRG_LDS_CW")) H->tune_lds_cw = std::atoi(e) & 0xF;
         if (const char* e = std::getenv("DMRG_SPLIT_TASK_ROUTE")) H->tune_split_task_route = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_PART_ITEMS")) H->tune_part_items = std::atoi(e) != 0;
         if (const char* e = std::getenv("DMRG_VEC_STEP")) H->vec_step = std::max(1, std::min(dmrg::kPartialVecs, std::atoi(e)));
         if (const char* e = std::getenv("DMRG_BIG_STAGES")) H->tune_big_stages = std::max(4, std::atoi(e));
-        if (const char* e = std::getenv("DMRG_BIG_STAGES1")) H->tune_big_stages1 = std::max(4, std::atoi(e));
         if (const char* e = std::getenv("DMRG_BIG_TBUDGET_MB")) H->tune_big_tbudget_mb = std::max(16, std::atoi(e));
         if (const char* e = std::getenv("DMRG_LDS_TASK_ORDER")) H->tune_lds_task_order = std::atoi(e) == 1 ? 1 : 0;
         if (const char* e = std::getenv("DMRG_SMALL_NQ")) H->tune_small_nq = std::max(2, std::min(6, std::atoi(e))) / 2 * 2;
@@ -1102,9 +1098,6 @@ extern "C" dmrg_status dmrg_hop_combine(dmrg_hop* const* hops, int32_t n, void* 
         C->tune_split_task_route = hops[0]->tune_split_task_route;
         C->tune_part_items = hops[0]->tune_part_items;
         C->vec_step = hops[0]->vec_step;
-        C->tune_lds_pf = hops[0]->tune_lds_pf;
-        C->tune_lds_w6 = hops[0]->tune_lds_w6;
-        C->tune_lds_cw = hops[0]->tune_lds_cw;
         build_plan(*C, s);
         *out = C;
         return DMRG_OK;
@@ -1204,16 +1197,14 @@ extern "C" dmrg_status dmrg_hop_autotune(dmrg_hop* H, int32_t precision, int32_t
         struct Knob { int* field; std::vector<int> cand; };
         std::vector<Knob> knobs;
         int small_shape = H->tune_small_nq > 2 ? 2 : H->tune_small_nr > 1 ? 1 : 0;
-        int one = 1;                             // settings that no longer exist keep their place in `chosen`
+        int one = 1, none = 0;                   // settings that no longer exist keep their place in `chosen`
         const bool split = precision == DMRG_PREC_SPLIT2;
         if (split) {
             knobs.push_back({&H->tune_lds_items, {4096, 8192, 16384, 32768, 65536}});
             knobs.push_back({&H->tune_lds_order, H->n_parts > 1 ? std::vector<int>{0, 1, 2} : std::vector<int>{0, 1}});
             knobs.push_back({&small_shape, {0, 1, 2}});
             knobs.push_back({&H->tune_lds_split64, {1, 0}});
-            knobs.push_back({&H->tune_lds_w6, {0x8, 0, 0xA}});
-            knobs.push_back({&H->tune_lds_cw, {0, 0xF}});
-            knobs.push_back({&H->tune_lds_pf, {0x4, 0}});
+            for (int i = 0; i < 3; ++i) knobs.push_back({&none, {}});   // (wavefront roles of the LDS-staged kernel it replaced)
         } else {
             const bool lds64 = H->tune_lds64 != 0;   // the register-streamed kernel
             knobs.push_back({&H->tune_lds64_items, lds64 ? std::vector<int>{8192, 16384, 32768, 65536} : std::vector<int>{}});

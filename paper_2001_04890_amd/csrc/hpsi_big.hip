@@ -1,313 +1,203 @@
-// Split-BF16 sector GEMMs of Eq. dgemm (Section 2.2.1) for large sector blocks (gfx950).
+// Split-BF16 sector GEMMs of Eq. dgemm (Section 2.2.1) for sector blocks above the row-mode kernel's classes
+// (gfx950): pass 1 T'^T = X^T A^T per task, pass 2 Y += sum_tasks T B^T.
 //
-// A task Y += f A X B^T whose blocks are larger than the 96-wide LDS stages of hpsi_lds.hip runs as
-// two GEMM passes over 128 x 128 workgroup tiles (4 wavefronts, 64 x 64 each):
-//   pass 1  T'^T = X^T A^T   per task; P = X^T fragments (row order of k_pack_xt), Q = A rows; the
-//                             result is scaled by f, re-split into hi/lo and stored as T tiles in the
-//                             A-operand layout of pass 2 (the MFMA result layout of T'^T is exactly
-//                             that layout, so no shuffle is needed)
-//   pass 2  Y += sum_tasks T B^T   per target tile; K runs over every task of the item and its
-//                             32-column chunks; P = T fragments, Q = B rows
-// Each stage holds 16 tiles (32 KB) of both operands for one 32-wide k step, copied with
-// global_load_lds_dwordx4 one stage ahead (two stages, 64 KB: two workgroups per CU). Tiles outside
-// the operands are not copied; they only feed output positions that are never stored.
-// Precision as in hpsi_lds.hip: hi.hi + hi.lo + lo.hi products with FP32 accumulation; pass 2 adds
-// its FP32 sums into the FP64 output every kFlushBig tasks.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
+// A wavefront by itself owns up to 4 x 4 tiles of T'^T or of Y and reads both operands, one 32-wide k tile at a
+// time, straight into registers; there is no LDS and no barrier. A k tile is 16 loads of 1 KB and 48 MFMAs
+// (768 cycles); two of them are in flight, and every register is loaded again, for the k tile after next, as
+// soon as its last MFMA has been issued. All loads are unconditional buffer loads (what lies outside the block
+// or past the last k tile moves nothing), so the compiler knows how many are in flight.
+//
+// Operands are stored pre-tiled in fragment order (internal.h: 16 rows x 32 columns, hi and lo, 2 KB). The
+// MFMA result layout of T'^T = X^T A^T is the A-operand layout of pass 2, so pass 1 stores its tiles of T
+// without a shuffle.
+//
+// What bounds it: the traffic between the L2s and the last-level cache and the vector cache (16 KB per 768
+// cycles and wavefront, 85 B per clock of the 64 a CU's cache delivers were the matrix cores always busy). In
+// the matvec of 24 orbitals at bond dimension 1024 the path takes 1.2 ms, 1.7 ms with 128 x 128 tiles of four
+// wavefronts staged through LDS, which multiplied whole tiles at the blocks' edges.
+//
+// Precision: each product a.b is a_hi b_hi + a_hi b_lo + a_lo b_hi on v_mfma_f32_16x16x32_bf16 with FP32
+// accumulation; T is scaled by f and re-split; the results of at most kFlushBig tasks are accumulated in FP32
+// and then added in FP64.
+#include "device.h"
 #include "internal.h"
 
 namespace dmrg {
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-constexpr int kStageTiles = 16;
-constexpr int kStageU16 = kStageTiles * kTileU16;
 constexpr int kFlushBig = 8;
+constexpr int kTileBytes = 2 * kTileU16;
 
-// hi and lo parts of eight values (v_cvt_pk_bf16_f32 rounds two at a time to nearest even; rounding in integer
-// arithmetic took as long as the MFMAs around it)
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
-}
-__device__ __forceinline__ void split8(const float (&v)[8], u16x8& hi, u16x8& lo) {
-    u32x4 h, l;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        h[i] = pack2(v[2 * i], v[2 * i + 1]);
-        l[i] = pack2(v[2 * i] - __builtin_bit_cast(float, h[i] << 16), v[2 * i + 1] - __builtin_bit_cast(float, h[i] & 0xffff0000u));
-    }
-    hi = __builtin_bit_cast(u16x8, h);
-    lo = __builtin_bit_cast(u16x8, l);
-}
-__device__ __forceinline__ bf16x8 as_bf(u16x8 v) { return __builtin_bit_cast(bf16x8, v); }
-__device__ __forceinline__ f32x4 mma3(u16x8 ah, u16x8 al, u16x8 bh, u16x8 bl, f32x4 c) {
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(ah), as_bf(bh), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(ah), as_bf(bl), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(al), as_bf(bh), c, 0, 0, 0);
-    return c;
-}
-__device__ __forceinline__ u16x8 lds8(const uint16_t* p) { return *reinterpret_cast<const u16x8*>(p); }
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
+// One k tile of both operands: P's tiles at byte po[i], Q's at qo[i]. use: 0 past the last k tile, 1 inside a
+// task, 2 a task's last k tile, 3 the last of all
+struct Step { __amdgpu_buffer_rsrc_t p, q; int use; };
 
-// Copy the 16 tiles of one stage: tile i (0..15) from (i < 8 ? p_base : q_base) + src[i] (u16
-// offset, < 0: not present) to stage + i * kTileU16. 32 half-tile copies of 1 KB, 8 per wavefront.
-__device__ __forceinline__ void copy_stage(const uint16_t* __restrict__ p_base, const uint16_t* __restrict__ q_base,
-                                           const int64_t (&src)[kStageTiles], uint16_t* stage, int wave, int lane) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int h = wave * 8 + k, tile = h >> 1, part = h & 1;
-        const uint16_t* base = tile < 8 ? p_base : q_base;
-        if (src[tile] >= 0)
-            __builtin_amdgcn_global_load_lds((const void*)(base + src[tile] + part * 512 + lane * 8),
-                                             (lds_ptr_t)(stage + tile * kTileU16 + part * 512), 16, 0, 0);
+// acc[i][j] += P tile i . Q tile j^T over the k tiles that next() gives, for i < np and j < nq; after(use)
+// follows each k tile
+template <class Next, class After>
+__device__ __forceinline__ void multiply(f32x4 (&acc)[4][4], int np, int nq, uint32_t (&po)[4], uint32_t (&qo)[4], Next&& next,
+                                         After&& after) {
+    Frag p[2][4], q[2][4];
+    int use[2];
+    each<2>([&](auto b) {
+        const Step S = next();
+        each<4>([&](auto i) { p[b][i] = ld_frag(S.p, po[i]); });
+        each<4>([&](auto i) { q[b][i] = ld_frag(S.q, qo[i]); });
+        use[b] = S.use;
+        fence();
+    });
+    for (bool more = true; more;) {
+        each<2>([&](auto bb) {
+            constexpr int b = bb;
+            if (!more) return;
+            if (use[b] == 0) {
+                more = false;
+                return;
+            }
+            const Step S = next();
+            each<4>([&](auto ii) {
+                constexpr int i = ii;
+                if (i < np) each<3>([&](auto w) {
+                    // the chains of the different accumulators alternate: an MFMA's result is not needed by the next
+                    each<4>([&](auto jj) {
+                        constexpr int j = jj, W = decltype(w)::value;
+                        if (j < nq) acc[i][j] = mma<W>(p[b][i], q[b][j], acc[i][j]);
+                    });
+                });
+                fence();
+                p[b][i] = ld_frag(S.p, po[i]);
+                fence();
+            });
+            each<4>([&](auto j) { q[b][j] = ld_frag(S.q, qo[j]); });
+            fence();
+            after(use[b]);
+            use[b] = S.use;
+        });
     }
 }
 
 }  // namespace
 
 // ------------------------------------------------------------------ pass 1: T = f A X per task
-// One workgroup runs the groups [ranges[blockIdx.x], ranges[blockIdx.x + 1]) (each: one task's 8 row
-// tiles x 4 column chunks) as one pipeline of k steps; at the end of a group its T tiles are stored.
-__global__ __launch_bounds__(256) void k_big_t(const BigT1* __restrict__ work, const int32_t* __restrict__ ranges,
-                                               const uint16_t* __restrict__ pool_t, const uint16_t* __restrict__ xt,
-                                               uint16_t* __restrict__ tbuf, const int32_t* __restrict__ mask) {
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kStageU16];
-    const int g_begin = uni(ranges[blockIdx.x]), g_end = uni(ranges[blockIdx.x + 1]);
-    if (mask && mask[work[g_begin].part] != kPartActive) return;   // a workgroup's groups share one part
-    const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wj = wave & 1, wr = wave >> 1;   // wave: chunks jb + 2 wj + {0,1}, row tiles rb + 4 wr + {0..3}
-    struct G { int64_t x, a, t; float f; int pa32, pd32, nrt, rb, jb; };
-    auto load_g = [&](int i) {
-        const BigT1* wp = work + i;
-        G d;
-        d.x = uni64(wp->xt); d.a = uni64(wp->a); d.t = uni64(wp->t);
-        d.f = (float)__builtin_bit_cast(double, uni64(__builtin_bit_cast(int64_t, wp->f)));
-        d.pa32 = uni(wp->pa32); d.pd32 = uni(wp->pd32); d.nrt = uni(wp->nrt); d.rb = uni(wp->rb); d.jb = uni(wp->jb);
-        return d;
-    };
-    // stage (group, kt): tiles 0..7 = X^T (chunk jb + i/2, half i%2, kt), tiles 8..15 = A (row tile rb + i, kt)
-    auto sources = [&](const G d, int kt, int64_t (&src)[kStageTiles]) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int jc = d.jb + (i >> 1), h2 = i & 1;
-            src[i] = jc < d.pd32 ? d.x + (int64_t)((jc * 2 + h2) * d.pa32 + kt) * kTileU16 : -1;
-            const int rt = d.rb + i;
-            src[8 + i] = rt < d.nrt ? d.a + (int64_t)(rt * d.pa32 + kt) * kTileU16 : -1;
-        }
-    };
-    f32x4 acc[2][2][4];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[a][b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto store = [&](const G d) {
-        int ln = lane;   // opaque copy: keep the store addresses out of the main loop
-        asm volatile("" : "+v"(ln));
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int jc = d.jb + 2 * wj + jj, rt = d.rb + 4 * wr + rr;
-                if (jc < d.pd32 && rt < d.nrt) {
-                    // acc[jj][h2][rr][v] = T'[row 16 rt + li][col 32 jc + 8 g + 4 h2 + v]
-                    u16x8 th, tl;
-                    float v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = d.f * acc[jj][u >> 2][rr][u & 3];
-                    split8(v, th, tl);
-                    uint16_t* dst = tbuf + d.t + (int64_t)(rt * d.pd32 + jc) * kTileU16 + ln * 8;
-                    *reinterpret_cast<u16x8*>(dst) = th;
-                    *reinterpret_cast<u16x8*>(dst + 512) = tl;
-                }
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) acc[jj][h2][rr] = f32x4{0.f, 0.f, 0.f, 0.f};
+__global__ __launch_bounds__(64, 2) void k_big_t(const BigT* __restrict__ work, const uint16_t* __restrict__ pool_t,
+                                                 const uint16_t* __restrict__ xt, uint16_t* __restrict__ tbuf,
+                                                 const int32_t* __restrict__ mask) {
+    const BigT* wp = work + blockIdx.x;
+    const int ka = uni(wp->ka), pd = uni(wp->pd);
+    if (ka == 0) return;                                       // filler
+    if (mask && mask[uni(wp->part)] != kPartActive) return;
+    const int rb = uni(wp->rb), nr = uni(wp->nr), jb = uni(wp->jb), nj = uni(wp->nj);
+    const int lane = threadIdx.x;
+    const uint16_t* x = xt + uni64(wp->xt);
+    const uint16_t* a = pool_t + uni64(wp->a);
+    f32x4 acc[4][4];                                           // [column chunk half][row tile]
+    uint32_t xo[4], ao[4];
+    each<4>([&](auto i) {
+        each<4>([&](auto j) { acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f}; });
+        xo[i] = i < 2 * nj ? (uint32_t)((2 * jb + i) * ka) * kTileBytes + (uint32_t)lane * 16u : kNowhere;
+        ao[i] = i < nr ? (uint32_t)((rb + i) * ka) * kTileBytes + (uint32_t)lane * 16u : kNowhere;
+    });
+    int left = ka;                                             // k tiles from the next one on
+    multiply(acc, 2 * nj, nr, xo, ao,
+             [&]() {
+                 const int bytes = left > 0 ? 0x7fffffff : 0;
+                 const Step S{buf(x, bytes), buf(a, bytes), left > 0};
+                 x += kTileU16;
+                 a += kTileU16;
+                 --left;
+                 return S;
+             },
+             [](int) {});
+    // acc[2 jj + h2][rr][v] = T'[row 16 rt + li][col 32 jc + 8 g + 4 h2 + v]
+    const float f = (float)unid(wp->f);
+    uint16_t* to = tbuf + uni64(wp->t) + (int64_t)(rb * pd + jb) * kTileU16 + lane * 8;
+    each<2>([&](auto jj) {
+        each<4>([&](auto rr) {
+            if (jj < nj && rr < nr) {
+                float v[8];
+                each<8>([&](auto i) {
+                    constexpr int u = i;
+                    v[u] = acc[2 * jj + (u >> 2)][rr][u & 3];
+                });
+                const Frag t = split8(f, v);
+                uint16_t* dst = to + (int64_t)(rr * pd + jj) * kTileU16;
+                *reinterpret_cast<u16x8*>(dst) = t.h;
+                *reinterpret_cast<u16x8*>(dst + 512) = t.l;
             }
-    };
-
-    int gi = g_begin, kt = 0;
-    G cur = load_g(gi);
-    {
-        int64_t src[kStageTiles];
-        sources(cur, 0, src);
-        copy_stage(xt, pool_t, src, lds, wave, lane);
-    }
-    wait_vm();
-    __syncthreads();
-    int st = 0;
-    for (;;) {
-        int ngi = gi, nkt = kt + 1;
-        if (nkt == cur.pa32) { ngi = gi + 1; nkt = 0; }
-        const bool has_next = ngi < g_end;
-        G nxt = cur;
-        if (has_next) {
-            if (ngi != gi) nxt = load_g(ngi);
-            int64_t src[kStageTiles];
-            sources(nxt, nkt, src);
-            copy_stage(xt, pool_t, src, lds + (st ^ 1) * kStageU16, wave, lane);
-        }
-        const uint16_t* sp = lds + st * kStageU16 + lane * 8;
-        u16x8 ph[2][2], pl[2][2], qh[4], ql[4];
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                const uint16_t* t = sp + ((2 * wj + jj) * 2 + h2) * kTileU16;
-                ph[jj][h2] = lds8(t);
-                pl[jj][h2] = lds8(t + 512);
-            }
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const uint16_t* t = sp + (8 + 4 * wr + rr) * kTileU16;
-            qh[rr] = lds8(t);
-            ql[rr] = lds8(t + 512);
-        }
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-#pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr)
-                    acc[jj][h2][rr] = mma3(ph[jj][h2], pl[jj][h2], qh[rr], ql[rr], acc[jj][h2][rr]);
-        if (ngi != gi) store(cur);        // last k step of the group
-        wait_vm();
-        __syncthreads();
-        if (!has_next) break;
-        gi = ngi; kt = nkt; cur = nxt;
-        st ^= 1;
-    }
+        });
+    });
 }
 
-// ------------------------------------------------------------------ pass 2: Y += sum T B^T per tile
-__global__ __launch_bounds__(256) void k_big_y(const Item* __restrict__ items, const BigT2* __restrict__ tasks,
-                                               const uint16_t* __restrict__ pool_t,
-                                               const uint16_t* __restrict__ tbuf, double* __restrict__ y,
-                                               double* __restrict__ part, const int32_t* __restrict__ mask) {
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kStageU16];
+// ------------------------------------------------------------------ pass 2: Y += sum T B^T
+__global__ __launch_bounds__(64, 2) void k_big_y(const Item* __restrict__ items, const BigT2* __restrict__ tasks,
+                                                 const uint16_t* __restrict__ pool_t, const uint16_t* __restrict__ tbuf,
+                                                 double* __restrict__ y, double* __restrict__ part,
+                                                 const int32_t* __restrict__ mask) {
     const Item* ip = items + blockIdx.x;
-    if (mask && mask[ip->part] != kPartActive) return;
+    int task = uni(ip->t_begin);
+    const int t_end = uni(ip->t_end);
+    if (task >= t_end) return;                                 // filler
+    if (mask && mask[uni(ip->part)] != kPartActive) return;
+    const int m_ap = uni(ip->m_ap), m_dp = uni(ip->m_dp), rb = uni(ip->r0) >> 4, qb = uni(ip->c0) >> 4;
+    const int nr = part_len((m_ap + 15) >> 4, rb, 4), nq = part_len((m_dp + 15) >> 4, qb, 4);
     const int64_t y_off = uni64(ip->y_off), part_off = uni64(ip->part_off);
-    const int m_ap = uni(ip->m_ap), m_dp = uni(ip->m_dp), r0 = uni(ip->r0), c0 = uni(ip->c0);
-    const int t_begin = uni(ip->t_begin), t_end = uni(ip->t_end);
-    const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int wr = wave >> 1, wq = wave & 1;   // wave: row tiles rb + 4 wr + {0..3}, col tiles qb + 4 wq + {0..3}
-    const int rb = r0 >> 4, qb = c0 >> 4;
-    const int nrt = (m_ap + 15) >> 4, nq = (m_dp + 15) >> 4;
-    const int tn = 16 * min(8, nq - qb);       // partial tile: rows [r0, r0 + 128), cols [c0, c0 + tn)
-
-    // stage (task t, chunk jc): tiles 0..7 = T (row tile rb + i, jc), tiles 8..15 = B (col tile qb + i, jc)
-    auto sources = [&](int64_t t_t, int64_t t_b, int pd32, int jc, int64_t (&src)[kStageTiles]) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int rt = rb + i;
-            src[i] = rt < nrt ? t_t + (int64_t)(rt * pd32 + jc) * kTileU16 : -1;
-            const int q = qb + i;
-            src[8 + i] = q < nq ? t_b + (int64_t)(q * pd32 + jc) * kTileU16 : -1;
-        }
-    };
+    const int lane = threadIdx.x;
     f32x4 acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    bool first_flush = true;
-    auto flush = [&]() {
-        // output addresses are recomputed here from an opaque copy of the lane id: hoisted out of the
-        // main loop they would hold 64 address pairs in registers for the whole kernel
-        int ln = lane;
-        asm volatile("" : "+v"(ln));
-        const int fli = ln & 15, fg = ln >> 4;
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-                const int rt = rb + 4 * wr + rr, q = qb + 4 * wq + qq;
-                if (rt < nrt && q < nq) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int row = 16 * rt + 4 * fg + v, col = 16 * q + fli;
-                        if (part_off < 0) {
-                            if (row < m_ap && col < m_dp) y[y_off + (int64_t)row * m_dp + col] += (double)acc[rr][qq][v];
-                        } else {
-                            double* d = part + part_off + (int64_t)(row - r0) * tn + (col - c0);
-                            *d = first_flush ? (double)acc[rr][qq][v] : *d + (double)acc[rr][qq][v];
-                        }
-                    }
-                    asm volatile("" ::: "memory");
-                }
-                acc[rr][qq] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        first_flush = false;
-    };
-
-    int t = t_begin, jc = 0;
-    int64_t T_t = uni64(tasks[t].t), T_b = uni64(tasks[t].b);
-    int T_pd = uni(tasks[t].pd32);
-    {
-        int64_t src[kStageTiles];
-        sources(T_t, T_b, T_pd, 0, src);
-        copy_stage(tbuf, pool_t, src, lds, wave, lane);
-    }
-    wait_vm();
-    __syncthreads();
-    int st = 0, since_flush = 0;
-    for (;;) {
-        // next stage
-        int nt = t, njc = jc + 1;
-        if (njc == T_pd) { nt = t + 1; njc = 0; }
-        const bool has_next = nt < t_end;
-        int64_t N_t = T_t, N_b = T_b;
-        int N_pd = T_pd;
-        if (has_next) {
-            if (nt != t) { N_t = uni64(tasks[nt].t); N_b = uni64(tasks[nt].b); N_pd = uni(tasks[nt].pd32); }
-            int64_t src[kStageTiles];
-            sources(N_t, N_b, N_pd, njc, src);
-            copy_stage(tbuf, pool_t, src, lds + (st ^ 1) * kStageU16, wave, lane);
-        }
-        const uint16_t* sp = lds + st * kStageU16 + lane * 8;
-        u16x8 ph[4], pl[4], qh[4], ql[4];
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-            const uint16_t* p = sp + (4 * wr + rr) * kTileU16;
-            ph[rr] = lds8(p);
-            pl[rr] = lds8(p + 512);
-        }
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-            const uint16_t* p = sp + (8 + 4 * wq + qq) * kTileU16;
-            qh[qq] = lds8(p);
-            ql[qq] = lds8(p + 512);
-        }
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) acc[rr][qq] = mma3(ph[rr], pl[rr], qh[qq], ql[qq], acc[rr][qq]);
-        if (nt != t || !has_next) {                 // task boundary
-            if (++since_flush == kFlushBig || !has_next) { since_flush = 0; flush(); }
-        }
-        wait_vm();
-        __syncthreads();
-        if (!has_next) break;
-        t = nt; jc = njc; T_t = N_t; T_b = N_b; T_pd = N_pd;
-        st ^= 1;
-    }
+    uint32_t to[4], bo[4];
+    each<4>([&](auto i) { each<4>([&](auto j) { acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
+    const uint16_t *t = nullptr, *b = nullptr;
+    int left = 0, since_flush = 0;                             // k tiles of the task from the next one on; tasks since
+    bool first = true;
+    multiply(acc, nr, nq, to, bo,
+             [&]() {
+                 if (left <= 0 && task < t_end) {
+                     const BigT2* tp = tasks + task++;
+                     const int pd = uni(tp->pd32);
+                     left = pd;
+                     t = tbuf + uni64(tp->t) + (int64_t)rb * pd * kTileU16;
+                     b = pool_t + uni64(tp->b) + (int64_t)qb * pd * kTileU16;
+                     each<4>([&](auto i) {
+                         const uint32_t at = (uint32_t)(i * pd) * kTileBytes + (uint32_t)lane * 16u;
+                         to[i] = i < nr ? at : kNowhere;
+                         bo[i] = i < nq ? at : kNowhere;
+                     });
+                 }
+                 const int bytes = left > 0 ? 0x7fffffff : 0;
+                 const Step S{buf(t, bytes), buf(b, bytes), left <= 0 ? 0 : left > 1 ? 1 : task < t_end ? 2 : 3};
+                 t += kTileU16;
+                 b += kTileU16;
+                 --left;
+                 return S;
+             },
+             [&](int use) __attribute__((always_inline)) {
+                 if (use < 2 || (++since_flush < kFlushBig && use != 3)) return;
+                 since_flush = 0;
+                 // addresses from an opaque copy of the lane id, so that they are not held through the main loop
+                 int ln = lane;
+                 asm volatile("" : "+v"(ln));
+                 const int li = ln & 15, g = ln >> 4, tn = 16 * nq;
+                 each<4>([&](auto rr) {
+                     each<4>([&](auto qq) {
+                         if (rr < nr && qq < nq) {
+                             each<4>([&](auto i) {
+                                 constexpr int v = i;
+                                 const int r = 16 * rr + 4 * g + v, c = 16 * qq + li;
+                                 if (part_off < 0) {
+                                     const int row = 16 * rb + r, col = 16 * qb + c;
+                                     if (row < m_ap && col < m_dp) y[y_off + (int64_t)row * m_dp + col] += (double)acc[rr][qq][v];
+                                 } else {
+                                     double* d = part + part_off + r * tn + c;
+                                     *d = first ? (double)acc[rr][qq][v] : *d + (double)acc[rr][qq][v];
+                                 }
+                             });
+                             fence();   // the read-modify-writes of one tile stay together (bounded register use)
+                         }
+                         acc[rr][qq] = f32x4{0.f, 0.f, 0.f, 0.f};
+                     });
+                 });
+                 first = false;
+             });
 }
 
 hipError_t launch_hpsi_big(const BigPlan& P, const uint16_t* pool_t, const uint16_t* xt, double* y, hipStream_t s,
@@ -315,10 +205,10 @@ hipError_t launch_hpsi_big(const BigPlan& P, const uint16_t* pool_t, const uint1
     for (int c = 0; c < P.n_chunks; ++c) {
         const BigChunk& C = P.chunks[c];
         if (C.t1_end > C.t1_begin)
-            hipLaunchKernelGGL(k_big_t, dim3(C.t1_end - C.t1_begin), dim3(256), 0, s, P.t1, P.t1_ranges + C.t1_begin,
-                               pool_t, xt, P.tbuf, active);
+            hipLaunchKernelGGL(k_big_t, dim3(C.t1_end - C.t1_begin), dim3(64), 0, s, P.t1 + C.t1_begin, pool_t, xt, P.tbuf,
+                               active);
         if (C.item_end > C.item_begin)
-            hipLaunchKernelGGL(k_big_y, dim3(C.item_end - C.item_begin), dim3(256), 0, s, P.items + C.item_begin, P.t2,
+            hipLaunchKernelGGL(k_big_y, dim3(C.item_end - C.item_begin), dim3(64), 0, s, P.items + C.item_begin, P.t2,
                                pool_t, P.tbuf, y, P.partial, active);
         const hipError_t e = launch_reduce_partials(P.reduces + C.red_begin, C.red_end - C.red_begin, P.red_chunks,
                                                     P.partial, y, s, active);

@@ -19,53 +19,16 @@
 // rest is the start and end of a wavefront's work and the ends of the launches). 76 orbitals at bond dimension
 // 6000, one share: 25.3 ms, of which 18.6 ms are MFMAs; 42.4 ms with 128 x 128 tiles of four wavefronts staged
 // through LDS, whose stages waited at a barrier and which multiplied whole tiles at the blocks' edges.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include <type_traits>
-#include <utility>
-
+#include "device.h"
 #include "internal.h"
 
 namespace dmrg {
 
 namespace {
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef int i32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
 constexpr int kTileD = 256;                  // doubles per tile
 
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// f(integral_constant<int, 0>), f(integral_constant<int, 1>), ..: a loop whose indices are constants before
-// any optimisation, so that arrays indexed by them are registers from the start.
-template <class F, int... I>
-__device__ __forceinline__ void each_of(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void each(F&& f) {
-    each_of(f, std::make_integer_sequence<int, N>{});
-}
-// keeps the loads before it from sinking to their uses and those after it from rising
-__device__ __forceinline__ void fence() { asm volatile("" ::: "memory"); }
-
-// `bytes` (0: none) at p, for buffer loads
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const double* p, int bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), (short)0, bytes, 0x00027000);
-}
-__device__ __forceinline__ f64x2 ld2(__amdgpu_buffer_rsrc_t b, uint32_t at) {
-    return __builtin_bit_cast(f64x2, (i32x4)__builtin_amdgcn_raw_buffer_load_b128(b, (int)at, 0, 0));
-}
-constexpr uint32_t kNowhere = 0x80000000u;   // an offset outside every buffer
+__device__ __forceinline__ f64x2 ld2(__amdgpu_buffer_rsrc_t b, uint32_t at) { return __builtin_bit_cast(f64x2, ld16(b, at, 0)); }
 
 // The lane's byte offset in row tile `tile` of a column group of an operand of r4 4-row groups (rows past the
 // operand's last group repeat its last row)
@@ -170,11 +133,11 @@ __global__ void k_pack_xt64(const PackBlock* __restrict__ packs, const double* _
 }
 
 // ------------------------------------------------------------------ pass 1: T = f A X per task
-__global__ __launch_bounds__(64, 2) void k_big64_t(const Big64T* __restrict__ work, const double* __restrict__ ops,
+__global__ __launch_bounds__(64, 2) void k_big64_t(const BigT* __restrict__ work, const double* __restrict__ ops,
                                                    const double* __restrict__ xt, double* __restrict__ tbuf,
                                                    const int32_t* __restrict__ mask) {
-    const Big64T* wp = work + blockIdx.x;
-    const int ka4 = uni(wp->ka4), kd4 = uni(wp->kd4), ra4 = uni(wp->ra4), pd = uni(wp->pd);
+    const BigT* wp = work + blockIdx.x;
+    const int ka4 = uni(wp->ka), kd4 = uni(wp->kd), ra4 = uni(wp->ra), pd = uni(wp->pd);
     if (ka4 == 0) return;                                      // filler
     if (mask && mask[uni(wp->part)] != kPartActive) return;
     const int rb = uni(wp->rb), nr = uni(wp->nr), jb = uni(wp->jb), nj = uni(wp->nj);
@@ -197,7 +160,7 @@ __global__ __launch_bounds__(64, 2) void k_big64_t(const Big64T* __restrict__ wo
         return G;
     });
     // acc[jj][rr][v] = T'^T[j 16 jt + g + 4 v][r 16 rt + li] = T tile (rt, jt), lane value v
-    const double f = __builtin_bit_cast(double, uni64(__builtin_bit_cast(int64_t, wp->f)));
+    const double f = unid(wp->f);
     double* to = tbuf + uni64(wp->t) + (int64_t)(rb * pd + jb) * kTileD + lane * 2;
     each<4>([&](auto jj) {
         each<4>([&](auto rr) {
@@ -222,7 +185,7 @@ __global__ __launch_bounds__(64, 2) void k_big64_y(const Item* __restrict__ item
     if (task >= t_end) return;                                 // filler
     if (mask && mask[uni(ip->part)] != kPartActive) return;
     const int m_ap = uni(ip->m_ap), m_dp = uni(ip->m_dp), rb = uni(ip->r0) >> 4, qb = uni(ip->c0) >> 4;
-    const int nr = big64_len((m_ap + 15) >> 4, rb), nq = big64_len((m_dp + 15) >> 4, qb), rb4 = (m_dp + 3) >> 2;
+    const int nr = part_len((m_ap + 15) >> 4, rb, 4), nq = part_len((m_dp + 15) >> 4, qb, 4), rb4 = (m_dp + 3) >> 2;
     const int lane = threadIdx.x;
     f64x4 acc[4][4];
     uint32_t to[4], bo[4];
@@ -294,7 +257,7 @@ hipError_t launch_hpsi_big64(const BigPlan& P, const double* ops, const double* 
     for (int c = 0; c < P.n_chunks; ++c) {
         const BigChunk& C = P.chunks[c];
         if (C.t1_end > C.t1_begin)
-            hipLaunchKernelGGL(k_big64_t, dim3(C.t1_end - C.t1_begin), dim3(64), 0, s, P.w1 + C.t1_begin, ops, xt,
+            hipLaunchKernelGGL(k_big64_t, dim3(C.t1_end - C.t1_begin), dim3(64), 0, s, P.t1 + C.t1_begin, ops, xt,
                                reinterpret_cast<double*>(P.tbuf), active);
         if (C.item_end > C.item_begin)
             hipLaunchKernelGGL(k_big64_y, dim3(C.item_end - C.item_begin), dim3(64), 0, s, P.items + C.item_begin, P.t2,

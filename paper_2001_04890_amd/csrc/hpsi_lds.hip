@@ -1,20 +1,20 @@
-// LDS-staged split-BF16 sector GEMMs of Eq. dgemm (Section 2.2.1) for gfx950.
+// Split-BF16 sector GEMMs of Eq. dgemm (Section 2.2.1) for sectors within 96 x 96 (gfx950).
 //
-// One workgroup of NW compute wavefronts (kLdsWaves, or six of one row tile each for targets of
-// 65..96 rows) owns a whole row block of a target psi block (every column) and loops over the
-// target's tasks Y += f * A . X . B^T, sorted by source block. Wave w owns row tiles
-// [TP w, TP w + TP) of the block; an optional extra wavefront only touches the cache lines of the
-// task after next. Per task:
-//   GEMM1  T'^T = X^T . A(rows)^T       A-operand: X^T fragments from LDS, B-operand: A rows held in
-//                                       registers (loaded straight from the tiled pool)
-//   GEMM2  Y   += T' . B^T              A-operand: T' (the MFMA result layout of GEMM1 is the
-//                                       A-operand layout of GEMM2), B-operand: B fragments from LDS
-// X^T (shared by the run of tasks with the same source) and B (per task) are copied into LDS with
-// global_load_lds_dwordx4 one task ahead (two stages), so the copy of task k+1 and the A-fragment
-// loads of task k+1 (branch-free: the compiler must not have to wait for them before task k's
-// MFMAs) overlap the MFMAs of task k. Operands are stored pre-tiled in fragment order
-// (internal.h), which makes every copy a contiguous 1 KB per wave instruction and every LDS read a
-// conflict-free ds_read_b128 at lane * 16 bytes.
+// Row-mode kernel: a workgroup owns a range of the tasks Y += f * A . X . B^T of a target psi block (every
+// column), sorted by source block; each of its two or three wavefronts owns two row tiles and runs the range by
+// itself. A task is cut into steps, one per 32-wide column chunk jc of the source, and per step:
+//   GEMM1  T'^T(:, jc) = X^T(jc, :) . A(rows)^T   A's rows stay in registers for the task
+//   GEMM2  Y          += T'(:, jc) . B(:, jc)^T   GEMM1's result layout is GEMM2's A-operand layout
+// X^T and B stream from the caches into registers that are loaded again, for the next step, as soon as their
+// last MFMA has been issued: every load is an unconditional buffer load a whole step (up to 1152 cycles of
+// MFMAs) ahead of its use. There is no barrier; the wavefronts of a workgroup read the same X^T and B and find
+// them in the vector cache. LDS holds the FP64 sums, which leaves the registers to the operands.
+// Operands are stored pre-tiled in fragment order (internal.h): every load is a contiguous 1 KB.
+//
+// What bounds it: the traffic between the L2s and the last-level cache (6.1 .. 6.5 TB/s in the row-mode launches
+// of 24 orbitals at bond dimension 1024; an operator block is read once per target that uses it). That
+// problem's matvec takes 3.63 ms; 4.55 ms when the X^T and B of one workgroup per CU were staged in LDS, with a
+// barrier per task and the matrix cores busy 13 .. 21% of the time.
 //
 // Precision: each product a.b is a_hi b_hi + a_hi b_lo + a_lo b_hi on v_mfma_f32_16x16x32_bf16 with
 // FP32 accumulation; T' is scaled by f and re-split; task results are accumulated in FP32 over at
@@ -22,15 +22,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "device.h"
 #include "internal.h"
 
 namespace dmrg {
 
 namespace {
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kFlush = 8;   // tasks accumulated in FP32 before the FP64 update
 
@@ -40,57 +37,7 @@ __device__ __forceinline__ unsigned short bf16_rne(float f) {
     return (unsigned short)(u >> 16);
 }
 __device__ __forceinline__ float bf16_f32(unsigned short h) { return __builtin_bit_cast(float, (uint32_t)h << 16); }
-// hi and lo parts of eight values (v_cvt_pk_bf16_f32 rounds two at a time to nearest even; rounding in integer
-// arithmetic took as long as the MFMAs around it)
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
-}
-__device__ __forceinline__ void split8(const float (&v)[8], u16x8& hi, u16x8& lo) {
-    u32x4 h, l;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        h[i] = pack2(v[2 * i], v[2 * i + 1]);
-        l[i] = pack2(v[2 * i] - __builtin_bit_cast(float, h[i] << 16), v[2 * i + 1] - __builtin_bit_cast(float, h[i] & 0xffff0000u));
-    }
-    hi = __builtin_bit_cast(u16x8, h);
-    lo = __builtin_bit_cast(u16x8, l);
-}
-
-__device__ __forceinline__ bf16x8 as_bf(u16x8 v) { return __builtin_bit_cast(bf16x8, v); }
-__device__ __forceinline__ f32x4 mma3(u16x8 ah, u16x8 al, u16x8 bh, u16x8 bl, f32x4 c) {
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(ah), as_bf(bh), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(ah), as_bf(bl), c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf(al), as_bf(bh), c, 0, 0, 0);
-    return c;
-}
-__device__ __forceinline__ u16x8 gld8(const uint16_t* p) { return *reinterpret_cast<const u16x8*>(p); }
-__device__ __forceinline__ u16x8 lds8(const uint16_t* p) { return *reinterpret_cast<const u16x8*>(p); }
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-// Copy n16 16-byte chunks (a multiple of 64) from global src to LDS dst, spread over the workgroup's
-// waves; each wave instruction moves 64 consecutive chunks (lane i -> dst + 16 i).
-template <int NW = kLdsWaves>
-__device__ __forceinline__ void copy_to_lds(const uint16_t* __restrict__ src, uint16_t* dst, int n16, int wave,
-                                            int lane) {
-    for (int c = wave * 64; c < n16; c += NW * 64)
-        __builtin_amdgcn_global_load_lds((const void*)(src + (int64_t)(c + lane) * 8), (lds_ptr_t)(dst + c * 8), 16,
-                                         0, 0);
-}
-
-__device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Wave-uniform values in scalar registers (descriptors must not round-trip through scratch memory:
-// a scratch reload waits on vmcnt and would drain the copies of the next task).
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
+// Wave-uniform values in scalar registers.
 __device__ __forceinline__ float unif(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
 }
@@ -189,277 +136,174 @@ __global__ void k_pack_xt(const PackBlock* __restrict__ packs, const double* __r
     }
 }
 
-// ------------------------------------------------------------------ the sector-GEMM kernel
-// S: largest padded dimension of the class (LDS stage size), TP: row tiles per wave. The item's
-// column tile count tq = ceil((m_d' - c0) / 16) <= S / 16 is a runtime bound of unrolled loops.
-// PF = 1: one more wavefront per workgroup touches, during task t, the cache lines of the operands
-// of task t+2 (X^T if its source changes, B, and the workgroup's A rows) with loads into a scratch
-// LDS word that nobody reads; it never waits for them, so the LDS copies of task t+2, issued by the
-// compute waves one task later, find their lines in L2.
-// NW compute wavefronts (16 TP rows each): kLdsWaves, or 3 for the (96, 2) class with a prefetch
-// wavefront, whose targets have at most 96 rows, so the workgroup stays at four wavefronts.
-// CW = 1 (with PF = 0): the extra wavefront is a copy wavefront instead, which issues every LDS copy
-// of the item one task ahead, so the compute wavefronts never wait for copies in flight (the compiler
-// makes the first LDS read after a global-to-LDS copy wait for it, per wavefront).
-template <int S, int TP, int PF, int NW = kLdsWaves, int CW = 0>
-__global__ __launch_bounds__(NW * 64 + PF * 64 + CW * 64) void k_hpsi_lds(const Item* __restrict__ items,
-                                                             const LTask* __restrict__ tasks,
-                                                             const uint16_t* __restrict__ pool_t,
-                                                             const uint16_t* __restrict__ xtall,
-                                                             double* __restrict__ yall, double* __restrict__ partall,
-                                                             int64_t n_coeff, int64_t xt_size, int64_t slot_stride,
-                                                             const int32_t* __restrict__ mask) {
-    if (mask && mask[items[blockIdx.x].part] != kPartActive) return;   // whole workgroup, before any barrier
-    constexpr int KS = S / 32;          // max k tiles (and j chunks) of a source
-    constexpr int QS = S / 16;          // max column tiles of the target
-    constexpr int XS = KS * 2 * KS * kTileU16;
-    constexpr int BS = QS * KS * kTileU16;
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2 * XS + 2 * BS + PF * 128];   // + touch target
+// ------------------------------------------------------------------ row-mode kernel
+// NR row tiles of one wavefront (see the head of the file). sum: the wavefront's FP64 sums in LDS, one
+// double per lane and accumulator register.
+template <int S, int NR>
+__device__ __forceinline__ void rows_item(const ID& I, const LTask* __restrict__ tasks, const uint16_t* __restrict__ pool_t,
+                                          const uint16_t* __restrict__ xt, double* __restrict__ y,
+                                          double* __restrict__ part, int rt0, int nrt, double* sum, int lane) {
+    constexpr int KS = S / 32, QS = S / 16;     // k tiles (and column chunks) of a source, column tiles of a target
+    const int tq = (I.m_dp + 15) >> 4;
+    const uint32_t at = (uint32_t)lane * 16u;
+    auto tile = [&](__amdgpu_buffer_rsrc_t op, int byte) { return ld_frag(op, at, (uint32_t)byte); };
+    auto a_op = [&](const TD& T) { return buf(pool_t + T.a, nrt * T.pa32 * 2048); };
+    auto x_op = [&](const TD& T) { return buf(xt + T.x, T.pd32 * T.pa32 * 4096); };
+    auto b_op = [&](const TD& T) { return buf(pool_t + T.b, tq * T.pd32 * 2048); };
+    Frag a[NR][KS], x[2 * KS], b[QS];
+    f32x4 c32[NR][QS];
+    auto load_a = [&](const TD& T) {
+        const __amdgpu_buffer_rsrc_t op = a_op(T);
+        each<NR>([&](auto p) {
+            each<KS>([&](auto kt) { a[p][kt] = tile(op, (kt < T.pa32 ? (rt0 + p) * T.pa32 + kt : nrt * T.pa32) * 2048); });
+        });
+    };
+    // X^T tile (half i % 2 of column chunk jc, k tile i / 2)
+    auto x_tile = [&](__amdgpu_buffer_rsrc_t op, const TD& T, int jc, int i) {
+        return tile(op, ((i >> 1) < T.pa32 ? (2 * jc + (i & 1)) * T.pa32 + (i >> 1) : 2 * T.pd32 * T.pa32) * 2048);
+    };
+    each<NR>([&](auto p) { each<QS>([&](auto q) { c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
 
+    int t = I.t_begin, jc = 0, since_flush = 0;
+    bool first = true;
+    TD T = load_td(tasks + t);
+    TD Tn = load_td(tasks + min(t + 1, I.t_end - 1));    // the following task, one ahead
+    load_a(T);
+    {
+        const __amdgpu_buffer_rsrc_t xo = x_op(T), bo = b_op(T);
+        each<2 * KS>([&](auto i) { x[i] = x_tile(xo, T, 0, i); });
+        each<QS>([&](auto q) { b[q] = tile(bo, q * T.pd32 * 2048); });
+    }
+    fence();
+    for (;;) {
+        const bool more_cols = jc + 1 < T.pd32;
+        const bool new_task = !more_cols && t + 1 < I.t_end;
+        // the next step (the last step's successor is its own task's first step: loaded, never used)
+        const int njc = more_cols ? jc + 1 : 0;
+        const TD N = new_task ? Tn : T;
+        const __amdgpu_buffer_rsrc_t nxo = x_op(N), nbo = b_op(N);
+        // the chains of the different accumulators alternate: an MFMA's result is not needed by the next
+        f32x4 tt[2][NR];
+        each<2>([&](auto h2) { each<NR>([&](auto p) { tt[h2][p] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
+        each<KS>([&](auto k) {
+            constexpr int kt = k;
+            if (kt < T.pa32) {
+                each<3>([&](auto w) {
+                    constexpr int W = w;
+                    each<2>([&](auto h) {
+                        constexpr int h2 = h;
+                        each<NR>([&](auto p) {
+                            tt[h2][p] = mma<W>(x[2 * kt + h2], a[p][kt], tt[h2][p]);
+                        });
+                    });
+                });
+            }
+            fence();
+            each<2>([&](auto h2) { x[2 * kt + h2] = x_tile(nxo, N, njc, 2 * kt + h2); });
+            fence();
+        });
+        // tt[h2][p][v] = T'[row 16 (rt0 + p) + li][col 32 jc + 8 g + 4 h2 + v] (unscaled); A is free now
+        if (new_task) {
+            fence();
+            load_a(Tn);
+            fence();
+        }
+        Frag tf[NR];
+        each<NR>([&](auto p) {
+            float v[8];
+            each<8>([&](auto i) {
+                constexpr int u = i;
+                v[u] = tt[u >> 2][p][u & 3];
+            });
+            tf[p] = split8(T.f, v);
+        });
+        each<QS / 2>([&](auto qq) {
+            auto gemm2 = [&](auto nq) {
+                each<3>([&](auto w) {
+                    constexpr int W = w;
+                    each<decltype(nq)::value>([&](auto i) {
+                        constexpr int q = 2 * decltype(qq)::value + i;
+                        each<NR>([&](auto p) {
+                            c32[p][q] = mma<W>(tf[p], b[q], c32[p][q]);
+                        });
+                    });
+                });
+            };
+            if (2 * qq + 1 < tq) gemm2(std::integral_constant<int, 2>{});
+            else if (2 * qq < tq) gemm2(std::integral_constant<int, 1>{});
+            fence();
+            each<2>([&](auto i) {
+                constexpr int q = 2 * decltype(qq)::value + i;
+                b[q] = tile(nbo, (q * N.pd32 + njc) * 2048);
+            });
+            fence();
+        });
+        if (!more_cols && (++since_flush == kFlush || !new_task)) {
+            since_flush = 0;
+            each<NR>([&](auto p) {
+                each<QS>([&](auto q) {
+                    each<4>([&](auto i) {
+                        constexpr int v = i;
+                        double* const at = sum + ((p * QS + q) * 4 + v) * 64 + lane;
+                        *at = (first ? 0.0 : *at) + (double)c32[p][q][v];
+                    });
+                    c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+                });
+            });
+            first = false;
+        }
+        if (!more_cols && !new_task) break;
+        jc = njc;
+        if (new_task) {
+            ++t;
+            T = Tn;
+            Tn = load_td(tasks + min(t + 1, I.t_end - 1));
+        }
+    }
+    // store: lane (li, g) holds Y[16 (rt0 + p) + 4 g + v][16 q + li]
+    const int li = lane & 15, g = lane >> 4, tn = 16 * tq;
+    each<NR>([&](auto p) {
+        each<QS>([&](auto q) {
+            if (q < tq) each<4>([&](auto v) {
+                const int row = 16 * (rt0 + p) + 4 * g + v, col = 16 * q + li;
+                const double s = sum[((p * QS + q) * 4 + v) * 64 + lane];
+                if (I.part_off < 0) {
+                    if (row < I.m_ap && col < I.m_dp) y[I.y_off + (int64_t)row * I.m_dp + col] += s;
+                } else {
+                    part[I.part_off + (int64_t)row * tn + col] = s;
+                }
+            });
+        });
+    });
+}
+
+// S: largest padded dimension of the class; NW wavefronts of two row tiles
+template <int S, int NW>
+__global__ __launch_bounds__(NW * 64, 2) void k_hpsi_rows(const Item* __restrict__ items, const LTask* __restrict__ tasks,
+                                                          const uint16_t* __restrict__ pool_t,
+                                                          const uint16_t* __restrict__ xtall, double* __restrict__ yall,
+                                                          double* __restrict__ partall, int64_t n_coeff, int64_t xt_size,
+                                                          int64_t slot_stride, const int32_t* __restrict__ mask) {
+    constexpr int kSums = 2 * (S / 16) * 4 * 64;
+    __shared__ double sums[NW * kSums];
+    if (mask && mask[items[blockIdx.x].part] != kPartActive) return;
     const ID I = load_item(items + blockIdx.x);
     const uint16_t* __restrict__ xt = xtall + (int64_t)blockIdx.y * xt_size;
     double* __restrict__ y = yall + (int64_t)blockIdx.y * n_coeff;
     double* __restrict__ part = partall + (int64_t)blockIdx.y * slot_stride;
     const int wave = uni(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int li = lane & 15, g = lane >> 4;
-    const int nrt = (I.m_ap + 15) >> 4;                 // row tiles of the target block
-    const int rt0 = (I.r0 >> 4) + wave * TP;            // this wave's first row tile
-    const int qt0 = I.c0 >> 4;
-    const int tq = min(QS, ((I.m_dp - I.c0) + 15) >> 4);
-    const bool active = rt0 < nrt;
-
-    if constexpr (PF == 1) {
-        if (wave == NW) {
-            const int rtw0 = I.r0 >> 4;
-            const int nrow = min(NW * TP, nrt - rtw0);            // row tiles of the workgroup
-            auto touch = [&](const TD P, bool with_x) {
-                const int nxl = with_x ? P.pd32 * P.pa32 * 32 : 0;                 // 128-byte lines
-                const int nbl = tq * P.pd32 * 16;
-                const int n = nxl + nbl + nrow * P.pa32 * 16;
-                const uint16_t* xb = xt + P.x;
-                const uint16_t* bb = pool_t + P.b + (int64_t)qt0 * P.pd32 * kTileU16;
-                const uint16_t* ab = pool_t + P.a + (int64_t)rtw0 * P.pa32 * kTileU16;
-                for (int l0 = 0; l0 < n; l0 += 64) {
-                    const int l = min(l0 + lane, n - 1);
-                    const uint16_t* src = l < nxl ? xb + (int64_t)l * 64
-                                        : l < nxl + nbl ? bb + (int64_t)(l - nxl) * 64
-                                                        : ab + (int64_t)(l - nxl - nbl) * 64;
-                    __builtin_amdgcn_global_load_lds((const void*)src, (lds_ptr_t)(lds + 2 * XS + 2 * BS), 4, 0, 0);
-                }
-            };
-            // one barrier before the loop and one per task, as the compute waves
-            int t = I.t_begin;
-            TD Pp = load_td(tasks + t);
-            if (t + 1 < I.t_end) {
-                const TD P1 = load_td(tasks + t + 1);
-                touch(P1, P1.x != Pp.x);
-                Pp = P1;
-            }
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            for (; t < I.t_end; ++t) {
-                if (t + 2 < I.t_end) {
-                    const TD P2 = load_td(tasks + t + 2);
-                    touch(P2, P2.x != Pp.x);
-                    Pp = P2;
-                }
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_s_barrier();
-            }
-            wait_vm();   // the touches land in LDS: all of them before the wave ends
-            return;
-        }
-    }
-
-    f32x4 c32[TP][QS];
-    double acc[TP][QS][4];
-#pragma unroll
-    for (int p = 0; p < TP; ++p)
-#pragma unroll
-        for (int q = 0; q < QS; ++q) {
-            c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int v = 0; v < 4; ++v) acc[p][q][v] = 0.0;
-        }
-
-    u16x8 ah[TP][KS], al[TP][KS];
-    // Branch-free: a fragment outside the block (k tile >= pa32, or a row tile past the target) is
-    // loaded from tile (0, 0) of the same block instead and never used for a stored result (the
-    // GEMMs skip k tiles >= pa32; rows past the target are not stored). A conditional load merged
-    // with a zero fragment would make the compiler wait for the load right away, which would
-    // serialize this prefetch of the next task with the current task's GEMMs.
-    auto load_a = [&](const TD T, u16x8 (&h)[TP][KS], u16x8 (&l)[TP][KS]) {
-#pragma unroll
-        for (int p = 0; p < TP; ++p)
-#pragma unroll
-            for (int kt = 0; kt < KS; ++kt) {
-                const bool in = kt < T.pa32 && rt0 + p < nrt;
-                const int64_t tile = in ? (int64_t)((rt0 + p) * T.pa32 + kt) : 0;
-                const uint16_t* src = pool_t + T.a + tile * kTileU16 + lane * 8;
-                h[p][kt] = gld8(src);
-                l[p][kt] = gld8(src + 512);
-            }
-    };
-    auto stage = [&](const TD T, int st, int xsl, bool load_x) {
-        if (load_x) copy_to_lds<NW>(xt + T.x, lds + xsl * XS, T.pd32 * T.pa32 * 256, wave, lane);
-        copy_to_lds<NW>(pool_t + T.b + (int64_t)qt0 * T.pd32 * kTileU16, lds + 2 * XS + st * BS, tq * T.pd32 * 128,
-                    wave, lane);
-    };
-
-    static_assert(CW == 0 || PF == 0, "the extra wavefront copies or prefetches, not both");
-    // per-task barrier: without a copy wavefront each wave waits for its own copies first; with one,
-    // the compute waves only read LDS (their reads are consumed before the barrier) and the copy
-    // wave waits for its copies
-    auto task_barrier = [&]() {
-        if constexpr (CW == 0) {
-            wait_vm();
-            __syncthreads();
-        } else {
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
-    };
-    int t = I.t_begin;
-    TD T = load_td(tasks + t);
-    int st = 0, xsl = 0;
-    int64_t xcur = T.x;
-    TD Tn = t + 1 < I.t_end ? load_td(tasks + t + 1) : T;   // descriptors are read one task ahead of use
-    if constexpr (CW == 1) {
-        if (wave == NW) {
-            auto stage1 = [&](const TD P, int st1, int xsl1, bool load_x) {
-                if (load_x) copy_to_lds<1>(xt + P.x, lds + xsl1 * XS, P.pd32 * P.pa32 * 256, 0, lane);
-                copy_to_lds<1>(pool_t + P.b + (int64_t)qt0 * P.pd32 * kTileU16, lds + 2 * XS + st1 * BS,
-                               tq * P.pd32 * 128, 0, lane);
-            };
-            stage1(T, 0, 0, true);
-            wait_vm();
-            task_barrier();
-            for (; t + 1 < I.t_end; ++t) {
-                const bool nx = Tn.x != xcur;
-                if (nx) xsl ^= 1;
-                stage1(Tn, st ^ 1, xsl, nx);          // that stage was last read before the previous barrier
-                wait_vm();
-                task_barrier();
-                st ^= 1;
-                xcur = Tn.x;
-                Tn = t + 2 < I.t_end ? load_td(tasks + t + 2) : Tn;
-            }
-            task_barrier();                           // the compute waves' barrier after their last task
-            return;
-        }
-    }
-    if constexpr (CW == 0) stage(T, 0, 0, true);
-    load_a(T, ah, al);
-    if constexpr (CW == 0) wait_vm();
-    task_barrier();
-    int since_flush = 0;
-    for (;;) {
-        const bool has_next = t + 1 < I.t_end;
-        const TD Tnn = t + 2 < I.t_end ? load_td(tasks + t + 2) : Tn;
-        int xsl_n = xsl;
-        u16x8 nh[TP][KS], nl[TP][KS];
-        if (has_next) {
-            const bool nx = Tn.x != xcur;
-            if (nx) xsl_n ^= 1;
-            if constexpr (CW == 0) stage(Tn, st ^ 1, xsl_n, nx);
-            load_a(Tn, nh, nl);
-        }
-        if (active) {
-            const uint16_t* xs = lds + xsl * XS;
-            const uint16_t* bs = lds + 2 * XS + st * BS;
-            const float f = T.f;
-            for (int jc = 0; jc < T.pd32; ++jc) {
-                f32x4 tt[2][TP];
-#pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-                    for (int p = 0; p < TP; ++p) tt[h2][p] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int kt = 0; kt < KS; ++kt) {
-                    if (kt < T.pa32) {
-#pragma unroll
-                        for (int h2 = 0; h2 < 2; ++h2) {
-                            const uint16_t* tl = xs + ((jc * 2 + h2) * T.pa32 + kt) * kTileU16 + lane * 8;
-                            const u16x8 xh = lds8(tl), xl = lds8(tl + 512);
-#pragma unroll
-                            for (int p = 0; p < TP; ++p) tt[h2][p] = mma3(xh, xl, ah[p][kt], al[p][kt], tt[h2][p]);
-                        }
-                    }
-                }
-                // tt[h2][p][v] = T'[row 16 (rt0 + p) + li][col 32 jc + 8 g + 4 h2 + v] (unscaled)
-                u16x8 th[TP], tlo[TP];
-#pragma unroll
-                for (int p = 0; p < TP; ++p) {
-                    float v[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = f * tt[u >> 2][p][u & 3];
-                    split8(v, th[p], tlo[p]);
-                }
-#pragma unroll
-                for (int q = 0; q < QS; ++q) {
-                    if (q < tq) {
-                        const uint16_t* tl = bs + (q * T.pd32 + jc) * kTileU16 + lane * 8;
-                        const u16x8 bh = lds8(tl), bl = lds8(tl + 512);
-#pragma unroll
-                        for (int p = 0; p < TP; ++p) c32[p][q] = mma3(th[p], tlo[p], bh, bl, c32[p][q]);
-                    }
-                }
-            }
-            if (++since_flush == kFlush || !has_next) {
-                since_flush = 0;
-#pragma unroll
-                for (int p = 0; p < TP; ++p)
-#pragma unroll
-                    for (int q = 0; q < QS; ++q) {
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) acc[p][q][v] += (double)c32[p][q][v];
-                        c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-                    }
-            }
-        }
-        task_barrier();
-        if (!has_next) break;
-        ++t;
-        T = Tn;
-        Tn = Tnn;
-        st ^= 1;
-        xsl = xsl_n;
-        xcur = T.x;
-#pragma unroll
-        for (int p = 0; p < TP; ++p)
-#pragma unroll
-            for (int kt = 0; kt < KS; ++kt) {
-                ah[p][kt] = nh[p][kt];
-                al[p][kt] = nl[p][kt];
-            }
-    }
-    if (!active) return;
-    // store: lane (li, g) holds Y[16 (rt0 + p) + 4 g + v][16 (qt0 + q) + li]
-    const int tn = 16 * tq;
-#pragma unroll
-    for (int p = 0; p < TP; ++p)
-#pragma unroll
-        for (int q = 0; q < QS; ++q) {
-            if (q >= tq || rt0 + p >= nrt) continue;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = 16 * (rt0 + p) + 4 * g + v, col = 16 * (qt0 + q) + li;
-                if (I.part_off < 0) {
-                    if (row < I.m_ap && col < I.m_dp) y[I.y_off + (int64_t)row * I.m_dp + col] += acc[p][q][v];
-                } else {
-                    part[I.part_off + (int64_t)(row - I.r0) * tn + (col - I.c0)] = acc[p][q][v];
-                }
-            }
-        }
+    const int nrt = (I.m_ap + 15) >> 4, rt0 = 2 * wave;
+    if (rt0 >= nrt) return;
+    if (rt0 + 1 < nrt) rows_item<S, 2>(I, tasks, pool_t, xt, y, part, rt0, nrt, sums + wave * kSums, lane);
+    else rows_item<S, 1>(I, tasks, pool_t, xt, y, part, rt0, nrt, sums + wave * kSums, lane);
 }
 
 // ------------------------------------------------------------------ task-mode kernel (small sources)
 // For tasks whose source block fits one 32 x 32 tile (pa32 = pd32 = 1). One wavefront owns a row
 // block of NR row tiles (every column, tq <= NQ column tiles) of a target and runs its tasks in
 // order with every operand fragment read straight from global memory (1 KB coalesced per wave
-// instruction); the fragments of task t+1 are loaded while task t computes, and many independent
-// wavefronts per CU hide the remaining latency. Results are accumulated in FP32 over kFlushT tasks
+// instruction); the fragments of tasks t+1 and t+2 are in flight while task t computes, and many
+// independent wavefronts per CU hide the remaining latency. Results are accumulated in FP32 over kFlushT tasks
 // and added into the FP64 output (y, or the item's partial tile) by read-modify-write: the item
 // is the only writer of those elements in its launch.
 constexpr int kFlushT = 32;
@@ -481,53 +325,32 @@ __global__ __launch_bounds__(64) void k_hpsi_small(const Item* __restrict__ item
     const int tq = min(NQ, ((I.m_dp - I.c0) + 15) >> 4);
     const int tn = 16 * tq;
 
-    // operand fragments of one task: A rows, X^T (two halves), B rows; hi and lo
-    u16x8 ah[NR], al[NR], xh[2], xl[2], bh[NQ], bl[NQ];
-    u16x8 nah[NR], nal[NR], nxh[2], nxl[2], nbh[NQ], nbl[NQ];
-    // Branch-free loads (a conditional load merged with a zero or kept fragment makes the compiler
-    // wait for it at once, serializing the prefetch of task t+1 with task t): row tiles past the
-    // target and column tiles past tq read the block's first tile instead and are never stored; the
-    // X^T fragments are re-read even when the source is unchanged (a cache hit).
-    auto load = [&](const TD T, u16x8 (&fah)[NR], u16x8 (&fal)[NR], u16x8 (&fxh)[2], u16x8 (&fxl)[2],
-                    u16x8 (&fbh)[NQ], u16x8 (&fbl)[NQ]) {
-#pragma unroll
-        for (int p = 0; p < NR; ++p) {
-            const uint16_t* src = pool_t + T.a + (int64_t)(p < nr ? rt0 + p : rt0) * kTileU16 + lane * 8;
-            fah[p] = gld8(src);
-            fal[p] = gld8(src + 512);
-        }
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) {
-            const uint16_t* src = xt + T.x + h2 * kTileU16 + lane * 8;
-            fxh[h2] = gld8(src);
-            fxl[h2] = gld8(src + 512);
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            const uint16_t* src = pool_t + T.b + (int64_t)(q < tq ? qt0 + q : qt0) * kTileU16 + lane * 8;
-            fbh[q] = gld8(src);
-            fbl[q] = gld8(src + 512);
-        }
+    // operand fragments of two tasks: A rows, X^T (two halves), B rows; row tiles past the target and column
+    // tiles past tq are outside the operand, so their loads move nothing
+    const uint32_t at = (uint32_t)lane * 16u;
+    const int a_bytes = ((I.m_ap + 15) >> 4) * 2048, b_bytes = ((I.m_dp + 15) >> 4) * 2048;
+    auto tile = [&](__amdgpu_buffer_rsrc_t op, int n) { return ld_frag(op, at, (uint32_t)n * 2048u); };
+    Frag a[2][NR], x[2][2], b[2][NQ];
+    auto load_ax = [&](const TD& T, Frag (&fa)[NR], Frag (&fx)[2]) {
+        const __amdgpu_buffer_rsrc_t ao = buf(pool_t + T.a, a_bytes), xo = buf(xt + T.x, 4096);
+        each<2>([&](auto h2) { fx[h2] = tile(xo, h2); });
+        each<NR>([&](auto p) { fa[p] = tile(ao, rt0 + p); });
     };
+    auto b_op = [&](const TD& T) { return buf(pool_t + T.b, b_bytes); };
 
     f32x4 c32[NR][NQ];
-#pragma unroll
-    for (int p = 0; p < NR; ++p)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    each<NR>([&](auto p) { each<NQ>([&](auto q) { c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
     bool first_flush = true;
-    auto flush = [&]() {
+    auto flush = [&]() __attribute__((always_inline)) {
         // addresses from an opaque copy of the lane id, so they are not hoisted into the main loop
         int ln = lane;
         asm volatile("" : "+v"(ln));
         const int fli = ln & 15, fg = ln >> 4;
-#pragma unroll
-        for (int p = 0; p < NR; ++p)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
+        each<NR>([&](auto p) {
+            each<NQ>([&](auto q) {
                 if (p < nr && q < tq) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
+                    each<4>([&](auto i) {
+                        constexpr int v = i;
                         const int row = 16 * (rt0 + p) + 4 * fg + v, col = 16 * (qt0 + q) + fli;
                         if (I.part_off < 0) {
                             if (row < I.m_ap && col < I.m_dp)
@@ -536,66 +359,86 @@ __global__ __launch_bounds__(64) void k_hpsi_small(const Item* __restrict__ item
                             double* d = part + I.part_off + (int64_t)(row - I.r0) * tn + (col - I.c0);
                             *d = first_flush ? (double)c32[p][q][v] : *d + (double)c32[p][q][v];
                         }
-                    }
+                    });
                     // keep the read-modify-writes of one tile together (bounded register use)
                     asm volatile("" ::: "memory");
                 }
                 c32[p][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-            }
+            });
+        });
         first_flush = false;
     };
 
     int t = I.t_begin;
-    TD T = load_td(tasks + t);
-    TD Tn = t + 1 < I.t_end ? load_td(tasks + t + 1) : T;
-    load(T, ah, al, xh, xl, bh, bl);
-    // nothing outstanding at the loop head: the first task's fragments are complete here, and each
-    // iteration's prefetch completes at its end (the copies into the current-task registers), so the
-    // compiler's wait analysis lets this task's GEMMs run while the next task's loads are in flight
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) expcnt(7) lgkmcnt(15)
+    const int last = I.t_end - 1;
+    float f[2];
+    each<2>([&](auto n) {
+        const TD T = load_td(tasks + min(t + n, last));
+        f[n] = T.f;
+        load_ax(T, a[n], x[n]);
+        const __amdgpu_buffer_rsrc_t bo = b_op(T);
+        each<NQ>([&](auto q) { b[n][q] = tile(bo, qt0 + q); });
+        fence();
+    });
+    TD N = load_td(tasks + min(t + 2, last));            // the task after next, one task ahead of its loads
     int since_flush = 0;
-    for (;;) {
-        const bool has_next = t + 1 < I.t_end;
-        const TD Tnn = t + 2 < I.t_end ? load_td(tasks + t + 2) : Tn;
-        if (has_next) load(Tn, nah, nal, nxh, nxl, nbh, nbl);
-        // GEMM1: T'^T (32 x 16 per row tile) = X^T A(rows)^T, one k step (K = 32)
-        f32x4 tt[2][NR];
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2)
-#pragma unroll
-            for (int p = 0; p < NR; ++p)
-                tt[h2][p] = mma3(xh[h2], xl[h2], ah[p], al[p], f32x4{0.f, 0.f, 0.f, 0.f});
-        u16x8 th[NR], tlo[NR];
-        const float f = T.f;
-#pragma unroll
-        for (int p = 0; p < NR; ++p) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = f * tt[u >> 2][p][u & 3];
-            split8(v, th[p], tlo[p]);
-        }
-        // GEMM2: Y += T' B^T
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            if (q < tq) {
-#pragma unroll
-                for (int p = 0; p < NR; ++p) c32[p][q] = mma3(th[p], tlo[p], bh[q], bl[q], c32[p][q]);
+    for (bool more = true; more;) {
+        each<2>([&](auto nn) {
+            constexpr int n = nn;
+            if (!more) return;
+            const bool ends = t == last;
+            // GEMM1: T'^T (32 x 16 per row tile) = X^T A(rows)^T, one k step (K = 32); the chains alternate
+            f32x4 tt[2][NR];
+            each<2>([&](auto h2) { each<NR>([&](auto p) { tt[h2][p] = f32x4{0.f, 0.f, 0.f, 0.f}; }); });
+            each<3>([&](auto w) {
+                constexpr int W = w;
+                each<2>([&](auto h) {
+                    constexpr int h2 = h;
+                    each<NR>([&](auto p) {
+                        tt[h2][p] = mma<W>(x[n][h2], a[n][p], tt[h2][p]);
+                    });
+                });
+            });
+            fence();
+            load_ax(N, a[n], x[n]);
+            fence();
+            Frag tf[NR];
+            each<NR>([&](auto p) {
+                float v[8];
+                each<8>([&](auto i) {
+                    constexpr int u = i;
+                    v[u] = tt[u >> 2][p][u & 3];
+                });
+                tf[p] = split8(f[n], v);
+            });
+            // GEMM2: Y += T' B^T
+            const __amdgpu_buffer_rsrc_t bo = b_op(N);
+            each<NQ / 2>([&](auto qq) {
+                each<3>([&](auto w) {
+                    constexpr int W = w;
+                    each<2>([&](auto i) {
+                        constexpr int q = 2 * decltype(qq)::value + i;
+                        if (q < tq) each<NR>([&](auto p) {
+                            c32[p][q] = mma<W>(tf[p], b[n][q], c32[p][q]);
+                        });
+                    });
+                });
+                fence();
+                each<2>([&](auto i) {
+                    constexpr int q = 2 * decltype(qq)::value + i;
+                    b[n][q] = tile(bo, qt0 + q);
+                });
+                fence();
+            });
+            f[n] = N.f;
+            N = load_td(tasks + min(t + 3, last));
+            if (++since_flush == kFlushT || ends) {
+                since_flush = 0;
+                flush();
             }
-        }
-        if (++since_flush == kFlushT || !has_next) {
-            since_flush = 0;
-            flush();
-        }
-        if (!has_next) break;
-        ++t;
-        T = Tn;
-        Tn = Tnn;
-#pragma unroll
-        for (int p = 0; p < NR; ++p) { ah[p] = nah[p]; al[p] = nal[p]; }
-#pragma unroll
-        for (int h2 = 0; h2 < 2; ++h2) { xh[h2] = nxh[h2]; xl[h2] = nxl[h2]; }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) { bh[q] = nbh[q]; bl[q] = nbl[q]; }
+            if (ends) more = false;
+            ++t;
+        });
     }
 }
 
@@ -655,62 +498,16 @@ hipError_t launch_hpsi_lds(const LdsPlan& P, const uint16_t* pool_t, const doubl
     for (int c = 0; c < kLdsClasses; ++c) {
         const int b = P.cls_begin[c], n = P.cls_begin[c + 1] - b;
         if (n <= 0) continue;
-        const dim3 grid(n, nvec), block(kLdsWaves * 64), block_pf(kLdsWaves * 64 + 64);
-        const bool cw = (P.copy_wave_mask >> c) & 1;     // a copy wavefront (replaces the prefetch one)
-        const bool pf = !cw && ((P.prefetch_mask >> c) & 1);
-        const bool w6 = (P.six_wave_mask >> c) & 1;      // (S, 2) classes as six one-row-tile wavefronts
-        const dim3 block6(6 * 64), block6_pf(7 * 64);
-        if (cw) {
-#define DMRG_LDS_CW(S_, TP_, NW_)                                                                          \
-    hipLaunchKernelGGL((k_hpsi_lds<S_, TP_, 0, NW_, 1>), grid, dim3((NW_ + 1) * 64), 0, s, P.items + b, P.tasks, \
-                       pool_t, P.xt, y, P.partial, n_coeff, P.xt_size, ss, active)
-            switch (c) {
-                case 0: DMRG_LDS_CW(64, 1, kLdsWaves); break;
-                case 1:
-                    if (w6) DMRG_LDS_CW(64, 1, 6);
-                    else DMRG_LDS_CW(64, 2, kLdsWaves);
-                    break;
-                case 2: DMRG_LDS_CW(96, 1, kLdsWaves); break;
-                default:
-                    if (w6) DMRG_LDS_CW(96, 1, 6);
-                    else DMRG_LDS_CW(96, 2, kLdsWaves);
-                    break;
-            }
-#undef DMRG_LDS_CW
-            continue;
-        }
+        const dim3 grid(n, nvec);
+#define DMRG_ROWS(S, NW) hipLaunchKernelGGL((k_hpsi_rows<S, NW>), grid, dim3(NW * 64), 0, s, P.items + b, P.tasks, pool_t, \
+                                            P.xt, y, P.partial, n_coeff, P.xt_size, ss, active)
         switch (c) {
-            case 0:
-                if (pf) hipLaunchKernelGGL((k_hpsi_lds<64, 1, 1>), grid, block_pf, 0, s, P.items + b, P.tasks, pool_t,
-                                           P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else hipLaunchKernelGGL((k_hpsi_lds<64, 1, 0>), grid, block, 0, s, P.items + b, P.tasks, pool_t, P.xt,
-                                        y, P.partial, n_coeff, P.xt_size, ss, active);
-                break;
-            case 1:
-                if (w6) hipLaunchKernelGGL((k_hpsi_lds<64, 1, 0, 6>), grid, block6, 0, s, P.items + b, P.tasks, pool_t,
-                                           P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else if (pf) hipLaunchKernelGGL((k_hpsi_lds<64, 2, 1>), grid, block_pf, 0, s, P.items + b, P.tasks,
-                                                pool_t, P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else hipLaunchKernelGGL((k_hpsi_lds<64, 2, 0>), grid, block, 0, s, P.items + b, P.tasks, pool_t, P.xt,
-                                        y, P.partial, n_coeff, P.xt_size, ss, active);
-                break;
-            case 2:
-                if (pf) hipLaunchKernelGGL((k_hpsi_lds<96, 1, 1>), grid, block_pf, 0, s, P.items + b, P.tasks, pool_t,
-                                           P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else hipLaunchKernelGGL((k_hpsi_lds<96, 1, 0>), grid, block, 0, s, P.items + b, P.tasks, pool_t, P.xt,
-                                        y, P.partial, n_coeff, P.xt_size, ss, active);
-                break;
-            default:   // with prefetch: 3 compute wavefronts (targets of at most 96 rows) + the prefetch one
-                if (w6 && pf) hipLaunchKernelGGL((k_hpsi_lds<96, 1, 1, 6>), grid, block6_pf, 0, s, P.items + b,
-                                                 P.tasks, pool_t, P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else if (w6) hipLaunchKernelGGL((k_hpsi_lds<96, 1, 0, 6>), grid, block6, 0, s, P.items + b, P.tasks,
-                                                pool_t, P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else if (pf) hipLaunchKernelGGL((k_hpsi_lds<96, 2, 1, 3>), grid, block, 0, s, P.items + b, P.tasks,
-                                                pool_t, P.xt, y, P.partial, n_coeff, P.xt_size, ss, active);
-                else hipLaunchKernelGGL((k_hpsi_lds<96, 2, 0>), grid, block, 0, s, P.items + b, P.tasks, pool_t, P.xt,
-                                        y, P.partial, n_coeff, P.xt_size, ss, active);
-                break;
+            case 0: DMRG_ROWS(64, 2); break;
+            case 1: DMRG_ROWS(64, 3); break;
+            case 2: DMRG_ROWS(96, 2); break;
+            default: DMRG_ROWS(96, 3); break;
         }
+#undef DMRG_ROWS
     }
     for (int c = 0; c < kSmallClasses; ++c) {
         const int b = P.small_begin[c], n = P.small_begin[c + 1] - b;

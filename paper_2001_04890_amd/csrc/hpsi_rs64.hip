@@ -17,41 +17,20 @@
 // and memory bound large sectors, latency (hidden by 8 .. 16 wavefronts per CU) and launches the small. One
 // matvec of 24 orbitals at bond dimension 1024 takes 5.3 ms (3.6 ms of MFMAs; 6.5 ms with pointer loads and
 // the accumulators copied around conditional MFMAs), of 17 orbitals at 333 states 278 us (336 us).
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include <type_traits>
-#include <utility>
-
+#include "device.h"
 #include "internal.h"
 
 namespace dmrg {
 
 namespace {
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef double f64x2 __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ int64_t uni64(int64_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)((uint64_t)v >> 32));
-    return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double unid(double v) {
-    return __builtin_bit_cast(double, uni64(__builtin_bit_cast(int64_t, v)));
-}
-
-typedef int i32x2 __attribute__((ext_vector_type(2)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-// 16 bytes per lane at byte `at` (wave-uniform) + lane_bytes of an operand; zero past its end.
+// 16 bytes per lane at byte `at` (wave-uniform) + lane_bytes of an operand; zero past its end
 __device__ __forceinline__ f64x2 ld2(__amdgpu_buffer_rsrc_t op, uint32_t lane_bytes, uint32_t at) {
-    return __builtin_bit_cast(f64x2, (i32x4)__builtin_amdgcn_raw_buffer_load_b128(op, (int)lane_bytes, (int)at, 0));
+    return __builtin_bit_cast(f64x2, ld16(op, lane_bytes, at));
 }
 // An operand of r4 4-row groups and k4 k steps in the compact form.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand(const double* p, int r4, int k4) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(p), (short)0, ((k4 + 1) >> 1) * r4 * 256, 0x00027000);
+    return buf(p, ((k4 + 1) >> 1) * r4 * 256);
 }
 
 // Task descriptor in scalar registers.
@@ -66,21 +45,6 @@ __device__ __forceinline__ TD load_td(const LTask64* __restrict__ p) {
     d.kd4 = uni(p->kd4);
     return d;
 }
-
-// f(integral_constant<int, 0>), f(integral_constant<int, 1>), ..: a loop whose indices are constants before
-// any optimisation. As an unrolled loop, the accumulators' array becomes one vector register of 16 .. 64
-// dwords first, and every conditional MFMA copies all of it.
-template <class F, int... I>
-__device__ __forceinline__ void each_of(F&& f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, class F>
-__device__ __forceinline__ void each(F&& f) {
-    each_of(f, std::make_integer_sequence<int, N>{});
-}
-
-// keeps the loads before it from sinking to their uses and those after it from rising
-__device__ __forceinline__ void fence() { asm volatile("" ::: "memory"); }
 
 // KP: column groups (two k steps each) of the A row tile; QT: column tiles of the target; JP: column
 // groups of a source column tile that are read (1: every source has at most 8 columns).
@@ -191,8 +155,7 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
         });
     } else {
         // the loads of four column tiles are in flight at once; what lies outside the block is neither read nor written
-        const __amdgpu_buffer_rsrc_t op = __builtin_amdgcn_make_buffer_rsrc(
-            y + y_off + (int64_t)rt * 16 * m_dp, (short)0, min(16, m_ap - 16 * rt) * m_dp * 8, 0x00027000);
+        const __amdgpu_buffer_rsrc_t op = buf(y + y_off + (int64_t)rt * 16 * m_dp, min(16, m_ap - 16 * rt) * m_dp * 8);
         auto at = [&](int q, int v) { return (int)(16 * q + li < (uint32_t)m_dp ? ((g + 4 * v) * m_dp + 16 * q + li) * 8u : ~0u); };
         each<(QT + 3) / 4>([&](auto h) {
             constexpr int q0 = 4 * h, nq = QT - q0 < 4 ? QT - q0 : 4;

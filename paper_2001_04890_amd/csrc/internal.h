@@ -62,7 +62,7 @@ struct Reduce {
 constexpr int32_t kPartActive = 1;
 
 // ---------------------------------------------------------------- tiled split-BF16 operands
-// Split-BF16 operands of the LDS-staged sector-GEMM kernel are stored pre-tiled in MFMA fragment
+// Split-BF16 operands of the sector-GEMM kernels are stored pre-tiled in MFMA fragment
 // order: a matrix with R rows (padded to 16) and K columns (padded to 32) is cut into 16 x 32 tiles,
 // tile (rt, kt) at ((rt * K/32) + kt) * kTileU16 elements, row-major over tiles. Inside a tile the
 // 64 lanes' 8-element fragments are contiguous (hi: lane * 8 + u, lo: 512 + lane * 8 + u) with lane
@@ -72,7 +72,7 @@ constexpr int32_t kPartActive = 1;
 constexpr int kTileU16 = 1024;
 struct PoolBlock { int64_t off; int32_t r16, k32, rows, cols; };   // rows, cols: before padding
 
-// Task of the LDS-staged split kernel: Y_tile += f * A . X . B^T with every factor present (identity
+// Task of the split row-mode and task-mode kernels: Y_tile += f * A . X . B^T with every factor present (identity
 // factors point at tiled identity blocks). Offsets are u16 offsets into the tiled arrays.
 struct LTask {
     int64_t x_off;   // tiled X^T of the source block (see k_pack_xt)
@@ -146,16 +146,16 @@ struct HpsiPlan {
     uint16_t* xt_lo;
 };
 
-// Launch plan of the LDS-staged split kernel (hpsi_lds.hip). Items (internal.h Item) cover whole
-// target row blocks; launch class = (S, TP): S = largest padded dimension (32, 64 or 96) sizing the
-// LDS stages, TP = row tiles per wave; each class is one launch of kLdsWaves-wave workgroups.
+// Launch plan of the split row-mode and task-mode kernels (hpsi_lds.hip). Row-mode items (internal.h Item)
+// cover whole targets; class (S, NW): S = largest padded dimension (64 or 96), NW = wavefronts of two row
+// tiles each; each class is one launch.
 // Tasks whose source is a single 32 x 32 tile run in the task-mode kernel (one wavefront per target
 // block of NR row tiles and at most NQ column tiles), classes (NR, NQ) = (1,2) (2,2) (1,4), launched
 // after the row-mode classes; items[small_begin[c] .. small_begin[c+1]).
-// Row-mode classes (S, TP) = (64,1) (64,2) (96,1) (96,2): a target's tasks whose source and target
-// fit 64-wide stages run in the S = 64 classes (64 KB of LDS, several workgroups per CU), the other
-// big-source tasks in the S = 96 classes.
-constexpr int kLdsWaves = 4;
+// Row-mode classes (64,2) (64,3) (96,2) (96,3): a target's tasks whose source and columns are within 64
+// run in the S = 64 classes (fewer registers, three wavefronts per SIMD), the other big-source tasks in the
+// S = 96 classes; targets of up to kLdsRows row tiles have two wavefronts, the others three.
+constexpr int kLdsRows = 4;
 constexpr int kLdsClasses = 4;
 constexpr int kSmallClasses = 3;
 constexpr int kReduceKinds = 3;         // partial tiles of S = 64 runs, S = 96 runs, task-mode runs
@@ -174,16 +174,6 @@ struct LdsPlan {
     int n_packs = 0;
     int64_t xt_size = 0;                // u16 elements of one tiled X^T vector (2 * packed_size)
     uint16_t* xt = nullptr;             // device, xt_size * kPartialVecs
-    int prefetch_mask = 0x4;            // row-mode classes (bit c) whose workgroups get a cache-line
-                                        // prefetch wavefront: (96,1) (one workgroup per CU anyway);
-                                        // the S = 64 classes would lose their second workgroup per
-                                        // CU (measured slower); (96,2) runs 3 compute wavefronts then
-    int copy_wave_mask = 0;             // row-mode classes (bit c) with a copy wavefront that issues every
-                                        // LDS copy (no prefetch wavefront then)
-    int six_wave_mask = 0x8;            // (S, 2) classes (bits 1, 3) run as six wavefronts of one row
-                                        // tile each (targets of 65..96 rows) instead of four of two:
-                                        // (96,2), whose one workgroup per CU then has two wavefronts on
-                                        // two of the SIMDs (measured faster; (64,2) is not)
 };
 
 // ---------------------------------------------------------------- FP64 operands of the MFMA kernels
@@ -249,49 +239,36 @@ hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x
 hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, const double* partial, double* y,
                                   hipStream_t s, const int32_t* active = nullptr);
 
-// ---------------------------------------------------------------- large blocks (hpsi_big.hip)
-// Targets whose blocks (or sources) exceed the 96-wide LDS stages take two passes per chunk of
-// targets: pass 1 writes T = f A X of every task into a tiled hi/lo buffer (tile (rt, jc) of the
-// task's T at t_off + (rt * pd32 + jc) * kTileU16, in the A-operand fragment layout of pass 2),
-// pass 2 accumulates Y += sum_tasks T B^T per 128 x 128 output tile.
-struct BigT1 {             // pass-1 group: one task, rows [16 rb, 16 rb + 128), T^T rows [32 jb, 32 jb + 128)
-    int64_t xt, a, t;      // tiled X^T of the source, tiled A, output T (u16 offsets)
-    double f;
-    int16_t pa32, pd32;    // source rows / cols in 32-element k tiles
-    int16_t nrt;           // row tiles of the target block
-    int16_t rb, jb;        // first row tile, first 32-column chunk
-    int16_t part;          // merged problem of the target (masks use part < 32768)
-    int16_t ka, kd;        // source rows / cols holding data, in k tiles
-};
-// FP64 form (hpsi_big64.hip): offsets in doubles, A, B and X^T in the FP64 operand form, T in whole 16 x 16
-// tiles of it (tile (rt, jt) at t + (rt * pd + jt) * 256). One wavefront's part of a task's T; ka4 = 0: none.
-struct Big64T {
+// Two-pass large-block path, split (hpsi_big.hip) or FP64 (hpsi_big64.hip). Targets are grouped into chunks;
+// per chunk, pass 1 writes T = f A X of every task into a buffer of tiles in the A-operand layout of pass 2
+// (tile (rt, jt) of a task's T is its tile rt * pd + jt), pass 2 accumulates Y += sum_tasks T B^T.
+// Split form: offsets in u16, T in tiles of 16 x 32 (hi and lo, kTileU16). FP64 form: offsets in doubles, A, B
+// and X^T in the FP64 operand form, T in tiles of 16 x 16 (256 doubles).
+struct BigT {              // one wavefront's part of a task's T; ka = 0: none
     int64_t xt, a, t;
     double f;
-    int32_t ka4, kd4, ra4; // source rows / columns and target rows in 4-wide groups
+    int32_t ka;            // source rows: in 32-wide k tiles (split), in 4-wide k steps (FP64)
+    int32_t kd, ra;        // FP64 form: source columns and target rows in 4-wide groups
     int32_t pd;            // T tiles along the source columns
-    int16_t rb, nr, jb, nj;   // row tiles [rb, rb + nr) and T column tiles [jb, jb + nj), at most 4 each
+    int16_t rb, nr, jb, nj;   // row tiles [rb, rb + nr) and T tile columns [jb, jb + nj)
     int32_t part;          // merged problem of the target
     int32_t pad;
 };
-// n tiles are cut into ceil(n / 4) parts, the longer ones first: length of the one that starts at tile t
-constexpr int big64_len(int n, int t) {
-    const int parts = (n + 3) / 4, len = n / parts, more = n % parts;
+// n tiles are cut into equal parts of at most `most`, the longer ones first: length of the one at tile t
+constexpr int part_len(int n, int t, int most) {
+    const int parts = (n + most - 1) / most, len = n / parts, more = n % parts;
     return t < more * (len + 1) ? len + 1 : len;
 }
 struct BigT2 {             // pass-2 task: T of the task and its B block
     int64_t t, b;
     int32_t pd32;
-    int32_t kd;            // T tiles holding data along k (FP64 form: 4-wide k steps holding data)
+    int32_t kd;            // FP64 form: 4-wide k steps holding data
 };
-// Chunk c: pass-1 workgroups [t1_begin, t1_end) (workgroup w runs groups t1_ranges[w] ..
-// t1_ranges[w + 1] - 1), pass-2 items [item_begin, item_end), reductions [red_begin, red_end).
+// Chunk c: pass-1 work [t1_begin, t1_end), pass-2 items [item_begin, item_end) (one wavefront each),
+// reductions [red_begin, red_end).
 struct BigChunk { int t1_begin, t1_end, item_begin, item_end, red_begin, red_end; };
-// FP64 form: pass-1 work [t1_begin, t1_end) of w1, one wavefront each.
-struct BigPlan {                    // split or FP64 form
-    const BigT1* t1 = nullptr;      // device, split form
-    const Big64T* w1 = nullptr;     // device, FP64 form
-    const int32_t* t1_ranges = nullptr;   // device, one entry per pass-1 workgroup plus one
+struct BigPlan {
+    const BigT* t1 = nullptr;       // device
     const BigT2* t2 = nullptr;      // device
     const Item* items = nullptr;    // device: pass-2 items (r0 = 16 rb, c0 = 16 qb, task range in t2)
     const Reduce* reduces = nullptr;

@@ -1,6 +1,6 @@
 // Launch planning of the two-site H.psi (Eq. dgemm, Section 2.2.1): the owner-computes task list of
 // a handle cut into balanced work items for each kernel path -- FP64 one-wavefront tiles, the FP64
-// register-streamed kernel, the split LDS-staged row-mode and task-mode kernels, the two-pass large-block
+// register-streamed kernel, the split row-mode and task-mode kernels, the two-pass large-block
 // path in both precisions -- with ordered reductions of the partial tiles of cut items (no atomics),
 // part tags for the part masks of merged handles, and the tiled operator copies these kernels read.
 #include <algorithm>
@@ -327,7 +327,7 @@ void build_plan_core(dmrg_hop& H, hipStream_t s, const std::vector<char>* only, 
 
 // Launch plan of the split kernels of hpsi_lds.hip. The tasks of every target block whose own and
 // sources' padded dimensions are at most 96 are divided into small tasks (source one 32 x 32 tile)
-// for the task-mode kernel and the others for the LDS-staged row-mode kernel; both lists keep the
+// for the task-mode kernel and the others for the row-mode kernel; both lists keep the
 // source order. Row-mode items cover the whole target (all rows and columns), task-mode items a row
 // block of one or two row tiles; each list is cut into items of bounded cost, and a target row block
 // covered by several items of one kind gets partial tiles that a reduction adds in item order.
@@ -412,8 +412,8 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
         }
         (void)big_s;
         if (!big.empty()) {
-            // tasks that fit 64-wide stages (source and target columns <= 64) -> S = 64 run, rest -> S = 96
-            const int tp = nrt > dmrg::kLdsWaves ? 2 : 1;
+            // source and target columns within 64 -> S = 64 run, rest -> S = 96
+            const int tp = nrt > dmrg::kLdsRows ? 2 : 1;
             std::vector<dmrg::LTask> b64, b96;
             for (const auto& L : big)
                 (L.pa32 <= 2 && L.pd32 <= 2 && tq <= 4 && H.tune_lds_split64 ? b64 : b96).push_back(L);
@@ -453,7 +453,7 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
     std::vector<dmrg::Reduce> reds_k[dmrg::kReduceKinds];
     int64_t part = 0;
     for (const Run& R : runs) {
-        const int tp = R.kind < 2 && R.nr > dmrg::kLdsWaves ? 2 : 1;
+        const int tp = R.kind < 2 && R.nr > dmrg::kLdsRows ? 2 : 1;
         std::vector<std::pair<int32_t, int32_t>> chunks;
         std::vector<double> ccost;
         int32_t b = R.tb;
@@ -592,9 +592,6 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
     H.lplan.n_packs = (int)packs.size();
     H.lplan.xt_size = 2 * psize;
     H.lplan.xt = plan_alloc<uint16_t>(H, (size_t)2 * psize * H.vec_step);
-    H.lplan.prefetch_mask = H.tune_lds_pf;
-    H.lplan.six_wave_mask = H.tune_lds_w6;
-    H.lplan.copy_wave_mask = H.tune_lds_cw;
     if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
         if (e[0] == '1') {
             std::fprintf(stderr, "[dmrg lds plan] items %zu row classes", items.size());
@@ -630,184 +627,10 @@ struct XcdDeal {
     }
 };
 
-// f(first tile, tiles) of the parts that n tiles are cut into
+// f(first tile, tiles) of the parts of at most `most` tiles that n tiles are cut into
 template <class F>
-void for_parts(int n, F&& f) {
-    for (int t = 0; t < n; t += dmrg::big64_len(n, t)) f(t, dmrg::big64_len(n, t));
-}
-
-// Launch plan of the split two-pass large-block path (hpsi_big.hip: 16 x 32 hi/lo tiles, u16 offsets) for
-// the targets flagged in `big`. Targets are grouped into chunks whose T buffers (one per task: target rows x source
-// columns, tiled) stay below the T budget; per chunk, pass 1 has one group per (task, 8 row tiles,
-// 128 T columns), consecutive groups packed into workgroups of about tune_big_stages1 k steps, and
-// pass 2 one item per (target, 8 row tiles, 8 column tiles, task range), the task lists cut into
-// items of about tune_big_stages k steps whose partial tiles a reduction adds in order.
-void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big,
-                    const std::vector<char>* task_keep) {
-    auto kept = [&](size_t k) { return !task_keep || (*task_keep)[k]; };
-    const int unit = 32;                             // k-tile width
-    const int64_t tile_el = dmrg::kTileU16;
-    const int64_t kBigTBudget = (int64_t)H.tune_big_tbudget_mb << 19;   // T elements per chunk
-    dmrg::BigPlan& plan = H.bplan;
-    std::vector<dmrg::BigChunk>& chunks = H.big_chunks;
-    plan = dmrg::BigPlan{};
-    chunks.clear();
-    const size_t nb = H.blk.size();
-    std::vector<int64_t> pk_off(nb);
-    int64_t ps = 0;
-    for (size_t i = 0; i < nb; ++i) { pk_off[i] = ps; ps += (int64_t)dmrg::ld_of(H.blk_ma[i]) * dmrg::ld_of(H.blk_md[i]); }
-    // operand offsets of a task (identity factors: identity blocks)
-    auto left_of = [&](const dmrg_hop::HTask& t) {
-        const int k = dmrg::ld_of(H.blk_ma[t.i]) / 32 - 1;
-        return t.lm >= 0 ? 2 * H.mats[t.lm].pool_of_in[H.blk[t.i][0]] : k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
-    };
-    auto right_of = [&](const dmrg_hop::HTask& t) {
-        const int k = dmrg::ld_of(H.blk_md[t.i]) / 32 - 1;
-        return t.rm >= 0 ? 2 * H.mats[t.rm].pool_of_in[H.blk[t.i][3]] : k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
-    };
-    std::vector<dmrg::BigT1> t1;
-    std::vector<dmrg::BigT2> t2;
-    std::vector<dmrg::Item> items;
-    std::vector<dmrg::Reduce> reds;
-    int64_t part_max = 0, tbuf_max = 0;
-    int red_max = 1;
-    // per target: its task range in H.tasks
-    std::vector<std::pair<size_t, size_t>> trange(nb, {0, 0});
-    for (size_t k = 0; k < H.tasks.size();) {
-        size_t e = k;
-        while (e < H.tasks.size() && H.tasks[e].j == H.tasks[k].j) ++e;
-        trange[H.tasks[k].j] = {k, e};
-        k = e;
-    }
-    dmrg::BigChunk cur{0, 0, 0, 0, 0, 0};
-    int64_t tsize = 0, part = 0;
-    std::vector<int32_t> t1_ranges;
-    int32_t g_first = 0;
-    std::vector<int> chunk_targets;
-    auto close_chunk = [&]() {
-        if (chunk_targets.empty()) return;
-        // pass-1 workgroups: consecutive groups of the chunk with about tune_big_stages1 k steps each
-        cur.t1_begin = (int)t1_ranges.size();
-        {
-            int c = 0;
-            t1_ranges.push_back(g_first);
-            for (int32_t gidx = g_first; gidx < (int32_t)t1.size(); ++gidx) {
-                // a workgroup's groups belong to one merged problem (part masks skip whole workgroups)
-                if (c >= H.tune_big_stages1 || (gidx > g_first && t1[gidx].part != t1[gidx - 1].part)) {
-                    t1_ranges.push_back(gidx);
-                    c = 0;
-                }
-                c += t1[gidx].pa32;
-            }
-            cur.t1_end = (int)t1_ranges.size();   // workgroups [t1_begin, t1_end); ranges has one more entry
-            t1_ranges.push_back((int32_t)t1.size());
-        }
-        g_first = (int32_t)t1.size();
-        cur.item_begin = (int)items.size();
-        cur.red_begin = (int)reds.size();
-        part = 0;
-        for (int j : chunk_targets) {
-            const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16, nq = dmrg::rows_of(H.blk_md[j]) / 16;
-            const int32_t b0 = H.big_t2_range[j].first, b1 = H.big_t2_range[j].second;
-            for (int rb = 0; rb < nrt; rb += 8)
-                for (int qb = 0; qb < nq; qb += 8) {
-                    const int tn = 16 * std::min(8, nq - qb);
-                    std::vector<std::pair<int32_t, int32_t>> cuts;
-                    int32_t b = b0;
-                    int c = 0;
-                    for (int32_t t = b0; t < b1; ++t) {
-                        if (c >= H.tune_big_stages && t > b) { cuts.push_back({b, t}); b = t; c = 0; }
-                        c += t2[t].pd32;
-                    }
-                    cuts.push_back({b, b1});
-                    if (cuts.size() == 1) {
-                        items.push_back({H.blk_off[j], -1, H.blk_ma[j], H.blk_md[j], 16 * rb, 16 * qb, cuts[0].first,
-                                         cuts[0].second});
-                    } else {
-                        reds.push_back({H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 16 * rb, 16 * qb, 128, tn,
-                                        (int32_t)cuts.size(), 0});
-                        red_max = std::max(red_max, 128 * tn);
-                        for (auto& cp : cuts) {
-                            items.push_back({H.blk_off[j], part, H.blk_ma[j], H.blk_md[j], 16 * rb, 16 * qb, cp.first,
-                                             cp.second});
-                            part += (int64_t)128 * tn;
-                        }
-                    }
-                }
-        }
-        cur.item_end = (int)items.size();
-        cur.red_end = (int)reds.size();
-        part_max = std::max(part_max, part);
-        tbuf_max = std::max(tbuf_max, tsize);
-        chunks.push_back(cur);
-        cur = dmrg::BigChunk{0, 0, 0, 0, 0, 0};
-        chunk_targets.clear();
-        tsize = 0;
-    };
-    H.big_t2_range.assign(nb, {0, 0});
-    for (size_t j = 0; j < nb; ++j) {
-        if (!big[j]) continue;
-        const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16;
-        int64_t need = 0;
-        for (size_t k = trange[j].first; k < trange[j].second; ++k)
-            if (kept(k)) need += (int64_t)nrt * dmrg::ld_of(H.blk_md[H.tasks[k].i]) / unit * tile_el;
-        if (need == 0) continue;                  // every task of the target runs elsewhere
-        if (tsize > 0 && tsize + need > kBigTBudget) close_chunk();
-        const int32_t b0 = (int32_t)t2.size();
-        const size_t g_t1 = t1.size();
-        const int32_t part_j = H.n_parts > 1 ? part_of(H, H.blk_off[j]) : 0;
-        for (size_t k = trange[j].first; k < trange[j].second; ++k) {
-            if (!kept(k)) continue;
-            const auto& ht = H.tasks[k];
-            const int64_t a_off = left_of(ht), b_off = right_of(ht);
-            if (a_off < 0 || b_off < 0) throw Error(DMRG_ERR_ARG, "internal: no tiled operand block");
-            const int64_t t_off = tsize;
-            const int pd = dmrg::ld_of(H.blk_md[ht.i]) / unit;
-            tsize += (int64_t)nrt * pd * tile_el;
-            const int ka = (H.blk_ma[ht.i] + unit - 1) / unit, kd = (H.blk_md[ht.i] + unit - 1) / unit;
-            const int pa = dmrg::ld_of(H.blk_ma[ht.i]) / unit;
-            for (int rb = 0; rb < nrt; rb += 8)
-                for (int jb = 0; jb < kd; jb += 128 / unit)
-                    t1.push_back({2 * pk_off[ht.i], a_off, t_off, ht.f, (int16_t)pa, (int16_t)pd, (int16_t)nrt, (int16_t)rb,
-                                  (int16_t)jb, 0, (int16_t)ka, (int16_t)kd});
-            t2.push_back({t_off, b_off, pd, kd});
-        }
-        H.big_t2_range[j] = {b0, (int32_t)t2.size()};
-        for (size_t g = g_t1; g < t1.size(); ++g) t1[g].part = (int16_t)part_j;
-        chunk_targets.push_back((int)j);
-    }
-    close_chunk();
-    if (t1.empty()) return;
-    dmrg::BigT1* d_t1 = plan_alloc<dmrg::BigT1>(H, t1.size());
-    int32_t* d_t1r = plan_alloc<int32_t>(H, t1_ranges.size());
-    HIPCHK(hipMemcpyAsync(d_t1r, t1_ranges.data(), t1_ranges.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    plan.t1_ranges = d_t1r;
-    dmrg::BigT2* d_t2 = plan_alloc<dmrg::BigT2>(H, t2.size());
-    tag_parts(H, items);
-    tag_parts(H, reds);
-    dmrg::Item* d_items = plan_alloc<dmrg::Item>(H, items.size());
-    dmrg::Reduce* d_red = plan_alloc<dmrg::Reduce>(H, reds.size());
-    HIPCHK(hipMemcpyAsync(d_t1, t1.data(), t1.size() * sizeof(t1[0]), hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(d_t2, t2.data(), t2.size() * sizeof(t2[0]), hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(d_items, items.data(), items.size() * sizeof(items[0]), hipMemcpyHostToDevice, s));
-    if (!reds.empty()) HIPCHK(hipMemcpyAsync(d_red, reds.data(), reds.size() * sizeof(reds[0]), hipMemcpyHostToDevice, s));
-    plan.t1 = d_t1;
-    plan.t2 = d_t2;
-    plan.items = d_items;
-    plan.reduces = d_red;
-    plan.chunks = chunks.data();
-    plan.n_chunks = (int)chunks.size();
-    plan.red_chunks = (red_max + 255) / 256;
-    const size_t tbytes = (size_t)std::max<int64_t>(tbuf_max, 1) * sizeof(uint16_t);
-    plan.tbuf = plan_alloc<uint16_t>(H, tbytes / sizeof(uint16_t));
-    plan.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part_max, 1));
-    plan.partial_size = part_max;
-    if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
-        if (e[0] == '1')
-            std::fprintf(stderr, "[dmrg big plan] chunks %zu pass-1 groups %zu pass-2 items %zu reduces %zu T %.1f MB "
-                         "partial %.1f MB\n", chunks.size(), t1.size(), items.size(), reds.size(),
-                         tbytes * 1e-6, part_max * 8e-6);
-    HIPCHK(hipStreamSynchronize(s));
+void for_parts(int n, int most, F&& f) {
+    for (int t = 0; t < n; t += dmrg::part_len(n, t, most)) f(t, dmrg::part_len(n, t, most));
 }
 
 }  // namespace
@@ -822,8 +645,8 @@ void drop_graphs(dmrg_hop& H) {
 
 namespace {
 
-// Targets whose own or some source's dimension exceeds `limit` (the 96-wide LDS stages of the split
-// kernel; 128 for the FP64 register-streamed kernel).
+// Targets whose own or some source's dimension exceeds `limit` (96 for the split row-mode kernel,
+// 128 for the FP64 register-streamed kernel).
 std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
     std::vector<int> smax(H.blk.size(), 0);
     for (size_t j = 0; j < H.blk.size(); ++j) smax[j] = std::max(H.blk_ma[j], H.blk_md[j]);
@@ -833,25 +656,44 @@ std::vector<char> large_targets(const dmrg_hop& H, int limit = 96) {
     return big;
 }
 
-// Launch plan of the FP64 two-pass path (hpsi_big64.hip) for the targets flagged in `big`, without the tasks
-// that run elsewhere. Targets are grouped into chunks whose T buffers (one per task: target rows x source
-// columns, in 16 x 16 tiles) stay below the T budget. A wavefront owns up to 4 x 4 tiles: both extents are
-// cut into equal parts of at most four tiles, so that the parts of one block differ by a tile at most. Per
+// Launch plan of the two-pass path, split (hpsi_big.hip) or FP64 (hpsi_big64.hip), for the targets flagged in
+// `big`, without the tasks that run elsewhere. Targets are grouped into chunks whose T buffers (one per task:
+// target rows x source columns, in tiles) stay below the T budget. A wavefront owns up to 64 x 64 elements:
+// both extents are cut into equal parts, so that the parts of one block differ by a tile at most. Per
 // chunk, pass 1 has one piece of work per task and part of its T; pass 2 one item per part of a target and
 // task range, the task lists cut into ranges of about tune_big_stages T tiles whose partial sums a reduction
 // adds in order. The pieces of one task, and those of one range of a target, read the same operands: they
 // are dealt together to one XCD, the least loaded so far.
-void build_big64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, const std::vector<char>& task_keep) {
-    dmrg::BigPlan& plan = H.bplan64;
-    std::vector<dmrg::BigChunk>& chunks = H.big_chunks64;
+void build_big_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, bool fp64, const std::vector<char>& task_keep) {
+    dmrg::BigPlan& plan = fp64 ? H.bplan64 : H.bplan;
+    std::vector<dmrg::BigChunk>& chunks = fp64 ? H.big_chunks64 : H.big_chunks;
     plan = dmrg::BigPlan{};
     chunks.clear();
-    const int64_t t_budget = (int64_t)H.tune_big_tbudget_mb << 18;   // T doubles per chunk (twice the split form's bytes)
-    std::vector<dmrg::Big64T> t1;
+    const int tw = fp64 ? 16 : 32, j_most = 64 / tw;                  // width of a T tile; tile columns of a part
+    const int64_t tile = fp64 ? 256 : dmrg::kTileU16;
+    const int64_t t_budget = (int64_t)H.tune_big_tbudget_mb << (fp64 ? 18 : 19);   // T elements per chunk
+    auto cols = [&](int i) { return (H.blk_md[i] + tw - 1) / tw; };
+    // operands of a task (identity factors: identity blocks); < 0: none
+    std::vector<int64_t> xt_off = H.xt64_off;
+    if (!fp64) {
+        xt_off.resize(H.blk.size());
+        int64_t at = 0;
+        for (size_t i = 0; i < H.blk.size(); ++i) {
+            xt_off[i] = 2 * at;
+            at += (int64_t)dmrg::ld_of(H.blk_ma[i]) * dmrg::ld_of(H.blk_md[i]);
+        }
+    }
+    auto operand = [&](int m, int sector, int dim) -> int64_t {
+        if (fp64) return op64_of(H, m, sector, dim);
+        if (m >= 0) return 2 * H.mats[m].pool_of_in[sector];
+        const int k = dmrg::ld_of(dim) / 32 - 1;
+        return k < (int)H.ident_off.size() ? H.ident_off[k] : -1;
+    };
+    std::vector<dmrg::BigT> t1;
     std::vector<dmrg::BigT2> t2;
     std::vector<dmrg::Item> items;
     std::vector<dmrg::Reduce> reds;
-    XcdDeal<dmrg::Big64T> deal1{dmrg::Big64T{}};
+    XcdDeal<dmrg::BigT> deal1{dmrg::BigT{}};
     dmrg::Item none{};
     none.part_off = -1;
     XcdDeal<dmrg::Item> deal2{none};
@@ -882,10 +724,10 @@ void build_big64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, 
         while (k < H.tasks.size() && H.tasks[k].j == (int)j) ++k;
         if (!big[j]) continue;
         const int ma = H.blk_ma[j], md = H.blk_md[j], nrt = (ma + 15) / 16, nq = (md + 15) / 16;
-        auto t_tiles = [&](const dmrg_hop::HTask& t) { return (int64_t)nrt * ((H.blk_md[t.i] + 15) / 16); };
+        auto t_size = [&](const dmrg_hop::HTask& t) { return (int64_t)nrt * cols(t.i) * tile; };
         int64_t need = 0;
         for (size_t t = kb; t < k; ++t)
-            if (task_keep[t]) need += t_tiles(H.tasks[t]) * 256;
+            if (task_keep[t]) need += t_size(H.tasks[t]);
         if (need == 0) continue;                  // every task of the target runs elsewhere
         if (tsize > 0 && tsize + need > t_budget) close_chunk();
         open = true;
@@ -897,14 +739,15 @@ void build_big64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, 
         for (size_t t = kb; t < k; ++t) {
             if (!task_keep[t]) continue;
             const auto& ht = H.tasks[t];
-            const int sa = H.blk_ma[ht.i], sd = H.blk_md[ht.i], pd = (sd + 15) / 16;
-            const int64_t a = op64_of(H, ht.lm, H.blk[ht.i][0], sa), b = op64_of(H, ht.rm, H.blk[ht.i][3], sd);
+            const int sa = H.blk_ma[ht.i], sd = H.blk_md[ht.i], pd = cols(ht.i);
+            const int64_t a = operand(ht.lm, H.blk[ht.i][0], sa), b = operand(ht.rm, H.blk[ht.i][3], sd);
             if (a < 0 || b < 0) throw Error(DMRG_ERR_ARG, "internal: no operand block");
-            deal1.open((double)nrt * pd * dmrg::k4_of(sa));
-            for_parts(nrt, [&](int rb, int nr) {
-                for_parts(pd, [&](int jb, int nj) {
-                    deal1.add({H.xt64_off[ht.i], a, tsize, ht.f, dmrg::k4_of(sa), dmrg::k4_of(sd), dmrg::k4_of(ma), pd,
-                               (int16_t)rb, (int16_t)nr, (int16_t)jb, (int16_t)nj, part_j, 0});
+            const int ka = fp64 ? dmrg::k4_of(sa) : (sa + 31) / 32, kd = fp64 ? dmrg::k4_of(sd) : pd;
+            deal1.open((double)nrt * pd * ka);
+            for_parts(nrt, 4, [&](int rb, int nr) {
+                for_parts(pd, j_most, [&](int jb, int nj) {
+                    deal1.add({xt_off[ht.i], a, tsize, ht.f, ka, kd, dmrg::k4_of(ma), pd, (int16_t)rb, (int16_t)nr,
+                               (int16_t)jb, (int16_t)nj, part_j, 0});
                     ++pieces;
                 });
             });
@@ -915,17 +758,17 @@ void build_big64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, 
             }
             if (c == 0) cost.push_back(0.0);
             c += pd;
-            cost.back() += (double)nrt * nq * dmrg::k4_of(sd);
-            t2.push_back({tsize, b, pd, dmrg::k4_of(sd)});
-            tsize += t_tiles(ht) * 256;
+            cost.back() += (double)nrt * nq * kd;
+            t2.push_back({tsize, b, pd, kd});
+            tsize += t_size(ht);
         }
         cuts.push_back({b0, (int32_t)t2.size()});
         const int64_t part0 = part;
         for (size_t q = 0; q < cuts.size(); ++q) {
             deal2.open(cost[q]);
             int64_t at = part0;                  // the records' partial tiles of this target, n_parts each
-            for_parts(nrt, [&](int rb, int nr) {
-                for_parts(nq, [&](int qb, int nqw) {
+            for_parts(nrt, 4, [&](int rb, int nr) {
+                for_parts(nq, 4, [&](int qb, int nqw) {
                     const int tm = 16 * nr, tn = 16 * nqw;
                     dmrg::Item it{H.blk_off[j], -1, ma, md, 16 * rb, 16 * qb, cuts[q].first, cuts[q].second};
                     if (cuts.size() > 1) {
@@ -953,20 +796,21 @@ void build_big64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& big, 
         if (!v.empty()) HIPCHK(hipMemcpyAsync(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
         return d;
     };
-    plan.w1 = upload(t1);
+    plan.t1 = upload(t1);
     plan.t2 = upload(t2);
     plan.items = upload(items);
     plan.reduces = upload(reds);
     plan.chunks = chunks.data();
     plan.n_chunks = (int)chunks.size();
     plan.red_chunks = (red_max + 255) / 256;
-    plan.tbuf = reinterpret_cast<uint16_t*>(plan_alloc<double>(H, (size_t)std::max<int64_t>(tbuf_max, 1)));
+    const size_t t_bytes = (size_t)std::max<int64_t>(tbuf_max, 4) * (fp64 ? sizeof(double) : sizeof(uint16_t));
+    plan.tbuf = reinterpret_cast<uint16_t*>(plan_alloc<double>(H, t_bytes / sizeof(double)));
     plan.partial = plan_alloc<double>(H, (size_t)std::max<int64_t>(part_max, 1));
     plan.partial_size = part_max;
     if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
         if (e[0] == '1')
-            std::fprintf(stderr, "[dmrg big plan fp64] chunks %zu pass-1 groups %zu pass-2 items %zu reduces %zu T %.1f MB "
-                         "partial %.1f MB\n", chunks.size(), pieces, ranges, reds.size(), tbuf_max * 8e-6, part_max * 8e-6);
+            std::fprintf(stderr, "[dmrg big plan%s] chunks %zu pass-1 groups %zu pass-2 items %zu reduces %zu T %.1f MB "
+                         "partial %.1f MB\n", fp64 ? " fp64" : "", chunks.size(), pieces, ranges, reds.size(), t_bytes * 1e-6, part_max * 8e-6);
     HIPCHK(hipStreamSynchronize(s));
 }
 
@@ -1232,7 +1076,7 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
         for (size_t j = 0; j < nb; ++j) rest[j] = !big64[j];
         for (size_t t = 0; t < rs64.size(); ++t) rest_tasks[t] = !rs64[t];
         build_plan_core(H, s, &rest, false, H.plan, H.launches, H.phases, &rest_tasks);
-        if (any_big) build_big64_plan(H, s, big64, rest_tasks);
+        if (any_big) build_big_plan(H, s, big64, true, rest_tasks);
     } else {
         build_plan_core(H, s, nullptr, false, H.plan, H.launches, H.phases);
     }
@@ -1246,7 +1090,7 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
     H.bplan = dmrg::BigPlan{};
     if (H.n_fallback_targets > 0) {
         if (H.tune_big) {
-            build_big_plan(H, s, fb, &fb_task);
+            build_big_plan(H, s, fb, false, fb_task);
             H.n_fallback_targets = 0;
         } else {
             if (!H.d_hi) throw Error(DMRG_ERR_ARG, "internal: row-major split operators missing");
