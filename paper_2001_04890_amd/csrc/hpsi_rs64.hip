@@ -14,9 +14,11 @@
 //
 // What bounds it: an FP64 16x16x4 MFMA takes 64 cycles, so a wavefront needs 2 KB per 256 cycles, half of
 // what a CU's vector cache delivers to four of them: the matrix cores and the traffic between the L2s
-// and memory bound large sectors, latency (hidden by 8 .. 16 wavefronts per CU) and launches the small. One
-// matvec of 24 orbitals at bond dimension 1024 takes 5.3 ms (3.6 ms of MFMAs; 6.5 ms with pointer loads and
-// the accumulators copied around conditional MFMAs), of 17 orbitals at 333 states 278 us (336 us).
+// and memory bound large sectors, latency (hidden by 8 .. 32 wavefronts per CU) and launches the small. One
+// matvec of 24 orbitals at bond dimension 1024 takes 5.1 ms (3.6 ms of MFMAs; 6.5 ms with pointer loads and
+// the accumulators copied around conditional MFMAs), of 17 orbitals at 333 states 230 us (278 us with the
+// smallest classes at 4 wavefronts per SIMD instead of 8), of a batch of 12 problems with sectors of up to some
+// 30 states 786 us (1.0 ms).
 #include "device.h"
 #include "internal.h"
 
@@ -149,9 +151,14 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
     // store: lane (li, g) holds Y[16 rt + g + 4 v][16 q + li]
     const int64_t y_off = uni64(ip->y_off), part_off = uni64(ip->part_off);
     if (part_off >= 0) {
-        double* dst = part + part_off + (int64_t)rt * 256 * tq + g * (16 * tq) + li;
+        const __amdgpu_buffer_rsrc_t op = buf(part + part_off + (int64_t)rt * 256 * tq, 2048 * tq);
+        const int at = (int)((g * 16 * tq + li) * 8);
         each<QT>([&](auto q) {
-            if (q < tq) each<4>([&](auto i) { constexpr int v = i; dst[64 * v * tq + 16 * q] = acc[q][v]; });
+            if (q < tq) each<4>([&](auto i) {
+                constexpr int v = i;
+                const double a = acc[q][v];
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i32x2, a), op, at, (64 * v * tq + 16 * q) * 8, 0);
+            });
         });
     } else {
         // the loads of four column tiles are in flight at once; what lies outside the block is neither read nor written
@@ -180,7 +187,7 @@ template <int G, int K, int Q>
 __device__ __forceinline__ bool rs_try(int cls, const Item* __restrict__ ip, const LTask64* __restrict__ tasks,
                                        const double* __restrict__ ops, const double* __restrict__ xt, double* __restrict__ y,
                                        double* __restrict__ part, int lane) {
-    if constexpr (rs_group(K, Q) == G) {
+    if constexpr (rs_group(K, Q) <= G) {
         if (cls == 8 * K + Q) {
             rs_item<K == 0 ? 1 : 2 * kRsK[K], kRsQ[Q], K == 0 ? 1 : 2>(ip, tasks, ops, xt, y, part, lane);
             return true;
@@ -201,7 +208,7 @@ __device__ __forceinline__ void rs_try_k(int cls, const Item* __restrict__ ip, c
 
 }  // namespace
 
-// Group G runs the classes of its register budget (rs_group).
+// Group G runs the classes within its register budget (rs_group and below).
 template <int G, int MINW>
 __global__ __launch_bounds__(kRsWaves * 64, MINW) void k_hpsi_rs64(const Item* __restrict__ items, int n_items,
                                                                 const LTask64* __restrict__ tasks,
@@ -232,9 +239,15 @@ hipError_t launch_hpsi_rs64(const RsPlan64& P, const double* ops, const double* 
         if (n <= 0) continue;
         const dim3 grid((n + kRsWaves - 1) / kRsWaves), block(kRsWaves * 64);
         const Item* it = P.items + b;
-        if (g == 0) hipLaunchKernelGGL((k_hpsi_rs64<0, 4>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active);
-        else if (g == 1) hipLaunchKernelGGL((k_hpsi_rs64<1, 3>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active);
-        else hipLaunchKernelGGL((k_hpsi_rs64<2, 2>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active);
+#define DMRG_RS(G, W) hipLaunchKernelGGL((k_hpsi_rs64<G, W>), grid, block, 0, s, it, n, P.tasks, ops, xt, y, P.partial, active)
+        switch (g) {
+            case 0: DMRG_RS(0, 8); break;
+            case 1: DMRG_RS(1, 5); break;
+            case 2: DMRG_RS(2, 4); break;
+            case 3: DMRG_RS(3, 3); break;
+            default: DMRG_RS(4, 2); break;
+        }
+#undef DMRG_RS
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || P.n_reduces <= 0) return e;

@@ -192,8 +192,8 @@ struct OpBlock64 { int64_t src, dst; int32_t ld, rows, cols, pad; };   // pool b
 // wavefronts: r0 = 16 x the row tile, c0 = the class 8 k + q, with k an index into kRsK (source rows in
 // 16-wide tiles; 0: source rows and columns both within 8) and q one into kRsQ (target columns).
 // begin[g] .. begin[g + 1]: the items of launch group g (register budgets, see the kernel).
-constexpr int kRsWaves = 1;             // wavefronts (items) per workgroup (4: 3% slower at 333 states, 3% faster at 1024)
-constexpr int kRsGroups = 3;
+constexpr int kRsWaves = 4;             // wavefronts (items) per workgroup (1: 3% slower at 1024 states, 1% faster at 333)
+constexpr int kRsGroups = 5;
 constexpr int kRsK[7] = {0, 1, 2, 3, 4, 6, 8};
 constexpr int kRsQ[6] = {1, 2, 3, 4, 6, 8};
 constexpr int kRsMaxTiles = 8;          // target rows are any; target columns, source rows and columns
@@ -205,13 +205,13 @@ inline int rs_kclass(int ka4, int kd4) {
 }
 inline int rs_qclass(int tiles) { int c = 0; while (kRsQ[c] < tiles) ++c; return c; }
 // Launch group of a class: the accumulators (8 registers a column tile), the A row tile (8 a source tile),
-// the two rings and what the compiler takes besides (16 .. 30) within 128 (group 0), 168 (1) or 256 (2)
-// registers, i.e. 4, 3 or 2 wavefronts per SIMD.
+// the two rings and what the compiler takes besides (16 .. 30) within 64, 96, 128, 168 or 256 registers, i.e.
+// 8, 5, 4, 3 or 2 wavefronts per SIMD.
 constexpr int rs_group(int k, int q) {
     const int kp = k == 0 ? 1 : 2 * kRsK[k], qt = kRsQ[q], jp = k == 0 ? 1 : 2;
     const int rx = kp == 16 ? 8 : kp, rb = qt == 8 ? 4 : qt;
-    const int regs = 8 * qt + 4 * (kp + rx + rb * jp) + (qt == 8 ? 30 : qt == 6 ? 20 : 16);
-    return regs < 128 ? 0 : regs <= 168 ? 1 : 2;
+    const int regs = 8 * qt + 4 * (kp + rx + rb * jp) + (qt == 8 ? 30 : qt == 6 ? 20 : qt == 4 ? 18 : 16);
+    return regs <= 64 ? 0 : regs <= 96 ? 1 : regs < 128 ? 2 : regs <= 168 ? 3 : 4;
 }
 struct LTask64 {
     int64_t x_off, a_off, b_off;        // doubles: X^T of the source in xt, A and B in the operand pool
@@ -224,7 +224,7 @@ struct RsPlan64 {
     const Reduce* reduces = nullptr;    // device; one record per target cut into several items
     int n_reduces = 0;
     int red_chunks = 1;                 // 256-element chunks of the largest partial tile
-    int begin[kRsGroups + 1] = {0, 0, 0, 0};
+    int begin[kRsGroups + 1] = {0, 0, 0, 0, 0, 0};
     double* partial = nullptr;          // device, partial tiles of one vector
     int64_t partial_size = 0;
     int n_items = 0;                    // task ranges (each runs as one wavefront per row tile of its target)
