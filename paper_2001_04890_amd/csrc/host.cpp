@@ -898,13 +898,15 @@ void enqueue_hpsi(dmrg_hop* H, const double* x, double* y, int32_t nvec, int32_t
         const double* xv = x + (int64_t)v0 * H->n_coeff;
         double* yv = y + (int64_t)v0 * H->n_coeff;
         if (precision == DMRG_PREC_FP64) {
-            // zeroes y, then the one-wave targets
-            HIPCHK(dmrg::launch_hpsi_f64(H->plan, H->d_pool, xv, yv, H->n_coeff, nv, s, act));
             const bool rs = H->rplan64.n_items > 0, big = H->bplan64.n_chunks > 0;
+            bool one_wave = !rs && !big;
+            for (const auto& l : H->launches) one_wave |= l.item_count > 0;
+            // zeroes y, then the one-wave targets; without any, the packing of x zeroes y
+            if (one_wave) HIPCHK(dmrg::launch_hpsi_f64(H->plan, H->d_pool, xv, yv, H->n_coeff, nv, s, act));
             for (int v = 0; v < nv && (rs || big); ++v) {
                 const double* x1 = xv + (int64_t)v * H->n_coeff;
                 double* y1 = yv + (int64_t)v * H->n_coeff;
-                HIPCHK(dmrg::launch_pack_xt64(H->packs64, H->n_packs64, x1, H->xt64, s));
+                HIPCHK(dmrg::launch_pack_xt64(H->packs64, H->n_packs64, x1, H->xt64, one_wave ? nullptr : y1, s));
                 if (rs) HIPCHK(dmrg::launch_hpsi_rs64(H->rplan64, H->d_op64, H->xt64, y1, s, act));
                 if (big) HIPCHK(dmrg::launch_hpsi_big64(H->bplan64, H->d_op64, H->xt64, y1, s, act));
             }

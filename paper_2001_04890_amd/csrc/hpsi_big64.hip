@@ -117,9 +117,15 @@ hipError_t launch_op64(const double* pool, const OpBlock64* blocks, int n_blocks
     return hipGetLastError();
 }
 
-// psi block X (m_a x m_d) -> X^T in operand form (m_d rows, m_a columns) at dst_off
-__global__ void k_pack_xt64(const PackBlock* __restrict__ packs, const double* __restrict__ x, double* __restrict__ xt) {
+// psi block X (m_a x m_d) -> X^T in operand form (m_d rows, m_a columns) at dst_off; clears the block of y (a
+// launch of its own took a tenth of the smallest matvecs)
+__global__ void k_pack_xt64(const PackBlock* __restrict__ packs, const double* __restrict__ x, double* __restrict__ xt,
+                            double* __restrict__ y) {
     const PackBlock P = packs[blockIdx.x];
+    if (y) {
+        const int64_t len = (int64_t)P.m_a * P.m_d;
+        for (int64_t e = threadIdx.x; e < len; e += blockDim.x) y[P.src_off + e] = 0.0;
+    }
     const int r4 = (P.m_d + 3) / 4, n = r4 * ((P.m_a + 7) / 8) * 16;
     for (int e = threadIdx.x; e < n; e += blockDim.x) {
         int j, k;
@@ -244,9 +250,9 @@ __global__ __launch_bounds__(64, 2) void k_big64_y(const Item* __restrict__ item
     });
 }
 
-hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x, double* xt, hipStream_t s) {
+hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x, double* xt, double* y, hipStream_t s) {
     if (n_packs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pack_xt64, dim3(n_packs), dim3(256), 0, s, packs, x, xt);
+    hipLaunchKernelGGL(k_pack_xt64, dim3(n_packs), dim3(256), 0, s, packs, x, xt, y);
     return hipGetLastError();
 }
 

@@ -108,8 +108,12 @@ hipError_t launch_split_tiled(const double* pool, const PoolBlock* blocks, int n
 // j = 32 jc + 8 (li / 4) + li % 4 + 4 h2, k = 32 kt + 8 g + u. With this row order the GEMM1 result
 // lane layout is the GEMM2 A-operand layout (see the kernel).
 __global__ void k_pack_xt(const PackBlock* __restrict__ packs, const double* __restrict__ xall, int64_t n_coeff,
-                          int64_t xt_size, uint16_t* __restrict__ xtall) {
+                          int64_t xt_size, uint16_t* __restrict__ xtall, double* __restrict__ yall) {
     const PackBlock P = packs[blockIdx.x];
+    if (yall) {   // clears the block of y
+        double* __restrict__ y = yall + (int64_t)blockIdx.y * n_coeff + P.src_off;
+        for (int64_t e = threadIdx.x; e < (int64_t)P.m_a * P.m_d; e += blockDim.x) y[e] = 0.0;
+    }
     const double* __restrict__ x = xall + (int64_t)blockIdx.y * n_coeff + P.src_off;
     uint16_t* __restrict__ xt = xtall + (int64_t)blockIdx.y * xt_size + 2 * P.dst_off;
     const int pa32 = P.pa / 32, pd32 = P.pd / 32;
@@ -480,20 +484,11 @@ hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, cons
     return hipGetLastError();
 }
 
-__global__ void k_zero_lds(double* __restrict__ y, int64_t n) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        y[i] = 0.0;
-}
-
 hipError_t launch_hpsi_lds(const LdsPlan& P, const uint16_t* pool_t, const double* x, double* y, int64_t n_coeff,
                            int nvec, bool zero_y, hipStream_t s, const int32_t* active) {
-    if (zero_y) {
-        int64_t n = n_coeff * nvec, blocks = (n + 255) / 256;
-        if (blocks > 8192) blocks = 8192;
-        hipLaunchKernelGGL(k_zero_lds, dim3((unsigned)blocks), dim3(256), 0, s, y, n);
-    }
     if (P.n_packs == 0) return hipGetLastError();
-    hipLaunchKernelGGL(k_pack_xt, dim3(P.n_packs, nvec), dim3(256), 0, s, P.packs, x, n_coeff, P.xt_size, P.xt);
+    hipLaunchKernelGGL(k_pack_xt, dim3(P.n_packs, nvec), dim3(256), 0, s, P.packs, x, n_coeff, P.xt_size, P.xt,
+                       zero_y ? y : nullptr);
     const int64_t ss = P.partial_size;
     for (int c = 0; c < kLdsClasses; ++c) {
         const int b = P.cls_begin[c], n = P.cls_begin[c + 1] - b;

@@ -232,9 +232,9 @@ struct RsPlan64 {
 // y (one vector) += the plan's targets of f A X B^T; xt = that vector's X^T in operand form
 hipError_t launch_hpsi_rs64(const RsPlan64& P, const double* ops, const double* xt, double* y, hipStream_t s,
                             const int32_t* active = nullptr);
-// operand form of the pool's blocks, and of X^T of every psi block (hpsi_big64.hip)
+// operand form of the pool's blocks, and of X^T of every psi block (hpsi_big64.hip); y (if given) = 0
 hipError_t launch_op64(const double* pool, const OpBlock64* blocks, int n_blocks, double* ops, hipStream_t s);
-hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x, double* xt, hipStream_t s);
+hipError_t launch_pack_xt64(const PackBlock* packs, int n_packs, const double* x, double* xt, double* y, hipStream_t s);
 // y (one vector) += the partial tiles of each record, in order (hpsi_lds.hip)
 hipError_t launch_reduce_partials(const Reduce* reduces, int n, int chunks, const double* partial, double* y,
                                   hipStream_t s, const int32_t* active = nullptr);
