@@ -123,14 +123,10 @@ dmrg_status dmrg::davidson_run(dmrg_hop* H, double* psi, const dmrg_dav_opts* o,
         // device-side classical Gram-Schmidt (twice) of x against the first k columns of V, and
         // normalization with the squared norm left in w.dots[slot]: no host round trip
         auto orth_dev = [&](int k, double* x) {
-            for (int pass = 0; pass < 2 && k > 0; ++pass) {
-                HIPCHK(dmrg::launch_multidot(w.V, k, n, x, w.part, np, w.dots, s));
-                HIPCHK(dmrg::launch_project_out(w.V, k, n, w.dots, x, s));
-            }
+            for (int pass = 0; pass < 2 && k > 0; ++pass) HIPCHK(dmrg::launch_orthogonalize(w.V, k, n, x, w.part, np, w.dots, s));
         };
         auto normalize_dev = [&](double* x, int slot) {
-            HIPCHK(dmrg::launch_multidot(x, 1, n, x, w.part, np, w.dots + slot, s));
-            HIPCHK(dmrg::launch_scale_dev(x, w.dots + slot, n, s));
+            HIPCHK(dmrg::launch_normalize(x, n, w.part, np, w.dots + slot, s));
         };
         auto combine = [&](const double* Vs, int nv, const std::vector<double>& c, double* out, double beta) {
             dmrg::Coefs cf;

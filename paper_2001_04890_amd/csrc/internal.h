@@ -302,8 +302,10 @@ hipError_t launch_precond(const double* r, const double* d, double theta, double
 hipError_t launch_scale(double* x, double a, int64_t n, hipStream_t s);
 int multidot_parts(int64_t n);
 // out -= sum_j c[j] V[j], c in device memory; x *= 1 / sqrt(*nrm2) with *nrm2 in device memory.
-hipError_t launch_project_out(const double* V, int nv, int64_t n, const double* c, double* out, hipStream_t s);
-hipError_t launch_scale_dev(double* x, const double* nrm2, int64_t n, hipStream_t s);
+// x -= sum_j (V[j] . x) V[j] (sums: room for nv doubles); x /= |x| with |x|^2 left in *nrm2
+hipError_t launch_orthogonalize(const double* V, int nv, int64_t n, double* x, double* partial, int n_part, double* sums,
+                                hipStream_t s);
+hipError_t launch_normalize(double* x, int64_t n, double* partial, int n_part, double* nrm2, hipStream_t s);
 
 // Reduced density matrix of the enlarged left block (Section 2.1), one item per (sector, row group,
 // row group): rho[rho_off + l * ld + l2] = sum over the sector's n_cd column groups k of
