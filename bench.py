@@ -31,11 +31,9 @@ HBM_PEAK = 8000.0                        # GB/s
 # commands in profiles/hpsi_L24_M1024_swept_kernel_trace.md and
 # profiles/hpsi_{fp64,split}_L24_M1024_synthetic_kernel_trace.md.
 TRAFFIC_L24_M1024 = {
-    # synthetic operators: counters taken before the current kernels (part-mask argument, FP64
-    # single-tile sources in k_hpsi_lds64), so not reported
+    # counters taken with earlier kernels are not reported
     "synthetic": {"fp64": None, "split": None},
-    "swept": {"fp64": {"fetch_bytes": 21708.0 * 2**20, "write_bytes": 2879.0 * 2**20},
-              "split": {"fetch_bytes": 13751.0 * 2**20, "write_bytes": 3037.0 * 2**20}},
+    "swept": {"fp64": None, "split": None},
 }
 
 
@@ -235,17 +233,16 @@ def main():
     roofline = {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK["fp64"], "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK["fp64"], 4),
                 "traffic": (tr64["fetch_bytes"] + tr64["write_bytes"]) if tr64 else None,
-                "kernel": "FP64 H.psi sequence (k_hpsi_lds64 classes for targets within 112 x 112; k_hpsi_f64 "
-                          "tiles and k_big64 passes for the rest, with k_pack when those tiles run; k_pack_xt64, "
-                          "k_reduce_lds, k_zero)",
+                "kernel": "FP64 H.psi sequence (k_hpsi_rs64 groups for targets and sources within 128 x 128, "
+                          "k_big64_t + k_big64_y for the rest; k_pack_xt64, k_reduce_lds)",
                 "algorithmic_bytes": st["bytes"],
                 "hbm_frac": round(st["bytes"] / t64 / 1e9 / HBM_PEAK, 4)}
     achieved_sp = st["flops"] / tsp / 1e12
     traffic_sp = (trsp["fetch_bytes"] + trsp["write_bytes"]) if trsp else None
     split_roofline = {"bound": "mfma", "achieved": round(achieved_sp, 3), "peak": PEAK["bf16"], "unit": "TFLOP/s",
                       "frac": round(achieved_sp / PEAK["bf16"], 5), "traffic": traffic_sp,
-                      "kernel": "split H.psi sequence (k_hpsi_lds, k_hpsi_small, k_big_t + k_big_y above 96 x 96, "
-                                "k_pack_xt, k_reduce_lds, k_reduce_big)",
+                      "kernel": "split H.psi sequence (k_hpsi_rows, k_hpsi_small, k_big_t + k_big_y above 96 x 96, "
+                                "k_pack_xt, k_reduce_lds)",
                       "mfma_products_per_flop": 3,
                       "algorithmic_bytes": st["bytes"] / 2,
                       "hbm_frac": round(st["bytes"] / 2 / tsp / 1e9 / HBM_PEAK, 4)}
@@ -292,7 +289,7 @@ def bench_batch(args):
     from dmrg_inputs import random_vector
     from dmrg_inputs.synthetic import synthetic_problem
     import multiprocessing as mp
-    # the FP64 LDS-staged kernel keeps an FP64 tiled copy of every operator; the merged handle next to
+    # the register-streamed kernel keeps an FP64 copy of every operator in its operand form; the merged handle next to
     # the 128 individual ones would not fit with it, so both sides of this comparison run FP64 on the
     # one-wavefront kernel
     os.environ["DMRG_LDS64"] = "0"

@@ -416,13 +416,11 @@ dmrg_status dmrg_davidson_batch(dmrg_hop* hop, double* psi, const dmrg_dav_opts*
  * plan's settings, each taking in turn its fastest candidate value with the others held at their
  * best so far; every candidate is timed on the device (the fastest of `reps` calls after one
  * warm-up) and the plan is rebuilt with the winners. Settings, in the order of `chosen`:
- * split: LDS work items (4k .. 64k; per merged problem on a merged handle), launch order (heaviest
+ * split: work items (4k .. 64k; per merged problem on a merged handle), launch order (heaviest
  * first / XCD-aware by left sector / each merged problem's items together), task-mode tile shape
- * (0: 1 x 2, 1: 2 x 2, 2: 1 x 4 row x column MFMA tiles per wavefront), 64-wide stage classes (1 on),
- * six-wavefront (S, 2) classes (bit mask 0x8 / 0 / 0xA), copy-wavefront classes (0 / 0xF), prefetch
- * wavefront (0x4 / 0), 0. FP64: LDS-staged kernel work items (8k .. 64k), its copy wavefront (1/0),
- * single-tile sources in it (1/0), its 7-wavefront register cap (1/0), two-pass routing of large
- * targets (1 where cheaper, 2 all), one-wavefront tile width (2, 4, 8 tiles of 16 columns), its work
+ * (0: 1 x 2, 1: 2 x 2, 2: 1 x 4 row x column MFMA tiles per wavefront), 64-wide classes (1 on), and
+ * 0, 0, 0, 0. FP64: register-streamed kernel work items (8k .. 64k), 1, single-tile sources in it (1/0), 1,
+ * two-pass routing of large targets (1), one-wavefront tile width (2, 4, 8 tiles of 16 columns), its work
  * items (8k, 32k, 64k) and launch order (0 heaviest first, 2 cache-aware). chosen
  * (DMRG_AUTOTUNE_KNOBS ints) and best_ms (milliseconds of the chosen plan) may be NULL. Drops the
  * handle's cached graphs. Synchronizes `stream`. */
