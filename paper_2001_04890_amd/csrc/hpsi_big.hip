@@ -89,14 +89,14 @@ __global__ __launch_bounds__(64, 2) void k_big_t(const BigT* __restrict__ work, 
     if (mask && mask[uni(wp->part)] != kPartActive) return;
     const int rb = uni(wp->rb), nr = uni(wp->nr), jb = uni(wp->jb), nj = uni(wp->nj);
     const int lane = threadIdx.x;
-    const uint16_t* x = xt + uni64(wp->xt);
-    const uint16_t* a = pool_t + uni64(wp->a);
+    const uint16_t* x = xt + uni64(wp->xt) + (int64_t)(2 * jb) * ka * kTileU16;
+    const uint16_t* a = pool_t + uni64(wp->a) + (int64_t)rb * ka * kTileU16;
     f32x4 acc[4][4];                                           // [column chunk half][row tile]
     uint32_t xo[4], ao[4];
     each<4>([&](auto i) {
         each<4>([&](auto j) { acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f}; });
-        xo[i] = i < 2 * nj ? (uint32_t)((2 * jb + i) * ka) * kTileBytes + (uint32_t)lane * 16u : kNowhere;
-        ao[i] = i < nr ? (uint32_t)((rb + i) * ka) * kTileBytes + (uint32_t)lane * 16u : kNowhere;
+        xo[i] = i < 2 * nj ? (uint32_t)(i * ka) * kTileBytes + (uint32_t)lane * 16u : kNowhere;
+        ao[i] = i < nr ? (uint32_t)(i * ka) * kTileBytes + (uint32_t)lane * 16u : kNowhere;
     });
     int left = ka;                                             // k tiles from the next one on
     multiply(acc, 2 * nj, nr, xo, ao,
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64, 2) void k_big_t(const BigT* __restrict__ work, 
              [](int) {});
     // acc[2 jj + h2][rr][v] = T'[row 16 rt + li][col 32 jc + 8 g + 4 h2 + v]
     const float f = (float)unid(wp->f);
-    uint16_t* to = tbuf + uni64(wp->t) + (int64_t)(rb * pd + jb) * kTileU16 + lane * 8;
+    uint16_t* to = tbuf + uni64(wp->t) + ((int64_t)rb * pd + jb) * kTileU16 + lane * 8;
     each<2>([&](auto jj) {
         each<4>([&](auto rr) {
             if (jj < nj && rr < nr) {

@@ -167,7 +167,7 @@ __global__ __launch_bounds__(64, 2) void k_big64_t(const BigT* __restrict__ work
     });
     // acc[jj][rr][v] = T'^T[j 16 jt + g + 4 v][r 16 rt + li] = T tile (rt, jt), lane value v
     const double f = unid(wp->f);
-    double* to = tbuf + uni64(wp->t) + (int64_t)(rb * pd + jb) * kTileD + lane * 2;
+    double* to = tbuf + uni64(wp->t) + ((int64_t)rb * pd + jb) * kTileD + lane * 2;
     each<4>([&](auto jj) {
         each<4>([&](auto rr) {
             if (jj < nj && rr < nr) {
