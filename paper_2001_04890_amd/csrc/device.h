@@ -39,11 +39,13 @@ __device__ __forceinline__ void each(F&& f) {
 // keeps the loads before it from sinking to their uses and those after it from rising
 __device__ __forceinline__ void fence() { asm volatile("" ::: "memory"); }
 
-// `bytes` at p for buffer loads; what a load asks for past them is zero and moves nothing
+// `bytes` at p for buffer loads; what a load asks for past them is zero and moves nothing. The card checks the sum of
+// the lane's and the scalar offset (4096 bytes and 0 .. 65536 as the scalar offset: zeros from 4096 on); by the
+// intrinsic's contract alone it is the lane's offset, hence kOperandSlack (internal.h).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const void* p, int bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, bytes, 0x00027000);
 }
-// 16 bytes at byte lane_bytes + at (wave-uniform)
+// 16 bytes at byte lane_bytes + at (wave-uniform, the scalar offset)
 __device__ __forceinline__ i32x4 ld16(__amdgpu_buffer_rsrc_t b, uint32_t lane_bytes, uint32_t at) {
     return (i32x4)__builtin_amdgcn_raw_buffer_load_b128(b, (int)lane_bytes, (int)at, 0);
 }

@@ -14,6 +14,12 @@ constexpr int kRowPad = 16;    // row padding of pool blocks (MFMA tile height)
 constexpr int kLd = 32;        // leading-dimension padding of pool blocks and packed psi blocks
 inline int32_t ld_of(int32_t m) { return (m + kLd - 1) / kLd * kLd; }
 inline int32_t rows_of(int32_t m) { return (m + kRowPad - 1) / kRowPad * kRowPad; }
+// Bytes allocated behind the arrays whose operands hpsi_rs64.hip and hpsi_lds.hip read with a scalar offset in
+// the buffer load (the operand pools and the packed X^T). A kernel class made for longer operands asks up to 15
+// column groups of 128 rows (120 KB) past the end of a short one. The card's range check stops these loads, but
+// the compiler's intrinsic leaves the scalar offset out of the check that it promises; with the slack they would
+// stay inside the allocation without it.
+constexpr int kOperandSlack = 15 * 32 * 256;
 
 // One sector-GEMM contribution to an output psi block (Eq. dgemm, Section 2.2.1):
 //   Y_target += f * A . X_source . B^T

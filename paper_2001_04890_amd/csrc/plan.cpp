@@ -591,7 +591,7 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
     H.lplan.packs = d_packs;
     H.lplan.n_packs = (int)packs.size();
     H.lplan.xt_size = 2 * psize;
-    H.lplan.xt = plan_alloc<uint16_t>(H, (size_t)2 * psize * H.vec_step);
+    H.lplan.xt = plan_alloc<uint16_t>(H, (size_t)2 * psize * H.vec_step + dmrg::kOperandSlack / sizeof(uint16_t));
     if (const char* e = std::getenv("DMRG_PLAN_TRACE"))
         if (e[0] == '1') {
             std::fprintf(stderr, "[dmrg lds plan] items %zu row classes", items.size());
@@ -857,7 +857,7 @@ void make_op64(dmrg_hop& H, hipStream_t s) {
         if (t.lm < 0) add_ident(H.blk_ma[t.i]);
         if (t.rm < 0) add_ident(H.blk_md[t.i]);
     }
-    H.op64_len = n + (int64_t)tail.size();
+    H.op64_len = n + (int64_t)tail.size() + dmrg::kOperandSlack / (int64_t)sizeof(double);
     H.d_op64 = dev_alloc<double>(H, H.op64_len);
     dmrg::OpBlock64* d_ob = dev_alloc<dmrg::OpBlock64>(H, ob.size());
     HIPCHK(hipMemcpyAsync(d_ob, ob.data(), ob.size() * sizeof(ob[0]), hipMemcpyHostToDevice, s));
@@ -879,7 +879,7 @@ void build_pack64(dmrg_hop& H, hipStream_t s) {
     }
     dmrg::PackBlock* d = plan_alloc<dmrg::PackBlock>(H, packs.size());
     HIPCHK(hipMemcpyAsync(d, packs.data(), packs.size() * sizeof(packs[0]), hipMemcpyHostToDevice, s));
-    H.xt64 = plan_alloc<double>(H, (size_t)std::max<int64_t>(n, 1));
+    H.xt64 = plan_alloc<double>(H, (size_t)n + dmrg::kOperandSlack / sizeof(double));
     H.packs64 = d;
     H.n_packs64 = (int)packs.size();
     HIPCHK(hipStreamSynchronize(s));
@@ -1150,7 +1150,7 @@ void make_tiled_split(dmrg_hop& H, hipStream_t s) {
             id[base + (size_t)(rt * k32 + kt) * dmrg::kTileU16 + lane * 8 + u] = 0x3F80;   // bf16 1.0
         }
     }
-    H.tiled_size = n + (int64_t)id.size();
+    H.tiled_size = n + (int64_t)id.size() + dmrg::kOperandSlack / (int64_t)sizeof(uint16_t);
     H.d_tiled = dev_alloc<uint16_t>(H, H.tiled_size);
     dmrg::PoolBlock* d_pb = dev_alloc<dmrg::PoolBlock>(H, H.pool_blocks.size());
     HIPCHK(hipMemcpyAsync(d_pb, H.pool_blocks.data(), H.pool_blocks.size() * sizeof(dmrg::PoolBlock),
