@@ -163,7 +163,7 @@ __device__ __forceinline__ void rs_item(const Item* __restrict__ ip, const LTask
     } else {
         // the loads of four column tiles are in flight at once; what lies outside the block is neither read nor written
         const __amdgpu_buffer_rsrc_t op = buf(y + y_off + (int64_t)rt * 16 * m_dp, min(16, m_ap - 16 * rt) * m_dp * 8);
-        auto at = [&](int q, int v) { return (int)(16 * q + li < (uint32_t)m_dp ? ((g + 4 * v) * m_dp + 16 * q + li) * 8u : ~0u); };
+        auto at = [&](int q, int v) { return (int)(16 * q + li < (uint32_t)m_dp ? ((g + 4 * v) * m_dp + 16 * q + li) * 8u : kNowhere); };
         each<(QT + 3) / 4>([&](auto h) {
             constexpr int q0 = 4 * h, nq = QT - q0 < 4 ? QT - q0 : 4;
             f64x4 old[nq];

@@ -5,8 +5,8 @@ lane by lane over work items whose tasks differ in size: every operand in turn i
 A buffer load is taken two ways, as the hardware checks it (lane offset + scalar offset against the buffer's
 size) and as the intrinsic promises it (the lane offset alone): by both, every byte that it may touch has to
 lie in the array or in the kOperandSlack bytes that the library allocates behind it. Buffer stores, and the
-loads of the result, must stay inside their own buffer by both. Values play
-no part: matrix products return their accumulator.
+loads of the result, must stay inside their own buffer by both, word by word
+with offsets of 32 bits. Values play no part: matrix products return their accumulator.
 """
 import os
 import shutil
@@ -72,10 +72,11 @@ inline B128 __builtin_amdgcn_raw_buffer_load_b128(Rsrc b, int lane, int scalar, 
 inline void word(Rsrc b, uint32_t lane, uint32_t scalar, int n) {   // n bytes of the result
     ++checked;
     const uint64_t sum = (uint64_t)lane + scalar;
-    if ((sum < b.num || lane < b.num) && sum + n > b.num) ++beyond;
+    if ((sum < b.num || lane < b.num) && (sum + n > b.num || (sum & 3))) ++beyond;
 }
 inline B64 __builtin_amdgcn_raw_buffer_load_b64(Rsrc b, int lane, int scalar, int) {
-    word(b, lane, scalar, 8);
+    word(b, lane, scalar, 4);
+    word(b, (uint32_t)lane + 4u, scalar, 4);
     return B64{0, 0};
 }
 template <class V> void __builtin_amdgcn_raw_buffer_store_b64(V, Rsrc b, int lane, int scalar, int) {
