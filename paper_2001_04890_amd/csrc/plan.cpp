@@ -898,7 +898,7 @@ void build_rs64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large,
     taken.assign(H.tasks.size(), 0);
     auto k16 = [](int k4) { return (k4 + 3) / 4; };
     auto cost = [&](const dmrg::LTask64& L, int tq) { return k16(L.kd4) * (4.0 * (k16(L.ka4) + tq) + 6.0) + 4.0; };
-    struct Run { int j, bucket, tq; int32_t tb, te; };
+    struct Run { int j, bucket, tq; int32_t tb, te; };   // bucket: kind of source and target, for the plan trace alone
     std::vector<dmrg::LTask64> lt;
     lt.reserve(H.tasks.size());
     std::vector<Run> runs;
@@ -925,7 +925,7 @@ void build_rs64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large,
         }
         for (int c = 0; c < 3; ++c) {
             if (v[c].empty()) continue;
-            Run R{(int)j, c == 2 ? 4 : 2 * c + (tq > 3), tq, (int32_t)lt.size(), 0};   // bucket: plan trace
+            Run R{(int)j, c == 2 ? 4 : 2 * c + (tq > 3), tq, (int32_t)lt.size(), 0};
             for (const auto& L : v[c]) {
                 lt.push_back(L);
                 caps.add((int)j, cost(L, tq));
@@ -1047,8 +1047,22 @@ void build_rs64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large,
         if (e[0] == '1') {
             std::fprintf(stderr, "[dmrg lds64 plan] items %zu classes", its.size());
             for (int c = 0; c < 5; ++c) std::fprintf(stderr, " %d", bucket[c]);
-            std::fprintf(stderr, " reduces %zu partial %.1f MB wavefronts", reds.size(), part * 8e-6);
-            for (int g = 0; g < dmrg::kRsGroups; ++g) std::fprintf(stderr, " %d", H.rplan64.begin[g + 1] - H.rplan64.begin[g]);
+            std::fprintf(stderr, " reduces %zu partial %.1f MB\n", reds.size(), part * 8e-6);
+            // what is launched: items by kernel class (8 k + q), wavefronts by launch group before and after joining
+            int cls[56] = {0}, own[dmrg::kRsGroups] = {0}, run[dmrg::kRsGroups] = {0};
+            for (const It& x : its) {
+                const int w = dmrg::rows_of(x.item.m_ap) / 16, g = own_group(x);
+                cls[x.cls]++;
+                own[g] += w;
+                run[group[g]] += w;
+            }
+            std::fprintf(stderr, "[dmrg rs64 plan] classes");
+            for (int c = 0; c < 56; ++c)
+                if (cls[c]) std::fprintf(stderr, " k%dq%d:%d", c / 8, c % 8, cls[c]);
+            std::fprintf(stderr, " own");
+            for (int n : own) std::fprintf(stderr, " %d", n);
+            std::fprintf(stderr, " launched");
+            for (int n : run) std::fprintf(stderr, " %d", n);
             std::fprintf(stderr, "\n");
         }
     HIPCHK(hipStreamSynchronize(s));
