@@ -145,6 +145,12 @@ void build_plan_core(dmrg_hop& H, hipStream_t s, const std::vector<char>* only, 
             }
         }
     }
+    if (only && dtasks.empty()) {                // the other paths run everything: no packed copy of x either
+        plan = dmrg::HpsiPlan{};
+        launches_out.clear();
+        phases_out.clear();
+        return;
+    }
     auto task_cost = [&](const dmrg::Task& T, int tp, int tq) -> double {
         double c = 8.0;                                   // per-task overhead
         if (T.a_off < 0 && T.b_off < 0) return c + 1.0;
@@ -386,7 +392,6 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
         }
         const int nrt = dmrg::rows_of(H.blk_ma[j]) / 16, tq = dmrg::rows_of(H.blk_md[j]) / 16;
         std::vector<dmrg::LTask> big, small;
-        int big_s = 32;
         std::vector<size_t> order;
         for (size_t t = kb; t < k; ++t)
             if (!fb_task[t]) order.push_back(t);
@@ -408,9 +413,8 @@ void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std
             L.pa32 = (int16_t)(pa / 32);
             L.pd32 = (int16_t)(pd / 32);
             if (L.pa32 == 1 && L.pd32 == 1 && H.tune_small_mode) small.push_back(L);
-            else { big.push_back(L); big_s = std::max({big_s, pa, pd}); }
+            else big.push_back(L);
         }
-        (void)big_s;
         if (!big.empty()) {
             // source and target columns within 64 -> S = 64 run, rest -> S = 96
             const int tp = nrt > dmrg::kLdsRows ? 2 : 1;
