@@ -219,8 +219,8 @@ dmrg_status dmrg_truncate(const double* rho, int32_t n_sec, const int32_t* dims,
                           int32_t* kept, double* evals, double* vecs, double* discarded);
 
 /* Eq. renorm_mat per sector block: out_b = O[sec_out[b]]^T A_b O[sec_in[b]] for n_blk operator blocks
- * given in an enlarged (untruncated) basis of n_sec sectors. FP64 on `device`, two passes (T = A O_in,
- * then O_out^T T), each element summed in a fixed order.
+ * given in an enlarged (untruncated) basis of n_sec sectors. FP64 on `device`, in one kernel (T = A O_in,
+ * then O_out^T T, T in on-chip memory), each element summed in a fixed order.
  * Host arrays: dims, kept (n_sec: sector dimension, kept states, 0 <= kept <= dims), o_off (n_sec:
  * offset of sector s's renormalization matrix in O), sec_out, sec_in (n_blk sector indices), a_off,
  * out_off (n_blk offsets). Device arrays: O (o_len doubles; sector s at o_off[s], row-major dims[s] x
@@ -229,7 +229,7 @@ dmrg_status dmrg_truncate(const double* rho, int32_t n_sec, const int32_t* dims,
  * row-major kept[sec_out] x kept[sec_in]; blocks must not overlap each other, A or O). Blocks with
  * nothing kept on a side are empty and skipped. Every index and extent is checked against the
  * lengths before launch. Synchronizes `stream` before returning (allocates and frees the
- * intermediate T). Errors: DMRG_ERR_ARG (NULL, negative counts, sector index, kept > dims),
+ * work list). Errors: DMRG_ERR_ARG (NULL, negative counts, sector index, kept > dims),
  * DMRG_ERR_SHAPE (a block outside its buffer), DMRG_ERR_UNSUPPORTED (block above 2^31 elements),
  * DMRG_ERR_DEVICE. */
 dmrg_status dmrg_renormalize_blocks(int32_t device, int32_t n_sec, const int32_t* dims, const int32_t* kept,
@@ -240,10 +240,11 @@ dmrg_status dmrg_renormalize_blocks(int32_t device, int32_t n_sec, const int32_t
 
 /* dmrg_renormalize_blocks for callers that cannot allocate device memory (code under stream
  * capture, serving loops, harnesses that forbid hipMalloc): same arguments, checks, kernels and
- * results (bit for bit), but the work list and the intermediate T = A O_in live in a fixed device
- * array of 64 MiB per GPU inside the library (held until the process ends) instead of fresh
- * allocations; the call allocates nothing. Limit: 256-byte-rounded work list (40 B per block that
- * keeps states on both sides) + 8 B x sum over those blocks of rows(sec_out) x kept(sec_in) must fit
+ * results (bit for bit), but the work list lives in a fixed device array of 48 MiB per GPU inside the
+ * library (held until the process ends) instead of a fresh allocation; the call allocates nothing.
+ * Limit (stated for a work list and an intermediate T = A O_in in one array of 64 MiB, and kept although T
+ * takes no device memory): 256-byte-rounded work list (56 B per block that keeps states on both sides) +
+ * 8 B x sum over those blocks of rows(sec_out) x kept(sec_in) must fit
  * in 64 MiB, else DMRG_ERR_NOMEM (nothing is launched). Every call on one GPU shares that GPU's
  * array: calls that overlap in time on the same GPU (other host threads or streams) race and must
  * be serialized by the caller. Synchronizes `stream` before returning. */

@@ -1,7 +1,7 @@
 // dmrg_renormalize_blocks_noalloc: Eq. renorm_mat per sector block (the work of
 // dmrg_renormalize_blocks, same kernels and summation order) for callers that cannot allocate device
-// memory. Its work list lives in one fixed device array, `scratch`,
-// of kScratchBytes per GPU, held until the process ends.
+// memory. Its work list lives in one fixed device array, `scratch`, of kArrayBytes per GPU, held until the
+// process ends. The limit that callers know, kLimitBytes, also counts T = A O_in, which the kernel keeps in LDS.
 //
 // `scratch` is a device symbol: its name in host code is a host-side stand-in, not a device address.
 // The first call on a device (with that device current) asks the runtime for the array's device
@@ -21,13 +21,14 @@ namespace {
 
 using dmrg::Error;
 
-constexpr size_t kScratchBytes = size_t(64) << 20;   // 64 MiB per GPU
+constexpr size_t kLimitBytes = size_t(64) << 20;     // of work list and T
 constexpr size_t kAlign = 256;
-constexpr size_t kListBytes = 56;                    // per block, in the limit (an item takes no more)
-static_assert(sizeof(dmrg::RenormItem) <= kListBytes, "work list within the limit");
+constexpr size_t kListBytes = 56;                    // per block, in the limit
+// The longest list within the limit: a block keeps states on both sides, so its T has at least one element.
+constexpr size_t kArrayBytes = kLimitBytes / (kListBytes + sizeof(double)) * sizeof(dmrg::RenormItem);   // 48 MiB
 constexpr int kMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kArrayBytes];
 
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
@@ -58,14 +59,13 @@ extern "C" dmrg_status dmrg_renormalize_blocks_noalloc(int32_t device, int32_t n
         const dmrg::RenormWork wk = dmrg::renorm_work(n_sec, dims, kept, o_off, O, o_len, n_blk, sec_out, sec_in,
                                                       a_off, A, a_len, out_off, out, out_len);
         if (wk.items.empty()) return DMRG_OK;
-        // the documented limit counts [items | pad to 256 B | T = A O_in]; the kernel keeps T in LDS, so
-        // only the items are written
+        // the limit counts [items | pad to 256 B | T]; only the items are written
         const size_t items_bytes = wk.items.size() * sizeof(dmrg::RenormItem);
         const size_t t_at = (wk.items.size() * kListBytes + kAlign - 1) / kAlign * kAlign;
-        if ((uint64_t)wk.t_len > (kScratchBytes - std::min(kScratchBytes, t_at)) / sizeof(double))
+        if ((uint64_t)wk.t_len > (kLimitBytes - std::min(kLimitBytes, t_at)) / sizeof(double))
             throw Error(DMRG_ERR_NOMEM, "work list + intermediate (" + std::to_string(t_at + wk.t_len * sizeof(double)) +
-                                            " bytes) exceed the fixed scratch of " +
-                                            std::to_string(kScratchBytes) + " bytes");
+                                            " bytes) exceed the fixed scratch limit of " +
+                                            std::to_string(kLimitBytes) + " bytes");
         HIPCHK(hipSetDevice(device));
         unsigned char* base = scratch_on(device);
         hipStream_t s = (hipStream_t)stream;
