@@ -1074,7 +1074,7 @@ void build_rs64_plan(dmrg_hop& H, hipStream_t s, const std::vector<char>& large,
 
 }  // namespace
 
-// Every launch plan of the handle: FP64 (all targets) and, with split operators, the LDS-staged
+// Every launch plan of the handle: FP64 (all targets) and, with split operators, the row-mode and task-mode
 // plan plus the plans for the targets it does not cover.
 void build_plan(dmrg_hop& H, hipStream_t s) {
     drop_graphs(H);
@@ -1091,7 +1091,14 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
     const size_t nb = H.blk.size();
     std::vector<char> big64(nb, 0), rs64;   // targets of the two-pass path; tasks of the register-streamed kernel
     bool any_big = false, any_rs = false;
-    if (H.tune_lds64 || H.tune_big64) {
+    if (H.tune_big64) {
+        // Every target above the limit: with tiles cut to the block no extent is too small for the two-pass
+        // path. 76 orbitals at bond dimension 6000 (one share): 25.3 ms; 30.4 ms when the few percent of the
+        // work in targets within 128 x 128 with a larger source ran on the one-wavefront kernel.
+        big64 = large_targets(H, H.tune_lds64 ? 16 * dmrg::kRsMaxTiles : 96);
+        for (char b : big64) any_big |= b != 0;
+    }
+    if (H.tune_lds64 || any_big) {
         make_op64(H, s);
         build_pack64(H, s);
     }
@@ -1103,13 +1110,6 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
             for (size_t j = 0; j < nb; ++j) large[j] = std::max(H.blk_ma[j], H.blk_md[j]) > 16 * dmrg::kRsMaxTiles;
         build_rs64_plan(H, s, large, rs64);
         for (char b : rs64) any_rs |= b != 0;
-    }
-    if (H.tune_big64) {
-        // Every target above the limit: with tiles cut to the block no extent is too small for the two-pass
-        // path. 76 orbitals at bond dimension 6000 (one share): 25.3 ms; 30.4 ms when the few percent of the
-        // work in targets within 128 x 128 with a larger source ran on the one-wavefront kernel.
-        big64 = large_targets(H, H.tune_lds64 ? 16 * dmrg::kRsMaxTiles : 96);
-        for (char b : big64) any_big |= b != 0;
     }
     if (any_big || any_rs) {
         std::vector<char> rest(nb), rest_tasks(H.tasks.size(), 1);
@@ -1140,8 +1140,8 @@ void build_plan(dmrg_hop& H, hipStream_t s) {
 }
 
 
-// True when some target block (or one of its sources) has a padded dimension above the LDS stage
-// size of the LDS-staged split kernel.
+// True when some target block (or one of its sources) has a dimension above the 96 of the split row-mode
+// kernel.
 bool needs_fallback(const dmrg_hop& H) {
     for (char b : large_targets(H)) if (b) return true;
     return false;

@@ -3,6 +3,7 @@ has none, and its H.psi is that of a plan with the copy (single-tile sources in 
 1e-13 of max|y| (summation order only). Read from the plan trace, which names the copy's size.
 """
 import os
+import re
 
 import pytest
 
@@ -44,3 +45,27 @@ def test_no_padded_copy_without_one_wavefront_tasks(L, M, capfd):
     y1, copy1 = run(p, {"DMRG_LDS64_SMALL": "0"}, capfd)
     assert not copy and copy1
     assert rel_err(y, y1) < 1e-13
+
+
+def test_no_operand_pool_without_its_kernels(capfd):
+    """With the register-streamed kernel off and no sector above 96 nothing reads the FP64 operand pool: the handle's
+    device data is less than with it."""
+    p = synth(12, 150, 0.8, 5)
+    data = []
+    for env in ({}, {"DMRG_LDS64": "0"}):
+        old = os.environ.get("DMRG_LDS64")
+        os.environ.update(env, DMRG_BUILD_TRACE="1")
+        try:
+            capfd.readouterr()
+            hop = lib_mod.Hop(*p, device=0)
+            err = capfd.readouterr().err
+        finally:
+            os.environ.pop("DMRG_BUILD_TRACE")
+            if env:
+                os.environ.pop("DMRG_LDS64")
+                if old is not None:
+                    os.environ["DMRG_LDS64"] = old
+        assert int(hop.dims.max()) <= 96
+        data.append(float(re.findall(r"device memory: ([\d.]+) MB data", err)[-1]))
+    print(f"[plan memory] {data}", flush=True)
+    assert data[1] < data[0]
