@@ -26,14 +26,14 @@ sys.path.insert(0, ROOT)
 PEAK = {"fp64": 78.6, "bf16": 2500.0}   # MI355X dense MFMA TFLOP/s
 HBM_PEAK = 8000.0                        # GB/s
 # HBM traffic of one H.psi call at L=24 M=1024 (seed 1), from rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE
-# over the launches of one call, FETCH_SIZE scaled by 2.0 and WRITE_SIZE by 1.0 (factors read off a
-# 1 GiB device copy in the same runs). Valid for these operators and these kernels only; summaries and
-# commands in profiles/hpsi_L24_M1024_swept_kernel_trace.md and
-# profiles/hpsi_{fp64,split}_L24_M1024_synthetic_kernel_trace.md.
+# over the launches of one call, FETCH_SIZE scaled by 2.0 (it takes every read request for 64 bytes, and nearly
+# all are of 128) and WRITE_SIZE by 1.0, as a 1 GiB device copy in the same runs shows. Valid for these
+# operators and these kernels only; summaries and commands in profiles/hpsi_kernels_counters.md.
 TRAFFIC_L24_M1024 = {
-    # counters taken with earlier kernels are not reported
-    "synthetic": {"fp64": None, "split": None},
-    "swept": {"fp64": None, "split": None},
+    "synthetic": {"fp64": {"fetch_bytes": 23378.0 * 2**20, "write_bytes": 630.0 * 2**20},
+                  "split": {"fetch_bytes": 21110.0 * 2**20, "write_bytes": 376.0 * 2**20}},
+    "swept": {"fp64": {"fetch_bytes": 23444.0 * 2**20, "write_bytes": 981.0 * 2**20},
+              "split": {"fetch_bytes": 15565.0 * 2**20, "write_bytes": 3032.0 * 2**20}},
 }
 
 

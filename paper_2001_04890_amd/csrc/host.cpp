@@ -1191,9 +1191,8 @@ extern "C" dmrg_status dmrg_hop_autotune(dmrg_hop* H, int32_t precision, int32_t
         HIPCHK(hipEventCreate(&e0));
         HIPCHK(hipEventCreate(&e1));
         // The plan's settings, each with its candidate values (the current value is measured first).
-        // Split: LDS item count and launch order, the task-mode tile (row tiles x column tiles per
-        // wavefront: 1 x 2 / 2 x 2 / 1 x 4), the 64-wide stage classes, the six-wavefront (S, 2)
-        // classes, the copy and prefetch wavefronts. FP64: the register-streamed kernel's item count and
+        // Split: item count and launch order, the task-mode tile (row tiles x column tiles per wavefront:
+        // 1 x 2 / 2 x 2 / 1 x 4), the 64-wide classes. FP64: the register-streamed kernel's item count and
         // single-tile sources, the two-pass routing of large targets, and the one-wavefront kernel's tile
         // width, item count and launch order.
         struct Knob { int* field; std::vector<int> cand; };
@@ -1206,11 +1205,11 @@ extern "C" dmrg_status dmrg_hop_autotune(dmrg_hop* H, int32_t precision, int32_t
             knobs.push_back({&H->tune_lds_order, H->n_parts > 1 ? std::vector<int>{0, 1, 2} : std::vector<int>{0, 1}});
             knobs.push_back({&small_shape, {0, 1, 2}});
             knobs.push_back({&H->tune_lds_split64, {1, 0}});
-            for (int i = 0; i < 3; ++i) knobs.push_back({&none, {}});   // (wavefront roles of the LDS-staged kernel it replaced)
+            for (int i = 0; i < 3; ++i) knobs.push_back({&none, {}});   // (wavefront roles of an earlier kernel)
         } else {
             const bool lds64 = H->tune_lds64 != 0;   // the register-streamed kernel
             knobs.push_back({&H->tune_lds64_items, lds64 ? std::vector<int>{8192, 16384, 32768, 65536} : std::vector<int>{}});
-            knobs.push_back({&one, {}});          // (the copy wavefront of the LDS-staged kernel it replaced)
+            knobs.push_back({&one, {}});          // (the copy wavefront of an earlier kernel)
             knobs.push_back({&H->tune_lds64_small, lds64 ? std::vector<int>{1, 0} : std::vector<int>{}});
             knobs.push_back({&one, {}});          // (that kernel's register cap)
             knobs.push_back({&H->tune_big64, {1}});

@@ -11,10 +11,11 @@
 // them in the vector cache. LDS holds the FP64 sums, which leaves the registers to the operands.
 // Operands are stored pre-tiled in fragment order (internal.h): every load is a contiguous 1 KB.
 //
-// What bounds it: the traffic between the L2s and the last-level cache (6.1 .. 6.5 TB/s in the row-mode launches
-// of 24 orbitals at bond dimension 1024; an operator block is read once per target that uses it). That
-// problem's matvec takes 3.63 ms; 4.55 ms when the X^T and B of one workgroup per CU were staged in LDS, with a
-// barrier per task and the matrix cores busy 13 .. 21% of the time.
+// What bounds it: the traffic between the L2s and the memory behind them (24 orbitals at bond dimension 1024: 10 GB
+// read in the row-mode launches, 6.0 .. 6.4 TB/s in three of the four; an operator block is read once per target
+// that uses it), with the 1.5 (S = 96) to 2.5 (S = 64) wavefronts per SIMD that the sums in LDS leave room for.
+// That problem's matvec takes 3.63 ms; 4.55 ms when the X^T and B of one workgroup per CU were staged in LDS, with
+// a barrier per task and the matrix cores busy 13 .. 21% of the time.
 //
 // Precision: each product a.b is a_hi b_hi + a_hi b_lo + a_lo b_hi on v_mfma_f32_16x16x32_bf16 with
 // FP32 accumulation; T' is scaled by f and re-split; task results are accumulated in FP32 over at

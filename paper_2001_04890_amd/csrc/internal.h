@@ -159,8 +159,9 @@ struct HpsiPlan {
 // block of NR row tiles and at most NQ column tiles), classes (NR, NQ) = (1,2) (2,2) (1,4), launched
 // after the row-mode classes; items[small_begin[c] .. small_begin[c+1]).
 // Row-mode classes (64,2) (64,3) (96,2) (96,3): a target's tasks whose source and columns are within 64
-// run in the S = 64 classes (fewer registers, three wavefronts per SIMD), the other big-source tasks in the
-// S = 96 classes; targets of up to kLdsRows row tiles have two wavefronts, the others three.
+// run in the S = 64 classes, the other big-source tasks in the S = 96 classes; targets of up to kLdsRows row
+// tiles have two wavefronts, the others three. The FP64 sums in LDS bound the wavefronts of a CU: 16 KB each
+// at S = 64, so 10 (two a workgroup) or 9 (three), 24 KB at S = 96, so 6; the registers would allow 12 and 8.
 constexpr int kLdsRows = 4;
 constexpr int kLdsClasses = 4;
 constexpr int kSmallClasses = 3;

@@ -339,7 +339,7 @@ void build_plan_core(dmrg_hop& H, hipStream_t s, const std::vector<char>* only, 
 // covered by several items of one kind gets partial tiles that a reduction adds in item order.
 // Targets with larger blocks (own, or every source with tune_split_task_route = 0) are flagged in
 // `fallback`, and with them the tasks in `fb_task`: those the other paths (two-pass or one-wave) run.
-// With tune_split_task_route, a target within the stages keeps its tasks whose source fits them too
+// With tune_split_task_route, a target within 96 keeps its tasks whose source is within 96 too
 // and only those with a larger source fall back, so one target can take both paths (each adds into y).
 void build_lds_plan(dmrg_hop& H, hipStream_t s, std::vector<char>& fallback, std::vector<char>& fb_task) {
     const size_t nb = H.blk.size();

@@ -27,7 +27,7 @@ T* dev_alloc(dmrg_hop& H, size_t n) {
 void build_plan(dmrg_hop& H, hipStream_t s);
 // Destroys the handle's cached H.psi graphs.
 void drop_graphs(dmrg_hop& H);
-// True when some target block (or one of its sources) is wider than the split LDS stages.
+// True when some target block (or one of its sources) is above the 96 of the split row-mode kernel.
 bool needs_fallback(const dmrg_hop& H);
 // Tiled split-BF16 copy of the handle's operator pool (and identity blocks).
 void make_tiled_split(dmrg_hop& H, hipStream_t s);
