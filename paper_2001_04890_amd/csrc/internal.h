@@ -330,14 +330,16 @@ hipError_t launch_rdm(bool right, const RdmItem* items, const RdmUnit* units, in
                       const int32_t* cdmd, const double* psi, double* rho, hipStream_t s);
 
 // Eq. renorm_mat per sector block, out = O_out^T A O_in (renorm.hip). A is rows x cols (= O_out rows x
-// O_in rows), row-major; O matrices are row-major (rows x k). max_in / max_out: most columns of O_in /
-// O_out of one item.
+// O_in rows), row-major; O matrices are row-major (rows x k). The first n_large items have a workgroup or
+// more each, max_in / max_out: most columns of O_in / O_out of one of them; the n_small others, for which
+// renorm_small holds, a wavefront.
 struct RenormItem {
     int64_t a_off, out_off, oo_off, oi_off;
     int32_t rows, cols, k_out, k_in;
 };
-hipError_t launch_renormalize(const RenormItem* items, int n_items, int max_in, int max_out, const double* A, const double* O,
-                              double* out, hipStream_t s);
+inline bool renorm_small(const RenormItem& it) { return it.rows <= 32 && it.k_in <= 32; }
+hipError_t launch_renormalize(const RenormItem* items, int n_large, int n_small, int max_in, int max_out, const double* A,
+                              const double* O, double* out, hipStream_t s);
 // Tiled split-BF16 kernels (hpsi_lds.hip).
 hipError_t launch_split_tiled(const double* pool, const PoolBlock* blocks, int n_blocks, uint16_t* tiled, hipStream_t s);
 // y (+)= H x over the LDS plan's targets; zero_y: clear y first (else accumulate into it).

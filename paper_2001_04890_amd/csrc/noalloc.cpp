@@ -72,7 +72,7 @@ extern "C" dmrg_status dmrg_renormalize_blocks_noalloc(int32_t device, int32_t n
         auto* d_items = reinterpret_cast<dmrg::RenormItem*>(base);
         try {
             HIPCHK(hipMemcpyAsync(d_items, wk.items.data(), items_bytes, hipMemcpyHostToDevice, s));
-            HIPCHK(dmrg::launch_renormalize(d_items, (int)wk.items.size(), wk.max_in, wk.max_out, A, O, out, s));
+            HIPCHK(dmrg::launch_renormalize(d_items, wk.n_large(), wk.n_small, wk.max_in, wk.max_out, A, O, out, s));
             HIPCHK(hipStreamSynchronize(s));   // the host work list is read by the copy until here
         } catch (...) {
             (void)hipStreamSynchronize(s);

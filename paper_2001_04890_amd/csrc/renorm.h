@@ -8,11 +8,14 @@
 namespace dmrg {
 
 // Work list of Eq. renorm_mat per sector block (out = O_out^T A O_in): one item per block that keeps
-// states on both sides, longest first; t_len: elements of T = A O_in over all items (the scratch limit of
-// dmrg_renormalize_blocks_noalloc is stated in them; the kernel keeps T in LDS).
+// states on both sides, of many small ones (renorm_small) these last, of the others the longest first;
+// t_len: elements of T = A O_in over all items (the scratch limit of dmrg_renormalize_blocks_noalloc is
+// stated in them; the kernels keep T on the chip).
 struct RenormWork {
     std::vector<RenormItem> items;
-    int max_in = 0, max_out = 0;                 // most columns of O_in, O_out of one item
+    int n_small = 0;                             // items of their own launch
+    int max_in = 0, max_out = 0;                 // most columns of O_in, O_out of one of the others
+    int n_large() const { return (int)items.size() - n_small; }
     int64_t t_len = 0;
 };
 

@@ -232,11 +232,77 @@ __global__ __launch_bounds__(256) void k_renorm(const RenormItem* __restrict__ i
         }
 }
 
-hipError_t launch_renormalize(const RenormItem* items, int n_items, int max_in, int max_out, const double* A, const double* O,
-                              double* out, hipStream_t s) {
-    if (n_items <= 0) return hipSuccess;
-    const dim3 grid((unsigned)n_items, (unsigned)((max_in + 31) / 32), (unsigned)((max_out + 255) / 256));
-    hipLaunchKernelGGL(k_renorm, grid, dim3(256), 0, s, items, A, O, out);
+// The same for a block of at most 32 rows and 32 kept states, by one wavefront: T stays in the registers in which
+// the first product leaves it, which are the second one's operand, so there is no LDS and no barrier, and 16 blocks
+// run on a CU, 2 of k_renorm. The sums are those of k_renorm. Bound by the latency of each block's loads (operators
+// of a few dozen states are thousands of such blocks): 20,000 blocks of 9 -> 5 states take 19 us, 133 us when each had
+// a workgroup of k_renorm.
+__global__ __launch_bounds__(256) void k_renorm_small(const RenormItem* __restrict__ items, int n_items,
+                                                      const double* __restrict__ A, const double* __restrict__ O,
+                                                      double* __restrict__ out) {
+    const int w = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    if (w >= n_items) return;
+    const RenormItem it = items[w];
+    const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+    const double *a = A + it.a_off, *oi = O + it.oi_off, *oo = O + it.oo_off;
+    const bool r2 = it.rows > 16, c2 = it.k_in > 16;           // the second tile of rows / columns holds data
+    const double* a0 = a + (int64_t)min(li, it.rows - 1) * it.cols;
+    const double* a1 = a + (int64_t)min(16 + li, it.rows - 1) * it.cols;
+    const int j0 = min(li, it.k_in - 1), j1 = min(16 + li, it.k_in - 1);
+    const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+    f64x4 tt[2][2] = {{zero, zero}, {zero, zero}};
+    for (int b = 0; b < it.cols; b += 16) {
+        const f64x4 x0 = row4(a0, b + g, it.cols), x1 = r2 ? row4(a1, b + g, it.cols) : zero;
+        const f64x4 y0 = col4(oi, b + g, it.cols, it.k_in, j0), y1 = c2 ? col4(oi, b + g, it.cols, it.k_in, j1) : zero;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            tt[0][0] = mfma(x0[v], y0[v], tt[0][0]);
+            if (c2) tt[0][1] = mfma(x0[v], y1[v], tt[0][1]);
+            if (r2) tt[1][0] = mfma(x1[v], y0[v], tt[1][0]);
+            if (r2 && c2) tt[1][1] = mfma(x1[v], y1[v], tt[1][1]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const bool in = 16 * q + g + 4 * v < it.rows;      // rows past the block enter the second product as zeros
+            tt[q][0][v] = in ? tt[q][0][v] : 0.0;
+            tt[q][1][v] = in ? tt[q][1][v] : 0.0;
+        }
+    for (int o = 0; o < it.k_out; o += 16) {
+        const int i = min(o + li, it.k_out - 1);
+        f64x4 acc[2] = {zero, zero};
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (q == 0 || r2) {
+                const f64x4 x = col4(oo, 16 * q + g, it.rows, it.k_out, i);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    acc[0] = mfma(x[v], tt[q][0][v], acc[0]);
+                    if (c2) acc[1] = mfma(x[v], tt[q][1][v], acc[1]);
+                }
+            }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = o + g + 4 * v;
+            if (row < it.k_out) {
+                double* to = out + it.out_off + (int64_t)row * it.k_in;
+                if (li < it.k_in) to[li] = acc[0][v];
+                if (16 + li < it.k_in) to[16 + li] = acc[1][v];
+            }
+        }
+    }
+}
+
+hipError_t launch_renormalize(const RenormItem* items, int n_large, int n_small, int max_in, int max_out, const double* A,
+                              const double* O, double* out, hipStream_t s) {
+    if (n_large > 0) {
+        const dim3 grid((unsigned)n_large, (unsigned)((max_in + 31) / 32), (unsigned)((max_out + 255) / 256));
+        hipLaunchKernelGGL(k_renorm, grid, dim3(256), 0, s, items, A, O, out);
+    }
+    if (n_small > 0)
+        hipLaunchKernelGGL(k_renorm_small, dim3((unsigned)((n_small + 3) / 4)), dim3(256), 0, s, items + n_large, n_small, A, O, out);
     return hipGetLastError();
 }
 

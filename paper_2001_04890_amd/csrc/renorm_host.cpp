@@ -335,14 +335,28 @@ dmrg::RenormWork dmrg::renorm_work(int32_t n_sec, const int32_t* dims, const int
         it.k_out = (int32_t)ko;
         it.k_in = (int32_t)ki;
         w.items.push_back(it);
-        w.max_in = std::max(w.max_in, it.k_in);
-        w.max_out = std::max(w.max_out, it.k_out);
+        w.n_small += dmrg::renorm_small(it);
         w.t_len += rows * ki;
     }
     if (w.items.size() > (size_t)INT32_MAX) throw Error(DMRG_ERR_UNSUPPORTED, "too many blocks");
-    std::sort(w.items.begin(), w.items.end(), [](const RenormItem& x, const RenormItem& y) {
-        return (int64_t)x.rows * (x.cols + x.k_out) > (int64_t)y.rows * (y.cols + y.k_out);
-    });
+    // As long as there is a place on the chip for a workgroup of k_renorm each (two per CU), small blocks run beside
+    // the others in one launch. 500 blocks of 9 -> 5 states: 54 us a call; 700: 62 us so, 54 apart.
+    constexpr int kApart = 512;
+    if (w.n_small <= kApart) w.n_small = 0;
+    else std::partition(w.items.begin(), w.items.end(), [](const RenormItem& x) { return !dmrg::renorm_small(x); });
+    const auto large = w.items.begin() + w.n_large();
+    auto work = [](const RenormItem& x) { return (int64_t)x.rows * (x.cols + x.k_out); };
+    int64_t total = 0;
+    for (auto it = w.items.begin(); it != large; ++it) {
+        w.max_in = std::max(w.max_in, it->k_in);
+        w.max_out = std::max(w.max_out, it->k_out);
+        total += work(*it);
+    }
+    // A long item that starts late ends the launch late, by its own length at most: the fewer than 4096 items that
+    // have more than a 4096th of the work go first, in order. (Sorting all took 0.6 ms of 20,000 blocks of 1 .. 40
+    // states, whose kernel takes 0.1.)
+    const auto some = std::partition(w.items.begin(), large, [&](const RenormItem& x) { return work(x) > total / 4096; });
+    std::sort(w.items.begin(), some, [&](const RenormItem& x, const RenormItem& y) { return work(x) > work(y); });
     return w;
 }
 
@@ -362,7 +376,7 @@ extern "C" dmrg_status dmrg_renormalize_blocks(int32_t device, int32_t n_sec, co
         try {
             HIPCHK(hipMalloc((void**)&d, wk.items.size() * sizeof(RenormItem)));
             HIPCHK(hipMemcpyAsync(d, wk.items.data(), wk.items.size() * sizeof(RenormItem), hipMemcpyHostToDevice, s));
-            HIPCHK(dmrg::launch_renormalize(d, (int)wk.items.size(), wk.max_in, wk.max_out, A, O, out, s));
+            HIPCHK(dmrg::launch_renormalize(d, wk.n_large(), wk.n_small, wk.max_in, wk.max_out, A, O, out, s));
             HIPCHK(hipStreamSynchronize(s));   // the work list ends here
         } catch (...) {
             (void)hipStreamSynchronize(s);
