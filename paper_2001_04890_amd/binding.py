@@ -24,7 +24,8 @@ DMRG_NOT_CONVERGED = 1
 PREC_FP64 = 0
 PREC_SPLIT2 = 1
 
-# dmrg_hop_autotune: settings reported in `chosen`, in order (DMRG_AUTOTUNE_KNOBS entries)
+# dmrg_hop_autotune: settings reported in `chosen`, in order (DMRG_AUTOTUNE_KNOBS entries); six_wave, copy_wave,
+# prefetch, lds64_copy_wave and lds64_w7_cap are of earlier kernels and keep their places with fixed values
 AUTOTUNE_KNOBS = 8
 _AUTOTUNE_SPLIT = ("lds_items", "lds_order", "small_shape", "split64", "six_wave", "copy_wave", "prefetch")
 _AUTOTUNE_FP64 = ("lds64_items", "lds64_copy_wave", "lds64_small", "lds64_w7_cap", "big64", "max_tq", "items",
