@@ -219,8 +219,8 @@ dmrg_status dmrg_truncate(const double* rho, int32_t n_sec, const int32_t* dims,
                           int32_t* kept, double* evals, double* vecs, double* discarded);
 
 /* Eq. renorm_mat per sector block: out_b = O[sec_out[b]]^T A_b O[sec_in[b]] for n_blk operator blocks
- * given in an enlarged (untruncated) basis of n_sec sectors. FP64 on `device`, in one kernel (T = A O_in,
- * then O_out^T T, T in on-chip memory), each element summed in a fixed order.
+ * given in an enlarged (untruncated) basis of n_sec sectors. FP64 on `device`: T = A O_in, then
+ * O_out^T T, with T kept on the chip, each element summed in a fixed order.
  * Host arrays: dims, kept (n_sec: sector dimension, kept states, 0 <= kept <= dims), o_off (n_sec:
  * offset of sector s's renormalization matrix in O), sec_out, sec_in (n_blk sector indices), a_off,
  * out_off (n_blk offsets). Device arrays: O (o_len doubles; sector s at o_off[s], row-major dims[s] x
